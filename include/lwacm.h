@@ -179,9 +179,10 @@ int lwacm_set_variant(lwacm_ctx *c, int variant);
 
 /* Planes per workgroup of the forward D3Q19 tile kernel: 32, 64 or 128
  * (LWACM_EINVAL otherwise; LWACM_EUNSUPPORTED if the tile kernel cannot run
- * this problem).  lwacm_init picks the depth that minimises the plane steps
- * per compute unit, ceil(workgroups / CUs) * (depth + 2); this call
- * overrides it (tuning, tests).  Results do not depend on the depth. */
+ * this problem).  lwacm_init picks the depth (any number of planes from 8 on)
+ * that minimises the plane steps per compute unit, ceil(workgroups / CUs) *
+ * (depth + 10); this call overrides it (tuning, tests).  Results do not
+ * depend on the depth. */
 int lwacm_set_march_chunk(lwacm_ctx *c, int planes);
 
 /* Separate relaxation frequency omega_p of the continuity (density) update
@@ -441,9 +442,7 @@ int lwacm_adjoint_step(lwacm_ctx *c, const void *d_state_t, const float *d_mu_in
  * grids without walls, nz >= 8; variant AUTO or MARCH2): the same result as
  *     lwacm_adjoint_step(c, d_state_t,   d_mu_in, tmp,      w, 0);
  *     lwacm_adjoint_step(c, d_state_tm1, tmp,     d_mu_out, w, final_t0);
- * (bitwise in d_mu_out; *d_dL_domega receives the same two additions where
- * both kernels split the planes among workgroups alike, nz <= 64, else the
- * same sums grouped by 128-plane chunks: equal to FP64 rounding) with
+ * (bitwise in d_mu_out, and the same two additions to *d_dL_domega) with
  * the intermediate mu kept on chip: 32 instead of 48 bytes of HBM per node
  * and step.  d_state_t and d_state_tm1 are the inputs of forward steps t and
  * t - 1 (storage format); d_mu_in = mu_t, node-interleaved.  final_t0: the

@@ -5,7 +5,7 @@
 // differentiated) is in lwacm_adjoint_common.hpp.
 //
 // Design (gfx950).  A workgroup owns a 32 x 16 tile of columns and a chunk of
-// 64 planes, as the forward march kernel.  Every plane of mu (tile plus a
+// planes, as the forward march kernel.  Every plane of mu (tile plus a
 // one-column halo ring) passes once through a rolling window of four LDS
 // planes, its four components in separate arrays; each interior thread then reads its 18
 // neighbours' mu from the three planes around its own, accumulates the ten
@@ -15,22 +15,22 @@
 // One barrier per plane; four window planes mean a plane is overwritten only
 // after every thread has passed the next barrier.  HBM traffic per node:
 // state + mu_in + mu_out = 48 B (FP32 state).
+//
+// The plane loop is rolled (plane_loop), so the chunk depth is a run-time
+// value and a ragged last chunk is moved down to end at nz, as in the other
+// tile kernels: its planes below zs are written twice with the same bits and
+// counted once.  Every load and store is unconditional and a ring slot is
+// refilled after its last use, so the loads stay in flight across the back
+// edge.
 #include "lwacm_adjoint_common.hpp"
 
 namespace lwacm {
 
 namespace {
 
-#ifndef LWACM_ADJ_NZC
-#define LWACM_ADJ_NZC 64
-#endif
-#ifndef LWACM_ADJ_RING
-#define LWACM_ADJ_RING 2
-#endif
 constexpr int TX = 32;
 constexpr int TY = 16;
-constexpr int NZC = LWACM_ADJ_NZC;          // planes per workgroup
-constexpr int RING = LWACM_ADJ_RING;        // planes of loads in flight per thread
+constexpr int RING = 3;                     // planes of loads in flight per thread
 constexpr int NWIN = 4;                     // LDS window planes
 constexpr int NINT = TX * TY;
 constexpr int NTHREADS = NINT + 2 * kWave;  // + Y-halo wave + X-halo wave
@@ -41,15 +41,17 @@ static_assert(2 * TX <= kWave && 2 * (TY + 2) <= kWave, "halo rows must fit one 
 
 enum Role { INTERIOR = 0, HALO_Y = 1, HALO_X = 2 };
 
-template <class T, bool MASK>
-__global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, const T *__restrict__ state,
+template <class T, int TAIL, bool MASK, bool FINAL>
+__global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, int nzc,
+                                                        const T *__restrict__ state,
                                                         const float *__restrict__ mu_in,
                                                         float *__restrict__ mu_out,
                                                         const unsigned *__restrict__ bb_bits,
                                                         const float4 *__restrict__ wallg,
-                                                        int final_t0, ReduceArgs r)
+                                                        ReduceArgs r)
 {
-    __shared__ float win[NWIN][4][NSLOT];
+    // one spare slot: idle halo lanes write there instead of branching
+    __shared__ float win[NWIN][4][NSLOT + 1];
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -57,17 +59,9 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, const T *
     const long long n = p.n;
     const long long plane = (long long)nx * ny;
 
-    const unsigned nb = gridDim.x;
-    const unsigned b = blockIdx.x;
-    const unsigned lb = (nb % 8u == 0u) ? (b % 8u) * (nb / 8u) + b / 8u : b;
-    const int tiles_x = nx / TX;
-    const int tiles_y = ny / TY;
-    const int tile_x = (int)(lb % (unsigned)tiles_x);
-    const unsigned rest = lb / (unsigned)tiles_x;
-    const int tile_y = (int)(rest % (unsigned)tiles_y);
-    const int zc = (int)(rest / (unsigned)tiles_y);
-    const int z0 = zc * NZC;
-    const int z1 = min(z0 + NZC, nz);
+    const TileIdx ti = tile_of_block(nx, ny, TX, TY);
+    const int zs = ti.zc * nzc;
+    const int z0 = min(zs, nz - nzc);
 
     // column in tile coordinates [-1, TX] x [-1, TY]
     const int role = tid < NINT ? INTERIOR : (tid < NINT + kWave ? HALO_Y : HALO_X);
@@ -90,97 +84,124 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, const T *
         active = lane < 2 * (TY + 2);
         if (!active) ly = 0;
     }
-    int gx = tile_x * TX + lx;
-    int gy = tile_y * TY + ly;
-    gx = gx < 0 ? gx + nx : (gx >= nx ? gx - nx : gx);
-    gy = gy < 0 ? gy + ny : (gy >= ny ? gy - ny : gy);
+    const int gx = wrap_index(ti.tile_x * TX + lx, nx);
+    const int gy = wrap_index(ti.tile_y * TY + ly, ny);
     const unsigned col = (unsigned)(gy * nx + gx);
     const int slot = (ly + 1) * SX + (lx + 1);
+    const int wslot = active ? slot : NSLOT;
 
-    auto wrapz = [&](int pz) { return pz < 0 ? pz + nz : (pz >= nz ? pz - nz : pz); };
+    auto wrapz = [&](int pz) { return wrap_index(pz, nz); };
+    constexpr unsigned NB = StateIO<T>::kNodeBytes;
     const Rsrc rmu = make_rsrc(mu_in, (unsigned long long)n * 16u);
-    const Rsrc rst = make_rsrc(state, (unsigned long long)n * StateIO<T>::kNodeBytes);
+    const Rsrc rst = make_rsrc(state, (unsigned long long)n * NB);
+    const Rsrc rout = make_rsrc(mu_out, (unsigned long long)n * 16u);
+    const Rsrc rbits = make_rsrc(bb_bits, MASK ? (unsigned long long)n * 4u : 0ull);
     const unsigned mu_plane = (unsigned)(plane * 16);
-    const unsigned st_plane = (unsigned)(plane * StateIO<T>::kNodeBytes);
+    const unsigned st_plane = (unsigned)(plane * NB);
     const unsigned voff_mu = col * 16u;
-    const unsigned voff_st = col * StateIO<T>::kNodeBytes;
+    const unsigned voff_st = col * NB;
 
-    // ring of loads: mu of plane pz (every thread) and the state of plane pz
-    // (interior threads; finalised one iteration later)
-    f32x4 rmu_ring[RING];
-    typename StateIO<T>::Raw rst_ring[RING];
+    // Load rings, indexed by k % 3 at compile time: mu of plane pz = z0 - 1 + k
+    // is in mr[k % 3] at iteration k, the state (and, with MASK, the link set)
+    // of the plane finalised there, pz - 1, in sr[(k + 2) % 3].
+    f32x4 mr[RING];
+    typename StateIO<T>::Raw sr[RING];
+    unsigned bw[RING] = {0u, 0u, 0u};
+    auto load_state = [&](int j, int pz) {
+        const unsigned pw = (unsigned)wrapz(pz);
+        sr[j] = StateIO<T>::load(rst, voff_st, pw * st_plane);
+        if (MASK)
+            bw[j] = __builtin_amdgcn_raw_buffer_load_b32(rbits, col * 4u, pw * (unsigned)(plane * 4),
+                                                         0);
+    };
 #pragma unroll
-    for (int j = 0; j < RING; ++j) {
-        const int pz = wrapz(min(z0 - 1 + j, z1));
-        rmu_ring[j] = load_f4(rmu, voff_mu, (unsigned)pz * mu_plane);
-        if (role == INTERIOR) rst_ring[j] = StateIO<T>::load(rst, voff_st, (unsigned)pz * st_plane);
+    for (int j = 0; j < RING; ++j) mr[j] = load_f4(rmu, voff_mu, (unsigned)wrapz(z0 - 1 + j) * mu_plane);
+    if (role == INTERIOR) {
+        load_state(1, z0);
+        load_state(2, z0 + 1);
+        load_state(0, z0 + 2);
     }
 
     float da = 0.0f;
-    float own_st[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // state of the plane finalised next
+    const int N = nzc + 2;  // planes z0 - 1 .. z1 of mu
 
-    static_for<NZC + 2>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        constexpr int rj = k % RING;
-        const int pz = z0 - 1 + k;  // plane entering the window
-        // ---- mu of plane pz into window slot pz % NWIN (k-indexed: same order)
-        if (active) {
-            const f32x4 q = rmu_ring[rj];
-            win[k % NWIN][0][slot] = q.x;
-            win[k % NWIN][1][slot] = q.y;
-            win[k % NWIN][2][slot] = q.z;
-            win[k % NWIN][3][slot] = q.w;
-        }
-        float cur_st[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (role == INTERIOR)
-            StateIO<T>::unpack(rst_ring[rj], p.ld_scale, cur_st[0], cur_st[1], cur_st[2], cur_st[3]);
-        // refill with plane pz + RING (past the chunk: plane z1 again, never used)
-        if (k + RING < NZC + 2) {
-            const int qz = wrapz(min(pz + RING, z1));
-            rmu_ring[rj] = load_f4(rmu, voff_mu, (unsigned)qz * mu_plane);
-            if (role == INTERIOR)
-                rst_ring[rj] = StateIO<T>::load(rst, voff_st, (unsigned)qz * st_plane);
-        }
-        __syncthreads();
-        const int tz = pz - 1;  // plane finalised now (window holds tz-1, tz, tz+1)
-        bool solid = false;
-        if (MASK && role == INTERIOR && k >= 2 && tz < z1)
-            solid = p.mask[(long long)tz * plane + col] != 0;
-        if (solid) {
-            // solid nodes carry no cotangent
-            const long long idx = (long long)tz * plane + col;
-            if (final_t0) {
-#pragma unroll
-                for (int f = 0; f < 4; ++f) mu_out[f * n + idx] = 0.0f;
+    // mu of plane pz into window slot k % NWIN (every thread)
+    auto enter = [&](int k, auto It) {
+        using I = decltype(It);
+        __builtin_amdgcn_sched_barrier(0);
+        float(*W)[NSLOT + 1] = win[k % NWIN];
+        const f32x4 q = mr[I::j];
+        W[0][wslot] = q.x;
+        W[1][wslot] = q.y;
+        W[2][wslot] = q.z;
+        W[3][wslot] = q.w;
+        __builtin_amdgcn_sched_barrier(0);
+        if (I::refill) mr[I::j] = load_f4(rmu, voff_mu, (unsigned)wrapz(z0 + 2 + k) * mu_plane);
+    };
+
+    if (role == INTERIOR) {
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            using I = decltype(kc);
+            constexpr int jm = (I::j + 2) % 3;
+            enter(k, I{});
+            __syncthreads();
+            if (I::phase < 2) return;
+            const int tz = z0 - 2 + k;  // plane finalised now (z0 .. z1 - 1)
+            float d, ux, uy, uz;
+            StateIO<T>::unpack(sr[jm], p.ld_scale, d, ux, uy, uz);
+            const unsigned bits = bw[jm];
+            const bool solid = MASK && (bits & 1u);  // bit 0: a solid node
+            float dan = da;
+            f32x4 lam = adj_point<MASK, NSLOT + 1, SX>(
+                win[(k + NWIN - 2) % NWIN], win[(k + NWIN - 1) % NWIN], win[k % NWIN], slot, d, ux,
+                uy, uz, bits, wallg, (long long)tz * plane + col, p, dan);
+            da = (tz >= zs && !solid) ? dan : da;
+            if (FINAL) {
+                // the gradient with respect to the initial state, field-major
+                if (solid) lam = f32x4{0.0f, 0.0f, 0.0f, 0.0f};  // solid nodes carry no cotangent
+                const unsigned so = (unsigned)tz * (unsigned)(plane * 4);
+                const unsigned fs = (unsigned)(n * 4);
+                const u32x4 lb = __builtin_bit_cast(u32x4, lam);
+                __builtin_amdgcn_raw_buffer_store_b32(lb.x, rout, col * 4u, so, 0);
+                store_data_guard();
+                __builtin_amdgcn_raw_buffer_store_b32(lb.y, rout, col * 4u, so + fs, 0);
+                store_data_guard();
+                __builtin_amdgcn_raw_buffer_store_b32(lb.z, rout, col * 4u, so + 2 * fs, 0);
+                store_data_guard();
+                __builtin_amdgcn_raw_buffer_store_b32(lb.w, rout, col * 4u, so + 3 * fs, 0);
+                store_data_guard();
             } else {
-                reinterpret_cast<float4 *>(mu_out)[idx] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                f32x4 mu = fold_normalisation(lam, d, ux, uy, uz);
+                if (solid) mu = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, mu), rout, voff_mu,
+                                                       (unsigned)tz * mu_plane, 0);
+                store_data_guard();
             }
-        } else if (role == INTERIOR && k >= 2 && tz < z1) {
-            const float(*Wm)[NSLOT] = win[(k + NWIN - 2) % NWIN];  // plane tz - 1
-            const float(*W0)[NSLOT] = win[(k + NWIN - 1) % NWIN];  // plane tz
-            const float(*Wp)[NSLOT] = win[k % NWIN];                // plane tz + 1
-            const long long idx = (long long)tz * plane + col;
-            unsigned bits = 0u;
-            if (MASK) bits = bb_bits[idx];
-            const f32x4 lam = adj_point<MASK, NSLOT, SX>(Wm, W0, Wp, slot, own_st[0], own_st[1],
-                                                         own_st[2], own_st[3], bits, wallg, idx,
-                                                         p, da);
-            if (final_t0) {
-                mu_out[idx] = lam.x;
-                mu_out[n + idx] = lam.y;
-                mu_out[2 * n + idx] = lam.z;
-                mu_out[3 * n + idx] = lam.w;
-            } else {
-                const f32x4 mu = fold_normalisation(lam, own_st[0], own_st[1], own_st[2], own_st[3]);
-                reinterpret_cast<float4 *>(mu_out)[idx] = make_float4(mu.x, mu.y, mu.z, mu.w);
-            }
-        }
-#pragma unroll
-        for (int f = 0; f < 4; ++f) own_st[f] = cur_st[f];
-    });
+            __builtin_amdgcn_sched_barrier(0);  // the state's last use is above
+            if (I::refill) load_state(jm, z0 + 1 + k);
+        });
+    } else {
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            enter(k, kc);
+            __syncthreads();
+        });
+    }
 
     double v[1] = {(double)da};
     store_block_partials<1>(v, r.partials, blockIdx.x);
+}
+
+template <class T, bool MASK, bool FINAL>
+void launch_t(const ProblemArgs &p, const T *st, const float *mu_in, float *mu_out,
+              const unsigned *bits, const float4 *wallg, const ReduceArgs &r, hipStream_t s)
+{
+    const unsigned nb = adj_march_num_blocks(p);
+    const int c = adj_march_depth(p);  // a loop of c + 2 iterations, its tail 3 + (c + 2) % 3
+    switch ((c + 2) % 3) {
+    case 0: k_adj_march<T, 3, MASK, FINAL><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, r); break;
+    case 1: k_adj_march<T, 4, MASK, FINAL><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, r); break;
+    default: k_adj_march<T, 5, MASK, FINAL><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, r); break;
+    }
 }
 
 template <class T>
@@ -188,12 +209,14 @@ hipError_t dispatch(const ProblemArgs &p, const void *state, const float *mu_in,
                     const unsigned *bits, const float4 *wallg, int final_t0, const ReduceArgs &r,
                     hipStream_t s)
 {
-    const unsigned nb = adj_march_num_blocks(p);
     const T *st = static_cast<const T *>(state);
-    if (p.mask)
-        k_adj_march<T, true><<<nb, NTHREADS, 0, s>>>(p, st, mu_in, mu_out, bits, wallg, final_t0, r);
-    else
-        k_adj_march<T, false><<<nb, NTHREADS, 0, s>>>(p, st, mu_in, mu_out, bits, wallg, final_t0, r);
+    if (p.mask) {
+        if (final_t0) launch_t<T, true, true>(p, st, mu_in, mu_out, bits, wallg, r, s);
+        else launch_t<T, true, false>(p, st, mu_in, mu_out, bits, wallg, r, s);
+    } else {
+        if (final_t0) launch_t<T, false, true>(p, st, mu_in, mu_out, bits, wallg, r, s);
+        else launch_t<T, false, false>(p, st, mu_in, mu_out, bits, wallg, r, s);
+    }
     return hipGetLastError();
 }
 
@@ -202,13 +225,16 @@ hipError_t dispatch(const ProblemArgs &p, const void *state, const float *mu_in,
 bool adj_march_supported(const ProblemArgs &p)
 {
     return p.Q == 19 && p.nx >= TX && p.ny >= TY && p.nx % TX == 0 && p.ny % TY == 0 &&
-           p.nz >= 1 && p.n < (1LL << 28);
+           p.nz >= 8 && p.n < (1LL << 28) && p.adj_nzc > 0;
 }
+
+int adj_march_depth(const ProblemArgs &p) { return p.adj_nzc < p.nz ? p.adj_nzc : p.nz; }
 
 unsigned adj_march_num_blocks(const ProblemArgs &p)
 {
     if (!adj_march_supported(p)) return 0;
-    return (unsigned)((long long)(p.nx / TX) * (p.ny / TY) * ((p.nz + NZC - 1) / NZC));
+    const int c = adj_march_depth(p);
+    return (unsigned)((long long)(p.nx / TX) * (p.ny / TY) * ((p.nz + c - 1) / c));
 }
 
 hipError_t launch_adj_march(const ProblemArgs &p, int storage, const void *state,

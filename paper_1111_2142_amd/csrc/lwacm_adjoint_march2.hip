@@ -8,7 +8,7 @@
 // initial state) on the tile: 32 bytes per node and step.
 //
 // Layout (the roles and chunks of the two-step forward kernel): tile
-// 32 x 16 columns, 768 threads, a chunk of NZC planes.  Every thread loads
+// 32 x 16 columns, 768 threads, a chunk of planes.  Every thread loads
 // mu_t of its column (tile, ring, outer ring) into a window of three LDS
 // planes (36 x 20 slots); tile and ring threads then compute mu_{t-1} of the
 // plane below from that window and their step-t state, into a second window
@@ -34,22 +34,8 @@ constexpr int HALO0 = NINT + 2 * kWave;              // first thread of the oute
 constexpr int NTHREADS = NINT + 4 * kWave;
 constexpr int SX1 = TX + 4, NS1 = SX1 * (TY + 4);    // mu_t window slots
 constexpr int SX2 = TX + 2, NS2 = SX2 * (TY + 2);    // mu_{t-1} window slots
-// Chunk depth: 128 planes, halved while deeper than nz.  At 256^3 that is one
-// workgroup per compute unit in a single round (the kernel's 136 VGPRs allow
-// one 768-thread workgroup per CU); 64-plane chunks, the one-step reverse
-// kernel's depth, take two rounds and measured 2.5 % slower.  Where the depths
-// differ, the dL/da block partials group the planes differently from the
-// one-step kernel's (equal to FP64 rounding of the per-thread partials).
-constexpr int kAdjChunk = 128;
-int adj2_nzc(const ProblemArgs &p)
-{
-    int c = kAdjChunk;
-    while (c > 8 && c > p.nz) c /= 2;
-    return c <= p.nz ? c : 0;
-}
-
-template <class T, bool FINAL, int NZC>
-__global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p,
+template <class T, bool FINAL, int TAIL>
+__global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p, int nzc,
                                                          const T *__restrict__ state_a,
                                                          const T *__restrict__ state_b,
                                                          const float *__restrict__ mu_in,
@@ -67,9 +53,9 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p,
     const TileIdx ti = tile_of_block(nx, ny, TX, TY);
     // full chunks: a ragged last one is moved down to end at nz; its planes
     // below zs are written twice with the same bits and counted once
-    const int zs = ti.zc * NZC;
-    const int z0 = min(zs, nz - NZC);
-    const int z1 = z0 + NZC;
+    const int zs = ti.zc * nzc;
+    const int z0 = min(zs, nz - nzc);
+    const int z1 = z0 + nzc;
 
     const Col2 c2 = col2_of<TX, TY>(tid);
     const int gx = wrap_index(ti.tile_x * TX + c2.lx, nx);
@@ -114,7 +100,7 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p,
     }
 
     float da_a = 0.0f, da_b = 0.0f;  // dL/da of the two steps (tile threads)
-    constexpr int N = NZC + 4;        // planes z0 - 2 .. z1 + 1 of mu_t
+    const int N = nzc + 4;        // planes z0 - 2 .. z1 + 1 of mu_t
 
     // mu_t of plane pz into the first window (every thread).
     auto enter = [&](int k, auto It) {
@@ -150,8 +136,8 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p,
     };
 
     if (tid < NINT) {
-        plane_loop<N>([&](int k, auto kc) {
-            using I = PlaneIter<decltype(kc)::value, N, RING>;
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            using I = decltype(kc);
             constexpr int j = I::j, j1 = (j + 1) % 3, jm = (j + 2) % 3;
             enter(k, I{});
             if (I::phase < 2) return;
@@ -193,8 +179,8 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p,
             if (I::refill) sb[j1] = StateIO<T>::load(rsb, voff_st, (unsigned)(z0 - 1 + k) * st_plane);
         });
     } else if (tid < HALO0) {
-        plane_loop<N>([&](int k, auto kc) {
-            using I = PlaneIter<decltype(kc)::value, N, RING>;
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            using I = decltype(kc);
             enter(k, I{});
             if (I::phase < 2) return;
             __syncthreads();
@@ -202,8 +188,8 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p,
             __syncthreads();
         });
     } else {
-        plane_loop<N>([&](int k, auto kc) {
-            using I = PlaneIter<decltype(kc)::value, N, RING>;
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            using I = decltype(kc);
             enter(k, I{});
             if (I::phase < 2) return;
             __syncthreads();
@@ -225,27 +211,23 @@ void launch_t(const ProblemArgs &p, const void *sa, const void *sb, const float 
 {
     const T *a = static_cast<const T *>(sa);
     const T *b = static_cast<const T *>(sb);
-    switch (adj2_nzc(p)) {
-    case 8: k_adj_march2<T, FINAL, 8><<<nb, NTHREADS, 0, s>>>(p, a, b, mu_in, mu_out, r); break;
-    case 16: k_adj_march2<T, FINAL, 16><<<nb, NTHREADS, 0, s>>>(p, a, b, mu_in, mu_out, r); break;
-    case 32: k_adj_march2<T, FINAL, 32><<<nb, NTHREADS, 0, s>>>(p, a, b, mu_in, mu_out, r); break;
-    case 64: k_adj_march2<T, FINAL, 64><<<nb, NTHREADS, 0, s>>>(p, a, b, mu_in, mu_out, r); break;
-    default: k_adj_march2<T, FINAL, 128><<<nb, NTHREADS, 0, s>>>(p, a, b, mu_in, mu_out, r); break;
+    const int c = adj_march_depth(p);  // a loop of c + 4 iterations, its tail 3 + (c + 4) % 3
+    switch ((c + 4) % 3) {
+    case 0: k_adj_march2<T, FINAL, 3><<<nb, NTHREADS, 0, s>>>(p, c, a, b, mu_in, mu_out, r); break;
+    case 1: k_adj_march2<T, FINAL, 4><<<nb, NTHREADS, 0, s>>>(p, c, a, b, mu_in, mu_out, r); break;
+    default: k_adj_march2<T, FINAL, 5><<<nb, NTHREADS, 0, s>>>(p, c, a, b, mu_in, mu_out, r); break;
     }
 }
 
 }  // namespace
 
-bool adj_march2_supported(const ProblemArgs &p)
-{
-    return adj_march_supported(p) && !p.mask && p.nz >= 8;
-}
+// the one-step kernel's grids (and its chunks, so that the dL/da partials of
+// both group the planes alike), without walls
+bool adj_march2_supported(const ProblemArgs &p) { return adj_march_supported(p) && !p.mask; }
 
 unsigned adj_march2_num_blocks(const ProblemArgs &p)
 {
-    if (!adj_march2_supported(p)) return 0;
-    const int c = adj2_nzc(p);
-    return (unsigned)((long long)(p.nx / TX) * (p.ny / TY) * ((p.nz + c - 1) / c));
+    return adj_march2_supported(p) ? adj_march_num_blocks(p) : 0;
 }
 
 hipError_t launch_adj_march2(const ProblemArgs &p, int storage, const void *state_t,

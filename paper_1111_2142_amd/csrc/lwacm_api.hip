@@ -144,6 +144,17 @@ ReduceArgs reduce_args(lwacm_ctx *c, double *out, double *out2)
     return r;
 }
 
+// Compute units of the current device.
+int device_cus()
+{
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        ncu < 1)
+        return 256;
+    return ncu;
+}
+
 size_t state_bytes(const lwacm_ctx *c)
 {
     return (size_t)(c->p.D + 1) * (size_t)c->p.n * (c->storage == LWACM_FP32 ? 4 : 2);
@@ -433,15 +444,14 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
     ProblemArgs unforced = p;
     unforced.has_force = 0;
     unforced.qd = nullptr;  // interpolated walls run on the tiles with the wall correction
-    if (lwacm::march_supported(unforced)) {
-        int dev = 0, ncu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            ncu = 256;
-        p.march_nzc = lwacm::march_choose_nzc(p, ncu);
-    }
-    unforced.march_nzc = p.march_nzc;
     size_t nb = lwacm::kGenericMaxBlocks;
+    if (lwacm::march_supported(unforced)) {
+        const int ncu = device_cus();
+        p.march_nzc = unforced.march_nzc = lwacm::march_choose_depth(p, ncu);
+        p.adj_nzc = unforced.adj_nzc = p.march_nzc;
+        const size_t sb = lwacm::march_scratch_blocks(p, ncu);
+        if (sb > nb) nb = sb;
+    }
     const size_t mb = lwacm::march_num_blocks(unforced);
     if (mb > nb) nb = mb;
     const size_t ab = lwacm::adj_march_num_blocks(unforced);
@@ -1203,15 +1213,14 @@ int lwacm_step_static(int lattice, int nx, int ny, int nz, double omega, float *
     c.a_exact = 1.0 - hq;
     set_scales(&c);
     set_wall_terms(&c);
-    if (lwacm::march_supported(p)) {
-        int dev = 0, ncu = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            ncu = 256;
-        p.march_nzc = lwacm::march_choose_nzc(p, ncu);
-    }
     // the partial sets of the kernels lwacm_step may launch must fit the scratch
     size_t nb = lwacm::generic_grid(p.n);
+    if (lwacm::march_supported(p)) {
+        const int ncu = device_cus();
+        p.march_nzc = lwacm::march_choose_depth(p, ncu);
+        const size_t sb = lwacm::march_scratch_blocks(p, ncu);
+        if (sb > nb) nb = sb;
+    }
     const size_t mb = lwacm::march_num_blocks(p);
     if (mb > nb) nb = mb;
     const size_t fb = lwacm::march2_num_blocks(p);

@@ -44,7 +44,8 @@ struct ProblemArgs {
     // before normalisation; nullptr: the halfway rule with the per-id
     // moving-wall sums
     const float4 *corr;
-    int march_nzc;           // planes per workgroup of the forward tile kernel (0: unused)
+    int march_nzc;           // planes per workgroup of the forward tile kernels (0: unused)
+    int adj_nzc;             // and of the reverse ones
     // the temperature step fused into the single-step tile kernel (thermal
     // problems, march_thermal_supported): T at the step's time and one step
     // later, h = 2/omega_t - 1 and kap = 2 - 2/omega_t; T_in null: no fusion
@@ -116,7 +117,10 @@ hipError_t launch_mask_scan(const ProblemArgs &p, unsigned *d_out2, hipStream_t 
 // classes and solid-upstream bit sets made by launch_classify (n bytes and
 // n unsigned).  Returns hipErrorNotSupported if the problem does not fit.
 bool march_supported(const ProblemArgs &p);
-int march_choose_nzc(const ProblemArgs &p, int ncu);  // chunk depth for a device of ncu CUs
+int march_choose_depth(const ProblemArgs &p, int ncu);  // chunk depth for a device of ncu CUs
+// Blocks a context's reduction scratch holds at least, whatever depth is
+// chosen: those of the best of the depths a caller may set (32, 64, 128).
+size_t march_scratch_blocks(const ProblemArgs &p, int ncu);
 unsigned march_num_blocks(const ProblemArgs &p);       // uses p.march_nzc
 // Moving walls also need a per-node float4 of geometry sums (wallg, n
 // entries; may be null when every wall is at rest).
@@ -124,10 +128,11 @@ constexpr unsigned kMovingWallFlag = 1u << 31;  // in bits: node sees a moving w
 hipError_t launch_classify(const ProblemArgs &p, uint8_t *cls, unsigned *bits, float4 *wallg,
                            hipStream_t s);
 // D3Q19 reverse step as a z-marching tile kernel (any mask, with or without
-// force); mu_in / mu_out node-interleaved, or field-major output when
+// force, nz >= 8); mu_in / mu_out node-interleaved, or field-major output when
 // final_t0.  Masked problems need the bit sets (and wallg for moving walls)
 // of launch_classify.
 bool adj_march_supported(const ProblemArgs &p);
+int adj_march_depth(const ProblemArgs &p);  // p.adj_nzc, at most nz
 unsigned adj_march_num_blocks(const ProblemArgs &p);
 hipError_t launch_adj_march(const ProblemArgs &p, int storage, const void *state,
                             const float *mu_in, float *mu_out, const unsigned *bits,
@@ -151,7 +156,7 @@ hipError_t launch_adj_march2(const ProblemArgs &p, int storage, const void *stat
                              const void *state_tm1, const float *mu_in, float *mu_out,
                              int final_t0, const ReduceArgs &r, hipStream_t stream);
 // Two D3Q19 forward steps per launch on FP32 state (same tiles as the
-// single-step kernel, its chunk depth halved while deeper than nz; halfway
+// single-step kernel, its chunk depth at most nz; halfway
 // walls (bb_bits and wallg from k_classify), no body force, no separate
 // omega_p, no per-step wall correction, nz >= 8).  Stores the first step's
 // partials in r.partials and the second step's in r.partials_b (2 doubles

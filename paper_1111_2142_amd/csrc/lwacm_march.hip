@@ -1,7 +1,7 @@
 // lwacm_march.hip -- D3Q19 LW-ACM forward step as a z-marching tile kernel.
 //
 // Design (gfx950).  A workgroup owns a TX x TY tile of (x, y) columns and a
-// chunk of NZC planes; every thread owns one column and walks up the chunk.
+// chunk of planes; every thread owns one column and walks up the chunk.
 // For each plane it loads the node's state once (three planes in flight in
 // a register ring), evaluates the node's own pre-combined link terms of
 // Eq. ACM2.0b and pushes them towards the columns that consume them.  Links
@@ -46,10 +46,6 @@ namespace {
 #endif
 constexpr int TX = 32;                // tile width (x, contiguous in memory)
 constexpr int TY = 16;                // tile height (y)
-// Planes per workgroup: a template parameter (ring and accumulator indices
-// are compile-time constants), chosen per problem among kChunkDepths by
-// march_choose_nzc().
-constexpr int kChunkDepths[3] = {32, 64, 128};
 // LDS exchange buffers: 2 = one barrier per plane; 1 = half the LDS (more
 // workgroups per CU) at the cost of a second barrier per plane.
 constexpr int NBUF = LWACM_MARCH_NBUF;
@@ -260,7 +256,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march(ProblemArgs p, const T *
 }
 
 // The same step with the plane loop rolled (plane_loop: small code, so the
-// instruction cache holds it) and every chunk NZC planes deep: a ragged last
+// instruction cache holds it) and every chunk nzc planes deep, any depth from
+// 8 on (march_choose_depth): a ragged last
 // chunk is moved down to end at nz, its planes below zs written twice with
 // the same bits and summed once.  Inside the loop every load and store is
 // unconditional and a ring slot is refilled right after its last use, so the
@@ -281,8 +278,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march(ProblemArgs p, const T *
 // state, pushes the temperature terms through the omega_p arrays and writes
 // the new T (p.T_out): 4 + 4 bytes more per node instead of a pass of its own
 // (with walls 8 more: the node's fixed-temperature wall links and their sum).
-template <class T, int NZC, bool SR, bool MASK, bool SPLIT, int FRC, bool CORR, bool THERM>
-__global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p,
+template <class T, int TAIL, bool SR, bool MASK, bool SPLIT, int FRC, bool CORR, bool THERM>
+__global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, int nzc,
                                                                const T *__restrict__ src,
                                                                T *__restrict__ dst,
                                                                const unsigned *__restrict__ bb_bits,
@@ -308,8 +305,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p,
     const long long plane = (long long)nx * ny;
 
     const TileIdx ti = tile_of_block(nx, ny, TX, TY);
-    const int zs = ti.zc * NZC;
-    const int z0 = min(zs, nz - NZC);
+    const int zs = ti.zc * nzc;
+    const int z0 = min(zs, nz - nzc);
 
     const int role = tid < NINT ? INTERIOR : (tid < NINT + kWave ? HALO_Y : HALO_X);
     int lx, ly;
@@ -402,7 +399,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p,
         for (int j = 0; j < 3; ++j) issue_g(j, z0 - 1 + j);
 
     float mass = 0.0f, energy = 0.0f;
-    constexpr int N = NZC + 2;  // planes z0 - 1 .. z1
+    const int N = nzc + 2;  // planes z0 - 1 .. z1
     auto value = [&](const Ring<T> &rg, float &dr, float &ux, float &uy, float &uz) {
         dr = BufIO<T>::value(rg.v, 0, p.ld_scale[0]);
         ux = BufIO<T>::value(rg.v, 1, p.ld_scale[1]);
@@ -414,8 +411,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p,
         Acc acc[3];
 #pragma unroll
         for (int j = 0; j < 3; ++j) acc[j] = Acc{};
-        plane_loop<N>([&](int k, auto kc) {
-            using I = PlaneIter<decltype(kc)::value, N, 3>;
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            using I = decltype(kc);
             constexpr int j = I::j;
             __builtin_amdgcn_sched_barrier(0);
             float dr, ux, uy, uz;
@@ -507,8 +504,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p,
         float hd1[3] = {0.0f, 0.0f, 0.0f}, hd2[3] = {0.0f, 0.0f, 0.0f};
         float hq[3] = {0.0f, 0.0f, 0.0f}, hq1[3] = {0.0f, 0.0f, 0.0f}, hq2[3] = {0.0f, 0.0f, 0.0f};
         const bool isY = role == HALO_Y;
-        plane_loop<N>([&](int k, auto kc) {
-            using I = PlaneIter<decltype(kc)::value, N, 3>;
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            using I = decltype(kc);
             constexpr int j = I::j, j1 = (j + 1) % 3, jm = (j + 2) % 3;
             __builtin_amdgcn_sched_barrier(0);
             float dr, ux, uy, uz;
@@ -538,13 +535,12 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p,
         finish_previous_sums(r.prev_partials, r.prev_nblocks, r.prev_out, r.prev_out2);
 }
 
-// Chunk depth of the rolled kernel: the problem's, halved while deeper than
-// nz (0: nz < 8, the unrolled kernel runs).
+// Chunk depth of the rolled kernel: the problem's, at most nz (0: nz < 8, the
+// unrolled kernel runs).
 int rolled_nzc(const ProblemArgs &p)
 {
-    int c = p.march_nzc;
-    while (c > 8 && c > p.nz) c /= 2;
-    return c <= p.nz ? c : 0;
+    if (p.nz < 8) return 0;
+    return p.march_nzc < p.nz ? p.march_nzc : p.nz;
 }
 
 // Node classes and solid-upstream bit sets for the bounce-back of the march
@@ -602,17 +598,16 @@ __global__ __launch_bounds__(256) void k_classify(ProblemArgs p, uint8_t *cls, u
     }
 }
 
+// c: planes per workgroup; its loop of c + 2 iterations has a tail of 3 + (c + 2) % 3
 template <class T, bool SR, bool MASK, bool SPLIT = false, int FRC = 0, bool CORR = false,
           bool THERM = false>
 void launch_rolled(int c, unsigned nb, hipStream_t s, const ProblemArgs &p, const T *a, T *b,
                    const unsigned *bits, const float4 *wallg, const ReduceArgs &r)
 {
-    switch (c) {
-    case 8: k_fwd_march_rolled<T, 8, SR, MASK, SPLIT, FRC, CORR, THERM><<<nb, NTHREADS, 0, s>>>(p, a, b, bits, wallg, r); break;
-    case 16: k_fwd_march_rolled<T, 16, SR, MASK, SPLIT, FRC, CORR, THERM><<<nb, NTHREADS, 0, s>>>(p, a, b, bits, wallg, r); break;
-    case 32: k_fwd_march_rolled<T, 32, SR, MASK, SPLIT, FRC, CORR, THERM><<<nb, NTHREADS, 0, s>>>(p, a, b, bits, wallg, r); break;
-    case 64: k_fwd_march_rolled<T, 64, SR, MASK, SPLIT, FRC, CORR, THERM><<<nb, NTHREADS, 0, s>>>(p, a, b, bits, wallg, r); break;
-    default: k_fwd_march_rolled<T, 128, SR, MASK, SPLIT, FRC, CORR, THERM><<<nb, NTHREADS, 0, s>>>(p, a, b, bits, wallg, r); break;
+    switch ((c + 2) % 3) {
+    case 0: k_fwd_march_rolled<T, 3, SR, MASK, SPLIT, FRC, CORR, THERM><<<nb, NTHREADS, 0, s>>>(p, c, a, b, bits, wallg, r); break;
+    case 1: k_fwd_march_rolled<T, 4, SR, MASK, SPLIT, FRC, CORR, THERM><<<nb, NTHREADS, 0, s>>>(p, c, a, b, bits, wallg, r); break;
+    default: k_fwd_march_rolled<T, 5, SR, MASK, SPLIT, FRC, CORR, THERM><<<nb, NTHREADS, 0, s>>>(p, c, a, b, bits, wallg, r); break;
     }
 }
 
@@ -705,23 +700,49 @@ static long long march_blocks_for(const ProblemArgs &p, int nzc)
     return tiles * ((p.nz + nzc - 1) / nzc);
 }
 
-int march_choose_nzc(const ProblemArgs &p, int ncu)
+// Chunk depth of the forward and the reverse tile kernels.  The workgroups a
+// CU receives run one after the other or share it, and each spends, besides
+// its planes, about ten planes' time on the halo planes and on filling and
+// draining the plane pipeline (one round of 64 against 48 planes at 64^3:
+// 35.2 and 27.8 us, 0.46 us a plane and 5.7 us besides), so the step time
+// follows ceil(blocks / CUs) * (depth + 10).  The chunks are of equal depth (nz
+// over their number), at least 8 planes; ties go to the deeper chunk (fewer
+// halo planes).  Against the best of 32, 64 and 128 planes, the depths used
+// before: 128^3 13.4 us a step (16 planes) against 20.0 (32), 160 x 96 x 100
+// with walls and a temperature 24.8 (13) against 46.7 (32), two reverse steps
+// at 96^3 29.6 (8) against 124.3 (64); 192^3 and 256^3 keep 64 and 128 planes.
+int march_choose_depth(const ProblemArgs &p, int ncu)
 {
-    // Per-CU work: the workgroups a CU receives run one after the other or
-    // share it, so the step time follows ceil(blocks / CUs) * (chunk planes +
-    // the two halo planes).  Ties go to the deeper chunk (fewer halo planes).
+    constexpr int extra = 10;
+    if (p.nz < 8) return 32;  // the unrolled kernel's
     if (ncu < 1) ncu = 1;
-    int best = kChunkDepths[0];
+    int best = p.nz;
     long long best_cost = -1;
-    for (int c : kChunkDepths) {
+    for (int m = 1;; ++m) {
+        const int c = (p.nz + m - 1) / m;
         const long long nb = march_blocks_for(p, c);
-        const long long cost = ((nb + ncu - 1) / ncu) * (c + 2);
-        if (best_cost < 0 || cost <= best_cost) {
+        if (m > 1 && (c < 8 || nb > 8LL * ncu)) break;
+        const long long cost = ((nb + ncu - 1) / ncu) * (c + extra);
+        if (best_cost < 0 || cost < best_cost) {
             best = c;
             best_cost = cost;
         }
     }
     return best;
+}
+
+size_t march_scratch_blocks(const ProblemArgs &p, int ncu)
+{
+    long long best = 0, best_cost = -1;
+    for (int c : {32, 64, 128}) {
+        const long long nb = march_blocks_for(p, c);
+        const long long cost = ((nb + ncu - 1) / ncu) * (c + 2);
+        if (best_cost < 0 || cost <= best_cost) {
+            best = nb;
+            best_cost = cost;
+        }
+    }
+    return (size_t)best;
 }
 
 unsigned march_num_blocks(const ProblemArgs &p)

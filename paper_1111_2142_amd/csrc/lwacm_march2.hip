@@ -10,7 +10,7 @@
 // which is the regime the paper anticipates for the link-wise method.
 //
 // Layout (tile 32 x 16 columns, one thread per column, marching up a chunk of
-// NZC planes, as in the single-step kernel):
+// planes, as in the single-step kernel):
 //   waves 0-7   the 32 x 16 tile: both steps, all 19 links;
 //   waves 8-9   the 100 columns around it: the first step (all links), and
 //               the five second-step links that point into the tile;
@@ -86,8 +86,8 @@ __device__ __forceinline__ void finish_previous_sums2(const ReduceArgs &r)
     }
 }
 
-template <int NZC, bool MASK>
-__global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p,
+template <int TAIL, bool MASK>
+__global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int nzc,
                                                          const float *__restrict__ src,
                                                          float *__restrict__ dst,
                                                          const unsigned *__restrict__ bb_bits,
@@ -108,14 +108,14 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p,
     const long long plane = (long long)nx * ny;
 
     const TileIdx ti = tile_of_block(nx, ny, TX, TY);
-    // Every chunk is NZC planes deep (nz >= NZC): a ragged last chunk is moved
+    // Every chunk is nzc planes deep (nz >= nzc): a ragged last chunk is moved
     // down to end at nz.  Planes it shares with the chunk below are written
     // twice with bitwise the same values and counted in the sums only once,
     // from zs on, so each block sums the planes the single-step kernel's
     // block of the same index sums.
-    const int zs = ti.zc * NZC;
-    const int z0 = min(zs, nz - NZC);
-    const int z1 = z0 + NZC;
+    const int zs = ti.zc * nzc;
+    const int z0 = min(zs, nz - nzc);
+    const int z1 = z0 + nzc;
 
     const Col2 c2 = col2_of<TX, TY>(tid);
     const int lx = c2.lx, ly = c2.ly;
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p,
     const float A = p.A;
     const float a = p.a;
 
-    // plane index with periodic wrap (nz >= NZC >= 2, so one period suffices)
+    // plane index with periodic wrap (nz >= nzc >= 8, so one period suffices)
     auto wrapz = [&](int pz) { return wrap_index(pz, nz); };
     constexpr unsigned NB = BufIO<float>::kNodeBytes;
     const unsigned plane_bytes = (unsigned)(plane * (long long)NB);
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p,
     for (int j = 0; j < RING; ++j) issue(j, ring[j], z0 - 2 + j);
 
     float m1 = 0.0f, e1 = 0.0f, m2 = 0.0f, e2 = 0.0f;
-    constexpr int N = NZC + 4;  // planes z0 - 2 .. z1 + 1
+    const int N = nzc + 4;  // planes z0 - 2 .. z1 + 1
 
     // The three roles run separate loops (wave-uniform), with the same
     // barriers: two per iteration from k = 2 on, after the first-step and
@@ -231,8 +231,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p,
     };
 
     if (tid < NINT) {
-        plane_loop<N>([&](int k, auto kc) {
-            using I = PlaneIter<decltype(kc)::value, N, RING>;
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            using I = decltype(kc);
             first_push(k, I{});
             if (I::phase < 2) return;
             middle(k, I{}, true);
@@ -255,15 +255,15 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p,
             e2 = count ? fmaf(o2.vx, o2.vx, fmaf(o2.vy, o2.vy, fmaf(o2.vz, o2.vz, e2))) : e2;
         });
     } else if (tid < HALO0) {
-        plane_loop<N>([&](int k, auto kc) {
-            using I = PlaneIter<decltype(kc)::value, N, RING>;
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            using I = decltype(kc);
             first_push(k, I{});
             if (I::phase < 2) return;
             middle(k, I{}, false);
         });
     } else {
-        plane_loop<N>([&](int k, auto kc) {
-            using I = PlaneIter<decltype(kc)::value, N, RING>;
+        plane_loop<TAIL>(N, [&](int k, auto kc) {
+            using I = decltype(kc);
             constexpr int j = I::j, j1 = (j + 1) % 3, jm = (j + 2) % 3;
             __builtin_amdgcn_sched_barrier(0);
             const f32x4 v = ring[j].v;
@@ -288,13 +288,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p,
     if (blockIdx.x == 0 && (r.prev_nblocks || r.prev_nblocks_b)) finish_previous_sums2(r);
 }
 
-// Chunk depth: the single-step kernel's, halved until it fits in nz.
-int march2_nzc(const ProblemArgs &p)
-{
-    int c = p.march_nzc;
-    while (c > 8 && c > p.nz) c /= 2;
-    return c <= p.nz ? c : 0;
-}
+// Chunk depth: the single-step kernel's (nz >= 8).
+int march2_nzc(const ProblemArgs &p) { return p.march_nzc < p.nz ? p.march_nzc : p.nz; }
 
 }  // namespace
 
@@ -319,15 +314,11 @@ hipError_t launch_march2_t(const ProblemArgs &p, const float *src, float *dst,
                            hipStream_t s)
 {
     const unsigned nb = march2_num_blocks(p);
-    switch (march2_nzc(p)) {
-    case 8: k_fwd_march2<8, MASK><<<nb, NTHREADS, 0, s>>>(p, src, dst, bb_bits, wallg, r); break;
-    case 16: k_fwd_march2<16, MASK><<<nb, NTHREADS, 0, s>>>(p, src, dst, bb_bits, wallg, r); break;
-    case 32: k_fwd_march2<32, MASK><<<nb, NTHREADS, 0, s>>>(p, src, dst, bb_bits, wallg, r); break;
-    case 64: k_fwd_march2<64, MASK><<<nb, NTHREADS, 0, s>>>(p, src, dst, bb_bits, wallg, r); break;
-    case 128:
-        k_fwd_march2<128, MASK><<<nb, NTHREADS, 0, s>>>(p, src, dst, bb_bits, wallg, r);
-        break;
-    default: return hipErrorInvalidValue;
+    const int c = march2_nzc(p);  // a loop of c + 4 iterations, its tail 3 + (c + 4) % 3
+    switch ((c + 4) % 3) {
+    case 0: k_fwd_march2<3, MASK><<<nb, NTHREADS, 0, s>>>(p, c, src, dst, bb_bits, wallg, r); break;
+    case 1: k_fwd_march2<4, MASK><<<nb, NTHREADS, 0, s>>>(p, c, src, dst, bb_bits, wallg, r); break;
+    default: k_fwd_march2<5, MASK><<<nb, NTHREADS, 0, s>>>(p, c, src, dst, bb_bits, wallg, r); break;
     }
     return hipGetLastError();
 }

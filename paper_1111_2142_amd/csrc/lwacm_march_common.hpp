@@ -14,7 +14,7 @@ namespace lwacm {
 namespace {
 
 // Compile-time loop: f(std::integral_constant<int, K>) for K = 0 .. N-1.
-// The plane loop runs through it so that every ring and accumulator index is
+// Plane loops run through it so that every ring and accumulator index is
 // a constant expression from the start and all per-plane state stays in
 // registers.
 template <class F, int... K>
@@ -29,40 +29,42 @@ __device__ __forceinline__ void static_for(F &&f)
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// Plane loop of N >= 9 iterations in small code: six specialised iterations,
+// What a plane-loop body knows about its iteration k at compile time: k % 3,
+// min(k, 5) and whether a plane is left to prefetch three iterations ahead.
+template <int J, int PHASE, bool REFILL>
+struct PlaneIter {
+    static constexpr int j = J;
+    static constexpr int phase = PHASE;
+    static constexpr bool refill = REFILL;
+};
+
+// Plane loop of n >= 9 iterations in small code: six specialised iterations,
 // a loop unrolled by three (the period of the accumulator and load-ring
 // rotations, so every register index stays a compile-time constant and the
-// back edge needs no copies), then three to five specialised iterations, so
+// back edge needs no copies), then TAIL = 3 + n % 3 specialised iterations, so
 // that every loop iteration has a plane left to prefetch.  The body is called
-// as body(k, K) with the iteration index k and a std::integral_constant K:
-// K = k in the specialised iterations, K = k % 3 - 3 in the loop, so that
-// k % 3, the early-iteration phases and the prefetch condition are all
-// compile-time constants.
-template <int N, class F>
-__device__ __forceinline__ void plane_loop(F &&body)
+// as body(k, PlaneIter).  n itself is a run-time value: the chunk depth of a
+// problem is chosen plane by plane, and one kernel serves every depth with
+// the same n % 3.
+template <int TAIL, class F>
+__device__ __forceinline__ void plane_loop(int n, F &&body)
 {
-    static_assert(N >= 9, "plane loop needs at least nine iterations");
-    constexpr int T = 3 + (N - 9) % 3;  // specialised tail iterations
-    static_for<6>([&](auto kc) { body((int)decltype(kc)::value, kc); });
+    static_assert(TAIL >= 3 && TAIL <= 5, "the tail is 3 + n % 3 iterations");
+    static_for<6>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        body(k, PlaneIter<k % 3, (k < 5 ? k : 5), true>{});
+    });
 #pragma unroll 1
-    for (int k = 6; k < N - T; k += 3) {
-        body(k, std::integral_constant<int, -3>{});
-        body(k + 1, std::integral_constant<int, -2>{});
-        body(k + 2, std::integral_constant<int, -1>{});
+    for (int k = 6; k < n - TAIL; k += 3) {
+        body(k, PlaneIter<0, 5, true>{});
+        body(k + 1, PlaneIter<1, 5, true>{});
+        body(k + 2, PlaneIter<2, 5, true>{});
     }
-    static_for<T>([&](auto tc) {
-        constexpr int k = N - T + decltype(tc)::value;
-        body(k, std::integral_constant<int, k>{});
+    static_for<TAIL>([&](auto tc) {
+        constexpr int t = decltype(tc)::value;  // n - TAIL is a multiple of three
+        body(n - TAIL + t, PlaneIter<t % 3, 5, (t < TAIL - 3)>{});
     });
 }
-
-// What a plane-loop body needs to know about iteration K at compile time.
-template <int K, int N, int RING>
-struct PlaneIter {
-    static constexpr int j = K >= 0 ? K % 3 : K + 3;     // k % 3
-    static constexpr int phase = K >= 0 && K < 5 ? K : 5;  // min(k, 5)
-    static constexpr bool refill = K < 0 || K + RING < N;  // a plane left to prefetch
-};
 
 // Per target plane accumulator of an interior column.
 struct Acc {
