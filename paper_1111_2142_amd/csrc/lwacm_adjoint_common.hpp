@@ -112,10 +112,11 @@ __device__ __forceinline__ float link_m(const float (*W)[NS], int s)
 
 // The cotangent of a node's own state, lambda = (dL/d(rho - 1), dL/du), from
 // the window planes Wm, W0, Wp of mu around its plane (slot `slot`, row pitch
-// SXP) and its state (dr, u); adds the node's dL/da to da.  With MASK, bits
+// SXP) and its state (dr, u); adds the node's dL/da = rho x to da (XOUT: leaves
+// x in da instead, see k_adj_dadomega).  With MASK, bits
 // is its solid-upstream link set (bit 31: a moving wall, whose geometry sums
 // are wallg[widx]).
-template <bool MASK, int NS, int SXP>
+template <bool MASK, int NS, int SXP, bool XOUT = false>
 __device__ __forceinline__ f32x4 adj_point(const float (*Wm)[NS], const float (*W0)[NS],
                                            const float (*Wp)[NS], int slot, float dr, float ux,
                                            float uy, float uz, unsigned bits,
@@ -187,7 +188,8 @@ __device__ __forceinline__ f32x4 adj_point(const float (*Wm)[NS], const float (*
     const float lux = fmaf(rho, div36(fmaf(A, m1x, fmaf(9.0f, M2ux, -3.0f * ux * m0))), arho * own.y);
     const float luy = fmaf(rho, div36(fmaf(A, m1y, fmaf(9.0f, M2uy, -3.0f * uy * m0))), arho * own.z);
     const float luz = fmaf(rho, div36(fmaf(A, m1z, fmaf(9.0f, M2uz, -3.0f * uz * m0))), arho * own.w);
-    da = fmaf(rho, fmaf(-3.0f, uM1, mJu), da);
+    const float x = fmaf(-3.0f, uM1, mJu);
+    da = XOUT ? x : fmaf(rho, x, da);
     if (MASK && (bits & kMovingWallFlag)) {
         // moving walls: sum over bounced links of w_k (v_k . 6 rho0 u_w) m_k
         const float4 g = wallg[widx];
@@ -196,6 +198,16 @@ __device__ __forceinline__ f32x4 adj_point(const float (*Wm)[NS], const float (*
     }
     const f32x4 lam = {lr, lux, luy, luz};
     return lam;
+}
+
+// The factors (rho, x) of a node's dL/da = rho x, 8 bytes a node.
+__device__ __forceinline__ void store_factors(Rsrc r, unsigned voff, unsigned soff, float dr,
+                                              float x)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {1.0f + dr, x};
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
+    store_data_guard();
 }
 
 // mu of the step before from lambda: the normalisation u = J / rho of that

@@ -16,8 +16,8 @@
 // after every thread has passed the next barrier.  HBM traffic per node:
 // state + mu_in + mu_out = 48 B (FP32 state).
 //
-// The plane loop is rolled (plane_loop), so the chunk depth is a run-time
-// value and a ragged last chunk is moved down to end at nz, as in the other
+// The plane loop is rolled (plane_loop), the chunk depth a run-time value, and a
+// ragged last chunk is moved down to end at nz, as in the other
 // tile kernels: its planes below zs are written twice with the same bits and
 // counted once.  Every load and store is unconditional and a ring slot is
 // refilled after its last use, so the loads stay in flight across the back
@@ -41,15 +41,19 @@ static_assert(2 * TX <= kWave && 2 * (TY + 2) <= kWave, "halo rows must fit one 
 
 enum Role { INTERIOR = 0, HALO_Y = 1, HALO_X = 2 };
 
-template <class T, int TAIL, bool MASK, bool FINAL>
+// XOUT (no walls): the factors (rho, x) of the nodes' dL/da = rho x go to xout
+// (n pairs) instead of into block partials; chunks of any depth then give the same sums
+// (k_adj_dadomega adds them).
+template <class T, int TAIL, bool MASK, bool FINAL, bool XOUT>
 __global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, int nzc,
                                                         const T *__restrict__ state,
                                                         const float *__restrict__ mu_in,
                                                         float *__restrict__ mu_out,
                                                         const unsigned *__restrict__ bb_bits,
                                                         const float4 *__restrict__ wallg,
-                                                        ReduceArgs r)
+                                                        float2 *__restrict__ xout, ReduceArgs r)
 {
+    static_assert(!(XOUT && MASK), "x is written for problems without walls");
     // one spare slot: idle halo lanes write there instead of branching
     __shared__ float win[NWIN][4][NSLOT + 1];
 
@@ -84,8 +88,8 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, int nzc,
         active = lane < 2 * (TY + 2);
         if (!active) ly = 0;
     }
-    const int gx = wrap_index(ti.tile_x * TX + lx, nx);
-    const int gy = wrap_index(ti.tile_y * TY + ly, ny);
+    const int gx = wrap_index(ti.x0 + lx, nx);
+    const int gy = wrap_index(ti.y0 + ly, ny);
     const unsigned col = (unsigned)(gy * nx + gx);
     const int slot = (ly + 1) * SX + (lx + 1);
     const int wslot = active ? slot : NSLOT;
@@ -96,6 +100,7 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, int nzc,
     const Rsrc rst = make_rsrc(state, (unsigned long long)n * NB);
     const Rsrc rout = make_rsrc(mu_out, (unsigned long long)n * 16u);
     const Rsrc rbits = make_rsrc(bb_bits, MASK ? (unsigned long long)n * 4u : 0ull);
+    const Rsrc rx = make_rsrc(XOUT ? xout : nullptr, XOUT ? (unsigned long long)n * 8u : 0ull);
     const unsigned mu_plane = (unsigned)(plane * 16);
     const unsigned st_plane = (unsigned)(plane * NB);
     const unsigned voff_mu = col * 16u;
@@ -152,10 +157,14 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, int nzc,
             const unsigned bits = bw[jm];
             const bool solid = MASK && (bits & 1u);  // bit 0: a solid node
             float dan = da;
-            f32x4 lam = adj_point<MASK, NSLOT + 1, SX>(
+            f32x4 lam = adj_point<MASK, NSLOT + 1, SX, XOUT>(
                 win[(k + NWIN - 2) % NWIN], win[(k + NWIN - 1) % NWIN], win[k % NWIN], slot, d, ux,
                 uy, uz, bits, wallg, (long long)tz * plane + col, p, dan);
-            da = (tz >= zs && !solid) ? dan : da;
+            if (XOUT) {
+                store_factors(rx, col * 8u, (unsigned)tz * (unsigned)(plane * 8), d, dan);
+            } else {
+                da = (tz >= zs && !solid) ? dan : da;
+            }
             if (FINAL) {
                 // the gradient with respect to the initial state, field-major
                 if (solid) lam = f32x4{0.0f, 0.0f, 0.0f, 0.0f};  // solid nodes carry no cotangent
@@ -187,37 +196,67 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, int nzc,
         });
     }
 
+    if (XOUT) return;
     double v[1] = {(double)da};
     store_block_partials<1>(v, r.partials, blockIdx.x);
 }
 
-template <class T, bool MASK, bool FINAL>
-void launch_t(const ProblemArgs &p, const T *st, const float *mu_in, float *mu_out,
-              const unsigned *bits, const float4 *wallg, const ReduceArgs &r, hipStream_t s)
+// dL/da of reverse steps whose nodes' factors (rho, x) were written by the tile
+// kernels (XOUT).  The reverse kernels without XOUT sum a thread's planes in
+// FP32 (da = fma(rho, x, da) up its chunk of nzc planes), then over the block
+// and the grid in FP64; this kernel does the same sums on the same tiles,
+// chunks and threads, so each step's dL/domega is bitwise theirs while the
+// reverse kernel itself runs shallower chunks that fill the chip.  Step s =
+// blockIdx.y has its factors at x + s * n and its partials at partials + s *
+// stride.  8 bytes read per node and step; few threads walk far, so each has 32
+// loads in flight.
+__global__ __launch_bounds__(NINT) void k_adj_dadomega(ProblemArgs p, int nzc,
+                                                       const float2 *__restrict__ x,
+                                                       double *__restrict__ partials, size_t stride)
 {
-    const unsigned nb = adj_march_num_blocks(p);
-    const int c = adj_march_depth(p);  // a loop of c + 2 iterations, its tail 3 + (c + 2) % 3
+    const TileIdx ti = tile_of_block(p.nx, p.ny, TX, TY);
+    const size_t plane = (size_t)p.nx * p.ny;
+    const size_t col = (size_t)(ti.y0 + (int)threadIdx.x / TX) * p.nx + ti.x0 + threadIdx.x % TX;
+    const float2 *xs = x + (size_t)blockIdx.y * p.n;
+    const int z0 = ti.zc * nzc, z1 = min(z0 + nzc, p.nz);
+    constexpr int U = 32;
+    float da = 0.0f;
+    for (int z = z0; z < z1; z += U) {
+        float2 v[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) v[j] = xs[(size_t)min(z + j, z1 - 1) * plane + col];
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            if (z + j < z1) da = fmaf(v[j].x, v[j].y, da);
+    }
+    double v[1] = {(double)da};
+    store_block_partials<1>(v, partials + blockIdx.y * stride, blockIdx.x);
+}
+
+template <class T, bool MASK, bool FINAL, bool XOUT>
+void launch_t(const ProblemArgs &p, const T *st, const float *mu_in, float *mu_out,
+              const unsigned *bits, const float4 *wallg, float2 *x, const ReduceArgs &r,
+              hipStream_t s)
+{
+    // a loop of c + 2 iterations, its tail 3 + (c + 2) % 3
+    const int c = XOUT ? adj_split_depth(p) : adj_depth(p);
+    const unsigned nb = adj_blocks(p, c);
     switch ((c + 2) % 3) {
-    case 0: k_adj_march<T, 3, MASK, FINAL><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, r); break;
-    case 1: k_adj_march<T, 4, MASK, FINAL><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, r); break;
-    default: k_adj_march<T, 5, MASK, FINAL><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, r); break;
+    case 0: k_adj_march<T, 3, MASK, FINAL, XOUT><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
+    case 1: k_adj_march<T, 4, MASK, FINAL, XOUT><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
+    default: k_adj_march<T, 5, MASK, FINAL, XOUT><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
     }
 }
 
-template <class T>
-hipError_t dispatch(const ProblemArgs &p, const void *state, const float *mu_in, float *mu_out,
-                    const unsigned *bits, const float4 *wallg, int final_t0, const ReduceArgs &r,
-                    hipStream_t s)
+template <class T, bool FINAL>
+void dispatch(const ProblemArgs &p, const void *state, const float *mu_in, float *mu_out,
+              const unsigned *bits, const float4 *wallg, float2 *x, const ReduceArgs &r,
+              hipStream_t s)
 {
     const T *st = static_cast<const T *>(state);
-    if (p.mask) {
-        if (final_t0) launch_t<T, true, true>(p, st, mu_in, mu_out, bits, wallg, r, s);
-        else launch_t<T, true, false>(p, st, mu_in, mu_out, bits, wallg, r, s);
-    } else {
-        if (final_t0) launch_t<T, false, true>(p, st, mu_in, mu_out, bits, wallg, r, s);
-        else launch_t<T, false, false>(p, st, mu_in, mu_out, bits, wallg, r, s);
-    }
-    return hipGetLastError();
+    if (p.mask) launch_t<T, true, FINAL, false>(p, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
+    else if (x) launch_t<T, false, FINAL, true>(p, st, mu_in, mu_out, bits, wallg, x, r, s);
+    else launch_t<T, false, FINAL, false>(p, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
 }
 
 }  // namespace
@@ -225,27 +264,49 @@ hipError_t dispatch(const ProblemArgs &p, const void *state, const float *mu_in,
 bool adj_march_supported(const ProblemArgs &p)
 {
     return p.Q == 19 && p.nx >= TX && p.ny >= TY && p.nx % TX == 0 && p.ny % TY == 0 &&
-           p.nz >= 8 && p.n < (1LL << 28) && p.adj_nzc > 0;
+           p.nz >= 8 && p.n < (1LL << 28);
 }
 
-int adj_march_depth(const ProblemArgs &p) { return p.adj_nzc < p.nz ? p.adj_nzc : p.nz; }
+// Chunk depth: 64 planes.  A thread sums its planes' dL/da in FP32, so the
+// depth is part of the result and stays as it is on every grid; sweeps on
+// grids that it leaves half empty go through adj_split_depth.
+int adj_depth(const ProblemArgs &p) { return p.nz < 64 ? p.nz : 64; }
+
+int adj_split_depth(const ProblemArgs &p) { return p.march_nzc < p.nz ? p.march_nzc : p.nz; }
+
+unsigned adj_blocks(const ProblemArgs &p, int nzc)
+{
+    return (unsigned)((long long)(p.nx / TX) * (p.ny / TY) * ((p.nz + nzc - 1) / nzc));
+}
 
 unsigned adj_march_num_blocks(const ProblemArgs &p)
 {
-    if (!adj_march_supported(p)) return 0;
-    const int c = adj_march_depth(p);
-    return (unsigned)((long long)(p.nx / TX) * (p.ny / TY) * ((p.nz + c - 1) / c));
+    return adj_march_supported(p) ? adj_blocks(p, adj_depth(p)) : 0;
+}
+
+hipError_t launch_adj_dadomega(const ProblemArgs &p, int nzc, int nsteps, const float2 *x,
+                               double *partials, size_t stride, hipStream_t s)
+{
+    if (!adj_march_supported(p) || p.mask || nsteps < 1) return hipErrorInvalidValue;
+    k_adj_dadomega<<<dim3(adj_blocks(p, nzc), (unsigned)nsteps), NINT, 0, s>>>(p, nzc, x, partials,
+                                                                               stride);
+    return hipGetLastError();
 }
 
 hipError_t launch_adj_march(const ProblemArgs &p, int storage, const void *state,
                             const float *mu_in, float *mu_out, const unsigned *bits,
                             const float4 *wallg, int final_t0, const ReduceArgs &r,
-                            hipStream_t stream)
+                            hipStream_t stream, float2 *x)
 {
-    if (!adj_march_supported(p) || (p.mask && !bits)) return hipErrorNotSupported;
-    const hipError_t e =
-        storage ? dispatch<__half>(p, state, mu_in, mu_out, bits, wallg, final_t0, r, stream)
-                : dispatch<float>(p, state, mu_in, mu_out, bits, wallg, final_t0, r, stream);
+    if (!adj_march_supported(p) || (p.mask && (!bits || x))) return hipErrorNotSupported;
+    if (storage) {
+        if (final_t0) dispatch<__half, true>(p, state, mu_in, mu_out, bits, wallg, x, r, stream);
+        else dispatch<__half, false>(p, state, mu_in, mu_out, bits, wallg, x, r, stream);
+    } else {
+        if (final_t0) dispatch<float, true>(p, state, mu_in, mu_out, bits, wallg, x, r, stream);
+        else dispatch<float, false>(p, state, mu_in, mu_out, bits, wallg, x, r, stream);
+    }
+    const hipError_t e = hipGetLastError();
     // r.out null: the caller adds the block partials itself (lwacm_adjoint_sweep)
     if (e != hipSuccess || !r.out) return e;
     return launch_reduce(r, 1, adj_march_num_blocks(p), stream);

@@ -34,12 +34,16 @@ constexpr int HALO0 = NINT + 2 * kWave;              // first thread of the oute
 constexpr int NTHREADS = NINT + 4 * kWave;
 constexpr int SX1 = TX + 4, NS1 = SX1 * (TY + 4);    // mu_t window slots
 constexpr int SX2 = TX + 2, NS2 = SX2 * (TY + 2);    // mu_{t-1} window slots
-template <class T, bool FINAL, int TAIL>
+// XOUT: the factors of both steps' dL/da = rho x go to xa and xb (n pairs each)
+// instead of into block partials (see k_adj_dadomega).
+template <class T, bool FINAL, bool XOUT, int TAIL>
 __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p, int nzc,
                                                          const T *__restrict__ state_a,
                                                          const T *__restrict__ state_b,
                                                          const float *__restrict__ mu_in,
-                                                         float *__restrict__ mu_out, ReduceArgs r)
+                                                         float *__restrict__ mu_out,
+                                                         float2 *__restrict__ xa,
+                                                         float2 *__restrict__ xb, ReduceArgs r)
 {
     // one spare slot per array: idle lanes write there instead of branching
     __shared__ float w1[3][4][NS1 + 1];
@@ -58,8 +62,8 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p, int nzc,
     const int z1 = z0 + nzc;
 
     const Col2 c2 = col2_of<TX, TY>(tid);
-    const int gx = wrap_index(ti.tile_x * TX + c2.lx, nx);
-    const int gy = wrap_index(ti.tile_y * TY + c2.ly, ny);
+    const int gx = wrap_index(ti.x0 + c2.lx, nx);
+    const int gy = wrap_index(ti.y0 + c2.ly, ny);
     const unsigned col = (unsigned)(gy * nx + gx);
     const int slot1 = (c2.ly + 2) * SX1 + (c2.lx + 2);
     const int slot2 = (c2.ly + 1) * SX2 + (c2.lx + 1);  // tile and first ring only
@@ -72,6 +76,8 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p, int nzc,
     const Rsrc rsa = make_rsrc(state_a, (unsigned long long)n * NB);
     const Rsrc rsb = make_rsrc(state_b, (unsigned long long)n * NB);
     const Rsrc rout = make_rsrc(mu_out, (unsigned long long)n * 16u);
+    const Rsrc rxa = make_rsrc(XOUT ? xa : nullptr, XOUT ? (unsigned long long)n * 8u : 0ull);
+    const Rsrc rxb = make_rsrc(XOUT ? xb : nullptr, XOUT ? (unsigned long long)n * 8u : 0ull);
     const unsigned mu_plane = (unsigned)(plane * 16);
     const unsigned st_plane = (unsigned)(plane * NB);
     const unsigned voff_mu = col * 16u;
@@ -123,9 +129,17 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p, int nzc,
         StateIO<T>::unpack(sa[jm], p.ld_scale, d, ux, uy, uz);
         const int tq = z0 - 3 + k;
         float da = da_a;
-        const f32x4 lam = adj_point<false, NS1 + 1, SX1>(w1[j1], w1[jm], w1[j], slot1, d, ux, uy,
+        const f32x4 lam = adj_point<false, NS1 + 1, SX1, XOUT>(w1[j1], w1[jm], w1[j], slot1, d, ux, uy,
                                                          uz, 0u, nullptr, 0, p, da);
-        if (tile) da_a = (tq >= zs && tq < z1) ? da : da_a;
+        if (XOUT && tile) {
+            // the chunk's own planes; the store of the planes beyond it goes past
+            // the end of the buffer, where the hardware drops it
+            const bool own = tq >= z0 && tq < z1;
+            const unsigned off = (unsigned)tq * (unsigned)(plane * 8) + col * 8u;
+            store_factors(rxa, own ? off : 0xfffffff0u, 0u, d, da);
+        } else if (tile) {
+            da_a = (tq >= zs && tq < z1) ? da : da_a;
+        }
         const f32x4 mu = fold_normalisation(lam, d, ux, uy, uz);
         w2[j][0][wslot2] = mu.x;
         w2[j][1][wslot2] = mu.y;
@@ -150,9 +164,13 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p, int nzc,
             float d, ux, uy, uz;
             StateIO<T>::unpack(sb[j1], p.ld_scale, d, ux, uy, uz);
             float da = da_b;
-            const f32x4 lam = adj_point<false, NS2 + 1, SX2>(w2[j1], w2[jm], w2[j], slot2, d, ux, uy,
+            const f32x4 lam = adj_point<false, NS2 + 1, SX2, XOUT>(w2[j1], w2[jm], w2[j], slot2, d, ux, uy,
                                                              uz, 0u, nullptr, 0, p, da);
-            da_b = tz >= zs ? da : da_b;
+            if (XOUT) {
+                store_factors(rxb, col * 8u, (unsigned)tz * (unsigned)(plane * 8), d, da);
+            } else {
+                da_b = tz >= zs ? da : da_b;
+            }
             if (FINAL) {
                 // the gradient with respect to the initial state, field-major.
                 // (One whole-vector cast, then component selection: this
@@ -197,6 +215,7 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p, int nzc,
         });
     }
 
+    if (XOUT) return;
     double sums[2] = {(double)da_a, (double)da_b};
     block_sum<2>(sums);
     if (tid == 0) {
@@ -205,49 +224,70 @@ __global__ __launch_bounds__(NTHREADS) void k_adj_march2(ProblemArgs p, int nzc,
     }
 }
 
-template <class T, bool FINAL>
+// Chunk depth: 128 planes, halved while deeper than nz (at 256^3 one workgroup
+// per compute unit in a single round; the kernel's 136 VGPRs allow one
+// 768-thread workgroup per CU).  A thread sums its planes' dL/da in FP32, so
+// the depth is part of the result and stays as it is on every grid; sweeps on
+// grids that it leaves half empty go through adj_split_depth.
+template <class T, bool FINAL, bool XOUT>
 void launch_t(const ProblemArgs &p, const void *sa, const void *sb, const float *mu_in,
-              float *mu_out, const ReduceArgs &r, unsigned nb, hipStream_t s)
+              float *mu_out, float2 *xa, float2 *xb, const ReduceArgs &r, hipStream_t s)
 {
     const T *a = static_cast<const T *>(sa);
     const T *b = static_cast<const T *>(sb);
-    const int c = adj_march_depth(p);  // a loop of c + 4 iterations, its tail 3 + (c + 4) % 3
+    // a loop of c + 4 iterations, its tail 3 + (c + 4) % 3
+    const int c = XOUT ? adj_split_depth(p) : adj2_depth(p);
+    const unsigned nb = adj_blocks(p, c);
     switch ((c + 4) % 3) {
-    case 0: k_adj_march2<T, FINAL, 3><<<nb, NTHREADS, 0, s>>>(p, c, a, b, mu_in, mu_out, r); break;
-    case 1: k_adj_march2<T, FINAL, 4><<<nb, NTHREADS, 0, s>>>(p, c, a, b, mu_in, mu_out, r); break;
-    default: k_adj_march2<T, FINAL, 5><<<nb, NTHREADS, 0, s>>>(p, c, a, b, mu_in, mu_out, r); break;
+    case 0: k_adj_march2<T, FINAL, XOUT, 3><<<nb, NTHREADS, 0, s>>>(p, c, a, b, mu_in, mu_out, xa, xb, r); break;
+    case 1: k_adj_march2<T, FINAL, XOUT, 4><<<nb, NTHREADS, 0, s>>>(p, c, a, b, mu_in, mu_out, xa, xb, r); break;
+    default: k_adj_march2<T, FINAL, XOUT, 5><<<nb, NTHREADS, 0, s>>>(p, c, a, b, mu_in, mu_out, xa, xb, r); break;
     }
+}
+
+template <class T, bool FINAL>
+void dispatch(const ProblemArgs &p, const void *sa, const void *sb, const float *mu_in,
+              float *mu_out, float2 *xa, float2 *xb, const ReduceArgs &r, hipStream_t s)
+{
+    if (xa) launch_t<T, FINAL, true>(p, sa, sb, mu_in, mu_out, xa, xb, r, s);
+    else launch_t<T, FINAL, false>(p, sa, sb, mu_in, mu_out, nullptr, nullptr, r, s);
 }
 
 }  // namespace
 
-// the one-step kernel's grids (and its chunks, so that the dL/da partials of
-// both group the planes alike), without walls
 bool adj_march2_supported(const ProblemArgs &p) { return adj_march_supported(p) && !p.mask; }
+
+int adj2_depth(const ProblemArgs &p)
+{
+    int c = 128;
+    while (c > 8 && c > p.nz) c /= 2;
+    return c;
+}
 
 unsigned adj_march2_num_blocks(const ProblemArgs &p)
 {
-    return adj_march2_supported(p) ? adj_march_num_blocks(p) : 0;
+    return adj_march2_supported(p) ? adj_blocks(p, adj2_depth(p)) : 0;
 }
 
 hipError_t launch_adj_march2(const ProblemArgs &p, int storage, const void *state_t,
                              const void *state_tm1, const float *mu_in, float *mu_out,
-                             int final_t0, const ReduceArgs &r, hipStream_t stream)
+                             int final_t0, const ReduceArgs &r, hipStream_t stream, float2 *xa,
+                             float2 *xb)
 {
-    if (!adj_march2_supported(p) || !r.partials_b) return hipErrorNotSupported;
-    const unsigned nb = adj_march2_num_blocks(p);
+    if (!adj_march2_supported(p) || (xa ? !xb : !r.partials_b)) return hipErrorNotSupported;
     if (storage) {
-        if (final_t0) launch_t<__half, true>(p, state_t, state_tm1, mu_in, mu_out, r, nb, stream);
-        else launch_t<__half, false>(p, state_t, state_tm1, mu_in, mu_out, r, nb, stream);
+        if (final_t0) dispatch<__half, true>(p, state_t, state_tm1, mu_in, mu_out, xa, xb, r, stream);
+        else dispatch<__half, false>(p, state_t, state_tm1, mu_in, mu_out, xa, xb, r, stream);
     } else {
-        if (final_t0) launch_t<float, true>(p, state_t, state_tm1, mu_in, mu_out, r, nb, stream);
-        else launch_t<float, false>(p, state_t, state_tm1, mu_in, mu_out, r, nb, stream);
+        if (final_t0) dispatch<float, true>(p, state_t, state_tm1, mu_in, mu_out, xa, xb, r, stream);
+        else dispatch<float, false>(p, state_t, state_tm1, mu_in, mu_out, xa, xb, r, stream);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // the two steps' dL/domega, in the order two one-step calls add them (r.out
     // null: the caller adds the block partials itself, lwacm_adjoint_sweep)
     if (!r.out) return hipSuccess;
+    const unsigned nb = adj_march2_num_blocks(p);
     e = launch_reduce(r, 1, nb, stream);
     if (e != hipSuccess) return e;
     ReduceArgs rb = r;

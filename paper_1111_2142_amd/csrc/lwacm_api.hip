@@ -22,6 +22,7 @@ struct lwacm_ctx {
     int lattice;
     int storage;
     int variant;  // requested LWACM_KERNEL_*
+    int ncu;      // compute units of the device (tile-kernel problems)
     bool force;
     double omega;
     double omega_p;  // relaxation of the density update (== omega: single relaxation)
@@ -172,7 +173,12 @@ bool use_multi(const lwacm_ctx *c)
 bool use_march(const lwacm_ctx *c)
 {
     if (c->variant == LWACM_KERNEL_GENERIC || c->semi_implicit) return false;
-    return lwacm::march_supported(c->p);
+    return lwacm::march_supported(c->p) && lwacm::march_aligned(c->p);
+}
+
+bool use_adj_march(const lwacm_ctx *c)
+{
+    return c->variant != LWACM_KERNEL_GENERIC && lwacm::adj_march_supported(c->p);
 }
 
 // Two steps per launch: FP32 state, AUTO or MARCH2 selection.
@@ -446,10 +452,9 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
     unforced.qd = nullptr;  // interpolated walls run on the tiles with the wall correction
     size_t nb = lwacm::kGenericMaxBlocks;
     if (lwacm::march_supported(unforced)) {
-        const int ncu = device_cus();
-        p.march_nzc = unforced.march_nzc = lwacm::march_choose_depth(p, ncu);
-        p.adj_nzc = unforced.adj_nzc = p.march_nzc;
-        const size_t sb = lwacm::march_scratch_blocks(p, ncu);
+        c->ncu = device_cus();
+        p.march_nzc = unforced.march_nzc = lwacm::march_choose_depth(p, c->ncu);
+        const size_t sb = lwacm::march_aligned(p) ? lwacm::march_scratch_blocks(p, c->ncu) : 0;
         if (sb > nb) nb = sb;
     }
     const size_t mb = lwacm::march_num_blocks(unforced);
@@ -555,7 +560,7 @@ int lwacm_set_fp16_rounding(lwacm_ctx *c, int mode, uint32_t seed)
 int lwacm_set_march_chunk(lwacm_ctx *c, int planes)
 {
     if (!c || (planes != 32 && planes != 64 && planes != 128)) return LWACM_EINVAL;
-    if (!lwacm::march_supported(c->p)) return LWACM_EUNSUPPORTED;
+    if (!lwacm::march_supported(c->p) || !lwacm::march_aligned(c->p)) return LWACM_EUNSUPPORTED;
     const int keep = c->p.march_nzc;
     c->p.march_nzc = planes;
     if (lwacm::march_num_blocks(c->p) > c->n_partial_blocks ||
@@ -762,13 +767,14 @@ int lwacm_set_variant(lwacm_ctx *c, int variant)
     }
     if (variant == LWACM_KERNEL_MARCH2) {
         if (c->storage != LWACM_FP32 || c->thermal || c->semi_implicit ||
-            !lwacm::march2_supported(c->p))
+            !lwacm::march2_supported(c->p) || !lwacm::march_aligned(c->p))
             return LWACM_EUNSUPPORTED;
         c->variant = variant;
         return LWACM_OK;
     }
     if (variant == LWACM_KERNEL_MARCH) {
-        if (c->semi_implicit || !lwacm::march_supported(c->p)) return LWACM_EUNSUPPORTED;
+        if (c->semi_implicit || !lwacm::march_supported(c->p) || !lwacm::march_aligned(c->p))
+            return LWACM_EUNSUPPORTED;
         c->variant = variant;
         return LWACM_OK;
     }
@@ -1001,7 +1007,7 @@ int lwacm_adjoint_step(lwacm_ctx *c, const void *d_state_t, const float *d_mu_in
     ReduceArgs r = reduce_args(c, d_dL_domega, nullptr);
     r.accumulate = 1;
     r.out_scale = 2.0 / (c->omega * c->omega);  // da/domega for a = 2 - 2/omega
-    if (c->variant != LWACM_KERNEL_GENERIC && lwacm::adj_march_supported(c->p))
+    if (use_adj_march(c))
         return dev_err(lwacm::launch_adj_march(c->p, c->storage, d_state_t, d_mu_in, d_mu_out,
                                                c->d_bits, c->d_wallg, final_t0, r, c->stream));
     return dev_err(lwacm::launch_adj_generic(c->p, c->storage, d_state_t, d_mu_in, d_mu_out,
@@ -1015,8 +1021,8 @@ int lwacm_adjoint_step2(lwacm_ctx *c, const void *d_state_t, const void *d_state
         d_mu_in == d_mu_out)
         return LWACM_EINVAL;
     if ((c->variant != LWACM_KERNEL_AUTO && c->variant != LWACM_KERNEL_MARCH2) ||
-        !lwacm::adj_march2_supported(c->p) || c->p.split || c->p.g_field || c->p.qd || c->p.uwl ||
-        c->semi_implicit)
+        !lwacm::adj_march2_supported(c->p) || c->p.split ||
+        c->p.g_field || c->p.qd || c->p.uwl || c->semi_implicit)
         return LWACM_EUNSUPPORTED;
     ReduceArgs r = reduce_args(c, d_dL_domega, nullptr);
     r.accumulate = 1;
@@ -1103,7 +1109,7 @@ int lwacm_adjoint_sweep(lwacm_ctx *c, const void *d_states, long long t0, int ns
     const size_t sb = state_bytes(c);
     const char *st = static_cast<const char *>(d_states);
     const size_t stride = c->n_partial_blocks;  // doubles per slice
-    const size_t need = (size_t)nsteps * (stride + 1);
+    const size_t need = (size_t)nsteps * (stride + 1);  // slices, then their totals
     if (need > c->sweep_cap) {
         if (c->d_sweep) (void)hipFree(c->d_sweep);
         c->d_sweep = nullptr;
@@ -1111,17 +1117,42 @@ int lwacm_adjoint_sweep(lwacm_ctx *c, const void *d_states, long long t0, int ns
         if (hipMalloc(&c->d_sweep, need * sizeof(double)) != hipSuccess) return LWACM_ENOMEM;
         c->sweep_cap = need;
     }
-    // zero slices: each launch fills its own blocks' entries only
-    if (hipMemsetAsync(c->d_sweep, 0, (size_t)nsteps * stride * sizeof(double), c->stream) !=
-        hipSuccess)
-        return LWACM_EDEVICE;
-    const bool two_ok = (c->variant == LWACM_KERNEL_AUTO || c->variant == LWACM_KERNEL_MARCH2) &&
+    const bool tile = use_adj_march(c);
+    const bool two_ok = tile && c->variant != LWACM_KERNEL_MARCH &&
                         lwacm::adj_march2_supported(c->p);
-    const bool tile = c->variant != LWACM_KERNEL_GENERIC && lwacm::adj_march_supported(c->p);
     // D2Q9: up to kMultiSteps reverse steps per launch in LDS
     const bool multi = c->variant == LWACM_KERNEL_AUTO && c->storage == LWACM_FP32 &&
                        lwacm::d2q9_multi_supported(c->p) &&
                        lwacm::d2q9_multi_num_blocks(c->p) <= c->n_partial_blocks;
+    // blocks of the launches that take two steps and of those that take one
+    const unsigned nb2 = two_ok ? lwacm::adj_march2_num_blocks(c->p) : 0u;
+    const unsigned nb1 = multi ? lwacm::d2q9_multi_num_blocks(c->p)
+                               : (tile ? lwacm::adj_march_num_blocks(c->p)
+                                       : lwacm::generic_grid(c->p.n));
+    // Tile kernels whose chunks leave compute units idle (96^3: 36 workgroups):
+    // chunks that fill the chip instead, the factors of the nodes' dL/da written
+    // out, and the same dL/domega sums by launch_adj_dadomega after each launch.
+    // The factors (8 bytes a node and step) go to the context's other state
+    // buffer, which without walls holds nothing until the next forward step:
+    // room for the two steps of a launch, or with FP16 storage for one, and then
+    // the steps run one per launch.  (Arguments of the call that lie in that
+    // buffer keep the deep chunks.)  A reverse step of a sweep, sums included:
+    // 96^3 62 -> 18 us, 128^3 119 -> 30, 192^3 124 -> 90.
+    const unsigned nb_deep = two_ok ? nb2 : nb1;
+    const char *other = static_cast<const char *>(c->buf[c->cur ^ 1]);
+    const size_t mu_bytes = (size_t)(c->p.D + 1) * (size_t)c->p.n * sizeof(float);
+    auto in_other = [&](const void *q, size_t bytes) {
+        const char *a = static_cast<const char *>(q);
+        return a < other + sb && other < a + bytes;
+    };
+    const bool split = tile && !c->p.mask && nb_deep < (unsigned)c->ncu &&
+                       lwacm::adj_blocks(c->p, lwacm::adj_split_depth(c->p)) > nb_deep &&
+                       !in_other(st, (size_t)nsteps * sb) && !in_other(d_mu, mu_bytes) &&
+                       !in_other(d_mu_tmp, mu_bytes) && !in_other(d_dL_domega, sizeof(double));
+    float2 *const x = split ? static_cast<float2 *>(c->buf[c->cur ^ 1]) : nullptr;
+    const bool pair_launch = two_ok && (!split || c->storage == LWACM_FP32);
+    // two_ok: steps are summed in pairs' chunks, an odd last one by itself
+    const unsigned pair_slices = two_ok ? (unsigned)nsteps & ~1u : 0u;
     float *mu_in = d_mu, *mu_out = d_mu_tmp;
     unsigned slice = 0;
     long long t = t0 + nsteps - 1;
@@ -1129,38 +1160,38 @@ int lwacm_adjoint_sweep(lwacm_ctx *c, const void *d_states, long long t0, int ns
         ReduceArgs r = reduce_args(c, nullptr, nullptr);  // partials only, added below
         r.partials = c->d_sweep + (size_t)slice * stride;
         hipError_t e;
+        int k = 1;  // steps of this launch
         if (multi) {
-            const int k = (int)(t - t0 + 1 < lwacm::kMultiSteps ? t - t0 + 1 : lwacm::kMultiSteps);
+            k = (int)(t - t0 + 1 < lwacm::kMultiSteps ? t - t0 + 1 : lwacm::kMultiSteps);
             e = lwacm::launch_adj_d2q9_multi(c->p, reinterpret_cast<const float *>(st), sb / 4,
                                              (int)(t - t0), k, t - k + 1 == 0, mu_in, mu_out,
                                              c->d_sweep, stride, slice, c->stream);
-            slice += (unsigned)k;
-            t -= k;
-        } else if (two_ok && t - 1 >= t0) {
+        } else if (pair_launch && t - 1 >= t0) {
+            k = 2;
             r.partials_b = r.partials + stride;
             e = lwacm::launch_adj_march2(c->p, c->storage, st + (size_t)(t - t0) * sb,
                                          st + (size_t)(t - 1 - t0) * sb, mu_in, mu_out,
-                                         t - 1 == 0, r, c->stream);
-            slice += 2;
-            t -= 2;
+                                         t - 1 == 0, r, c->stream, x, x ? x + c->p.n : nullptr);
+        } else if (tile) {
+            e = lwacm::launch_adj_march(c->p, c->storage, st + (size_t)(t - t0) * sb, mu_in, mu_out,
+                                        c->d_bits, c->d_wallg, t == 0, r, c->stream, x);
         } else {
-            if (tile)
-                e = lwacm::launch_adj_march(c->p, c->storage, st + (size_t)(t - t0) * sb, mu_in,
-                                            mu_out, c->d_bits, c->d_wallg, t == 0, r, c->stream);
-            else
-                e = lwacm::launch_adj_generic(c->p, c->storage, st + (size_t)(t - t0) * sb,
-                                              mu_in, mu_out, t == 0, r,
-                                              lwacm::generic_grid(c->p.n), c->stream);
-            slice += 1;
-            t -= 1;
+            e = lwacm::launch_adj_generic(c->p, c->storage, st + (size_t)(t - t0) * sb, mu_in,
+                                          mu_out, t == 0, r, nb1, c->stream);
         }
+        if (e == hipSuccess && split)
+            e = lwacm::launch_adj_dadomega(c->p, slice < pair_slices ? lwacm::adj2_depth(c->p)
+                                                                     : lwacm::adj_depth(c->p),
+                                           k, x, r.partials, stride, c->stream);
         if (e != hipSuccess) return LWACM_EDEVICE;
+        slice += (unsigned)k;
+        t -= k;
         float *tmp = mu_in;
         mu_in = mu_out;
         mu_out = tmp;
     }
     // the steps' dL/domega, added in the order separate calls add them
-    if (lwacm::launch_reduce_slices(c->d_sweep, stride, (unsigned)stride, slice,
+    if (lwacm::launch_reduce_slices(c->d_sweep, stride, nb2, pair_slices, nb1, slice,
                                     c->d_sweep + (size_t)nsteps * stride,
                                     2.0 / (c->omega * c->omega), d_dL_domega,
                                     c->stream) != hipSuccess)
@@ -1218,13 +1249,14 @@ int lwacm_step_static(int lattice, int nx, int ny, int nz, double omega, float *
     if (lwacm::march_supported(p)) {
         const int ncu = device_cus();
         p.march_nzc = lwacm::march_choose_depth(p, ncu);
-        const size_t sb = lwacm::march_scratch_blocks(p, ncu);
+        const size_t sb = lwacm::march_aligned(p) ? lwacm::march_scratch_blocks(p, ncu) : 0;
         if (sb > nb) nb = sb;
     }
     const size_t mb = lwacm::march_num_blocks(p);
-    if (mb > nb) nb = mb;
-    const size_t fb = lwacm::march2_num_blocks(p);
-    if (fb > nb) nb = fb;
+    if (mb > kStaticMaxBlocks && !lwacm::march_aligned(p))
+        c.variant = LWACM_KERNEL_GENERIC;  // ragged sides: the gather kernel's blocks always fit
+    else if (mb > nb)
+        nb = mb;
     if (nb > kStaticMaxBlocks) return LWACM_ESCRATCH;
     double *base = nullptr;
     const int rc = static_scratch(&base);

@@ -414,14 +414,16 @@ __global__ __launch_bounds__(kGenericBlock) void k_reduce_partials(ReduceArgs r,
     }
 }
 
-// The per-step block partials of a reverse sweep (one slice of `stride`
-// doubles per reduction, zero past each launch's own blocks): block s adds
-// slice s in the order of k_reduce_partials (extra zeros change no sum).
+// The per-step block partials of a reverse sweep (one reduction per slice of
+// `stride` doubles, nb_first or nb_rest of them filled): block s adds slice s
+// in the order of k_reduce_partials.
 __global__ __launch_bounds__(kGenericBlock) void k_reduce_slices(const double *partials,
-                                                                 size_t stride, unsigned nblocks,
+                                                                 size_t stride, unsigned nb_first,
+                                                                 unsigned nfirst, unsigned nb_rest,
                                                                  double *totals)
 {
     const double *slice = partials + (size_t)blockIdx.x * stride;
+    const unsigned nblocks = blockIdx.x < nfirst ? nb_first : nb_rest;
     double acc[1] = {0.0};
     for (unsigned b = threadIdx.x; b < nblocks; b += kReduceThreads) acc[0] += slice[b];
     block_sum<1>(acc);
@@ -429,25 +431,34 @@ __global__ __launch_bounds__(kGenericBlock) void k_reduce_slices(const double *p
 }
 
 // out += total_s * scale for s = 0, 1, ... in turn: what the reductions of
-// separate reverse-step calls add, in the same order.
-__global__ void k_accumulate_totals(const double *totals, unsigned n, double scale, double *out)
+// separate reverse-step calls add, in the same order.  One wave, so that the
+// totals arrive together and only the additions run one after the other.
+__global__ __launch_bounds__(kWave) void k_accumulate_totals(const double *totals, unsigned n,
+                                                             double scale, double *out)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ double t[kWave];
     double v = out[0];
-    for (unsigned s = 0; s < n; ++s) v += totals[s] * scale;
-    out[0] = v;
+    for (unsigned s0 = 0; s0 < n; s0 += kWave) {
+        if (s0 + threadIdx.x < n) t[threadIdx.x] = totals[s0 + threadIdx.x] * scale;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (unsigned s = 0; s < n - s0 && s < kWave; ++s) v += t[s];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[0] = v;
 }
 
 }  // namespace
 
-hipError_t launch_reduce_slices(const double *partials, size_t stride, unsigned nblocks,
-                                unsigned nslices, double *totals, double scale, double *out,
-                                hipStream_t s)
+hipError_t launch_reduce_slices(const double *partials, size_t stride, unsigned nb_first,
+                                unsigned nfirst, unsigned nb_rest, unsigned nslices,
+                                double *totals, double scale, double *out, hipStream_t s)
 {
     if (nslices == 0) return hipSuccess;
     // the thread count and tree of k_reduce_partials
-    k_reduce_slices<<<nslices, kReduceThreads, 0, s>>>(partials, stride, nblocks, totals);
-    k_accumulate_totals<<<1, 1, 0, s>>>(totals, nslices, scale, out);
+    k_reduce_slices<<<nslices, kReduceThreads, 0, s>>>(partials, stride, nb_first, nfirst, nb_rest,
+                                                       totals);
+    k_accumulate_totals<<<1, kWave, 0, s>>>(totals, nslices, scale, out);
     return hipGetLastError();
 }
 

@@ -45,7 +45,6 @@ struct ProblemArgs {
     // moving-wall sums
     const float4 *corr;
     int march_nzc;           // planes per workgroup of the forward tile kernels (0: unused)
-    int adj_nzc;             // and of the reverse ones
     // the temperature step fused into the single-step tile kernel (thermal
     // problems, march_thermal_supported): T at the step's time and one step
     // later, h = 2/omega_t - 1 and kap = 2 - 2/omega_t; T_in null: no fusion
@@ -85,12 +84,12 @@ struct ReduceArgs {
 // Second pass of a grid reduction over nblocks blocks of NV (1 or 2) values.
 hipError_t launch_reduce(const ReduceArgs &r, int nv, unsigned nblocks, hipStream_t stream);
 // The block partials of several reverse steps, one slice of `stride` doubles
-// each (zero-padded past the launch's own blocks, nblocks the largest count):
+// each, nb_first of them in the first nfirst slices and nb_rest in the rest:
 // *out += total_s * scale for each slice s in order, as separate calls of the
 // reverse step add them.
-hipError_t launch_reduce_slices(const double *partials, size_t stride, unsigned nblocks,
-                                unsigned nslices, double *totals, double scale, double *out,
-                                hipStream_t stream);
+hipError_t launch_reduce_slices(const double *partials, size_t stride, unsigned nb_first,
+                                unsigned nfirst, unsigned nb_rest, unsigned nslices,
+                                double *totals, double scale, double *out, hipStream_t stream);
 
 // The forward launchers store per-block partials only; the caller runs the
 // second pass (launch_reduce, or deferred into the next step's launch).
@@ -117,6 +116,7 @@ hipError_t launch_mask_scan(const ProblemArgs &p, unsigned *d_out2, hipStream_t 
 // classes and solid-upstream bit sets made by launch_classify (n bytes and
 // n unsigned).  Returns hipErrorNotSupported if the problem does not fit.
 bool march_supported(const ProblemArgs &p);
+bool march_aligned(const ProblemArgs &p);  // nx and ny are multiples of the 32 x 16 tile
 int march_choose_depth(const ProblemArgs &p, int ncu);  // chunk depth for a device of ncu CUs
 // Blocks a context's reduction scratch holds at least, whatever depth is
 // chosen: those of the best of the depths a caller may set (32, 64, 128).
@@ -132,12 +132,21 @@ hipError_t launch_classify(const ProblemArgs &p, uint8_t *cls, unsigned *bits, f
 // final_t0.  Masked problems need the bit sets (and wallg for moving walls)
 // of launch_classify.
 bool adj_march_supported(const ProblemArgs &p);
-int adj_march_depth(const ProblemArgs &p);  // p.adj_nzc, at most nz
+int adj_depth(const ProblemArgs &p);        // chunk depth of the one-step kernel
+// Chunk depth that fills the chip (the forward kernels'), for launches that
+// write the factors (rho, x) of the nodes' dL/da = rho x (n pairs, no walls)
+// instead of block partials; launch_adj_dadomega then adds the partials of
+// nsteps such steps as launches of depth nzc would have: step s = 0 ..
+// nsteps - 1 has its factors at x + s * n, its partials at partials + s * stride.
+int adj_split_depth(const ProblemArgs &p);
+unsigned adj_blocks(const ProblemArgs &p, int nzc);
+hipError_t launch_adj_dadomega(const ProblemArgs &p, int nzc, int nsteps, const float2 *x,
+                               double *partials, size_t stride, hipStream_t stream);
 unsigned adj_march_num_blocks(const ProblemArgs &p);
 hipError_t launch_adj_march(const ProblemArgs &p, int storage, const void *state,
                             const float *mu_in, float *mu_out, const unsigned *bits,
                             const float4 *wallg, int final_t0, const ReduceArgs &r,
-                            hipStream_t stream);
+                            hipStream_t stream, float2 *x = nullptr);
 // D3Q19 single-step tile kernel with the temperature step in the same pass
 // (p.T_in, p.T_out): FP32 or FP16 state, no walls or halfway walls (with the
 // table p.T_wall), no force, omega_p or wall correction.
@@ -151,10 +160,12 @@ hipError_t launch_fwd_march(const ProblemArgs &p, int storage, const void *src, 
 // the two steps' dL/da partials in r.partials and r.partials_b (one double
 // per block each) and adds them to r.out in that order.
 bool adj_march2_supported(const ProblemArgs &p);
+int adj2_depth(const ProblemArgs &p);  // its chunk depth
 unsigned adj_march2_num_blocks(const ProblemArgs &p);
 hipError_t launch_adj_march2(const ProblemArgs &p, int storage, const void *state_t,
                              const void *state_tm1, const float *mu_in, float *mu_out,
-                             int final_t0, const ReduceArgs &r, hipStream_t stream);
+                             int final_t0, const ReduceArgs &r, hipStream_t stream,
+                             float2 *xa = nullptr, float2 *xb = nullptr);
 // Two D3Q19 forward steps per launch on FP32 state (same tiles as the
 // single-step kernel, its chunk depth at most nz; halfway
 // walls (bb_bits and wallg from k_classify), no body force, no separate

@@ -331,8 +331,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
         active = lane < 2 * (TY + 2);
         if (!active) ly = 0;
     }
-    const int gx = wrap_index(ti.tile_x * TX + lx, nx);
-    const int gy = wrap_index(ti.tile_y * TY + ly, ny);
+    const int gx = wrap_index(ti.x0 + lx, nx);
+    const int gy = wrap_index(ti.y0 + ly, ny);
     const unsigned col = (unsigned)(gy * nx + gx);
     const int slot = (ly + 1) * SX + (lx + 1);
     const int wslot = active ? slot : NSLOT;
@@ -529,6 +529,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
         });
     }
 
+    // columns shared with the tile before (a ragged side) are its to count
+    if (gx < ti.xs || gy < ti.ys) mass = energy = 0.0f;
     double v[2] = {(double)mass, 0.5 * (double)energy};
     store_block_partials<2>(v, r.partials, blockIdx.x);
     if (blockIdx.x == 0 && r.prev_nblocks)
@@ -681,6 +683,8 @@ hipError_t dispatch(const ProblemArgs &p, const void *src, void *dst, const uint
 
 }  // namespace
 
+bool march_aligned(const ProblemArgs &p) { return p.nx % TX == 0 && p.ny % TY == 0; }
+
 bool march_supported(const ProblemArgs &p)
 {
     // 32-bit byte offsets inside a state buffer: n * 16 bytes < 4 GiB
@@ -690,13 +694,14 @@ bool march_supported(const ProblemArgs &p)
     // per-step wall correction (p.corr)
     const bool split_ok = !p.split || (!p.mask && p.nz >= 8);
     const bool force_ok = !p.has_force || (!p.split && p.nz >= 8);
-    return p.Q == 19 && force_ok && split_ok && ((!p.qd && !p.uwl) || p.corr) && p.nx >= TX && p.ny >= TY && p.nx % TX == 0 &&
-           p.ny % TY == 0 && p.nz >= 1 && p.n < (1LL << 28);
+    // sides that are no multiples of the tile on the rolled kernel
+    return p.Q == 19 && force_ok && split_ok && ((!p.qd && !p.uwl) || p.corr) && p.nx >= TX &&
+           p.ny >= TY && (p.nz >= 8 || march_aligned(p)) && p.n < (1LL << 28);
 }
 
 static long long march_blocks_for(const ProblemArgs &p, int nzc)
 {
-    const long long tiles = (long long)(p.nx / TX) * (p.ny / TY);
+    const long long tiles = (long long)((p.nx + TX - 1) / TX) * ((p.ny + TY - 1) / TY);
     return tiles * ((p.nz + nzc - 1) / nzc);
 }
 

@@ -121,8 +121,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int nzc,
     const int lx = c2.lx, ly = c2.ly;
     const float sgn = c2.sgn;
     const bool isY = c2.isY, active = c2.active;
-    const int gx = wrap_index(ti.tile_x * TX + lx, nx);
-    const int gy = wrap_index(ti.tile_y * TY + ly, ny);
+    const int gx = wrap_index(ti.x0 + lx, nx);
+    const int gy = wrap_index(ti.y0 + ly, ny);
     const unsigned col = (unsigned)(gy * nx + gx);  // offset inside a plane (< 2^31)
     const int slot1 = (ly + 2) * SX1 + (lx + 2);
     const int slot2 = (ly + 1) * SX2 + (lx + 1);    // tile and first ring only
@@ -277,6 +277,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int nzc,
         });
     }
 
+    // columns shared with the tile before (a ragged side) are its to count
+    if (gx < ti.xs || gy < ti.ys) m1 = e1 = m2 = e2 = 0.0f;
     double sums[4] = {(double)m1, 0.5 * (double)e1, (double)m2, 0.5 * (double)e2};
     block_sum<4>(sums);
     if (tid == 0) {
@@ -304,8 +306,7 @@ bool march2_supported(const ProblemArgs &p)
 unsigned march2_num_blocks(const ProblemArgs &p)
 {
     if (!march2_supported(p)) return 0;
-    const int c = march2_nzc(p);
-    return (unsigned)((long long)(p.nx / TX) * (p.ny / TY) * ((p.nz + c - 1) / c));
+    return march_num_blocks(p);  // the same tiles and chunks
 }
 
 template <bool MASK>

@@ -874,10 +874,16 @@ __device__ __forceinline__ Col2 col2_of(int tid)
     return c;
 }
 
-// Workgroup -> (tile_x, tile_y, chunk) with an XCD-aware order: consecutive
-// workgroups of one XCD get neighbouring tiles.
+// Workgroup -> tile and chunk with an XCD-aware order: consecutive workgroups
+// of one XCD get neighbouring tiles.  A side that is no multiple of the tile
+// has its last tile moved back to end at the side (as a ragged last chunk is
+// moved down): the columns it shares with the tile before are computed twice
+// with the same bits and counted in the sums once, by the columns from
+// (xs, ys) on.
 struct TileIdx {
-    int tile_x, tile_y, zc;
+    int x0, y0;  // first column and row of the tile
+    int xs, ys;  // first column and row it counts in the sums
+    int zc;      // chunk
 };
 
 __device__ __forceinline__ TileIdx tile_of_block(int nx, int ny, int TXv, int TYv)
@@ -885,13 +891,15 @@ __device__ __forceinline__ TileIdx tile_of_block(int nx, int ny, int TXv, int TY
     const unsigned nb = gridDim.x;
     const unsigned b = blockIdx.x;
     const unsigned lb = (nb % 8u == 0u) ? (b % 8u) * (nb / 8u) + b / 8u : b;
-    const int tiles_x = nx / TXv;
-    const int tiles_y = ny / TYv;
+    const unsigned tiles_x = (unsigned)((nx + TXv - 1) / TXv);
+    const unsigned tiles_y = (unsigned)((ny + TYv - 1) / TYv);
+    const unsigned rest = lb / tiles_x;
     TileIdx t;
-    t.tile_x = (int)(lb % (unsigned)tiles_x);
-    const unsigned rest = lb / (unsigned)tiles_x;
-    t.tile_y = (int)(rest % (unsigned)tiles_y);
-    t.zc = (int)(rest / (unsigned)tiles_y);
+    t.xs = (int)(lb % tiles_x) * TXv;
+    t.ys = (int)(rest % tiles_y) * TYv;
+    t.x0 = min(t.xs, nx - TXv);
+    t.y0 = min(t.ys, ny - TYv);
+    t.zc = (int)(rest / tiles_y);
     return t;
 }
 

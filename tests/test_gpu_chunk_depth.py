@@ -1,9 +1,9 @@
 """Chunk depths of the D3Q19 tile kernels are any number of planes: the depth
 lwacm_init picks (unequal remainders of the rolled plane loop, a ragged last
 chunk) against one chunk over all planes, bitwise in the fields for every
-forward kernel, and the reverse kernels of the same depths against the
-generic reverse step (2e-6, the bound of the other comparisons of the two)
-and each other (bitwise)."""
+forward kernel, and the reverse kernels on such grids against the generic
+reverse step (2e-6, the bound of the other comparisons of the two) and each
+other (mu bitwise, dL/domega to the FP32 rounding of its partial sums)."""
 import numpy as np
 import pytest
 import torch
@@ -87,7 +87,7 @@ def test_reverse_steps_of_any_depth(nz, walls, final):
     c = torch.empty_like(mu0)
     dw = torch.zeros(1, dtype=torch.float64, device="cuda")
     if L.lwacm_adjoint_step2(s.ctx, st1, st0, mu0, c, dw, final):
-        assert torch.equal(a, c) and wa == float(dw.item())
+        assert torch.equal(a, c) and abs(wa - float(dw.item())) <= 1e-6 * abs(wa) + 1e-9
     else:
         assert walls
     s.close()
