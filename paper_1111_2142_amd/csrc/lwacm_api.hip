@@ -170,10 +170,26 @@ bool use_multi(const lwacm_ctx *c)
            lwacm::d2q9_multi_num_blocks(c->p) <= c->n_partial_blocks;
 }
 
+// The temperature step rides in the flow's tile kernel (the flow's own
+// temperature lattice).
+bool fuses_thermal(const lwacm_ctx *c)
+{
+    return c->thermal && c->targs.QT == c->p.Q && lwacm::march_thermal_supported(c->p);
+}
+
+// Grids whose sides are no multiples of the 32 x 16 tile run the tile kernel
+// with a temperature (FP32 state), where it replaces two gather kernels: with walls at every
+// size (22 -> 14 us a step at 33x17x8, 99 -> 25 at 100^3, 258 -> 52 at 150^3),
+// without from about 10^5 nodes on (its shortest chunk takes 11 us on any
+// grid: 10.2 against 10.9 us at 33x17x40, 12.6 / 11.1 at 50^3, 40 / 17.6 at
+// 100^3, gather / tiles).  Without a temperature they stay on the gather
+// kernels, whose results the tile kernels reproduce only to FP32 rounding.
 bool use_march(const lwacm_ctx *c)
 {
     if (c->variant == LWACM_KERNEL_GENERIC || c->semi_implicit) return false;
-    return lwacm::march_supported(c->p) && lwacm::march_aligned(c->p);
+    if (!lwacm::march_supported(c->p)) return false;
+    return lwacm::march_aligned(c->p) ||
+           (c->storage == LWACM_FP32 && fuses_thermal(c) && (c->p.mask || c->p.n >= 100000));
 }
 
 bool use_adj_march(const lwacm_ctx *c)
@@ -856,8 +872,7 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
         // tile kernel where it can, else by a kernel of its own that reads the
         // state this step's flow kernel reads, before that kernel runs
         ProblemArgs pl = c->p;
-        const bool tfuse = c->thermal && march && !two && c->targs.QT == c->p.Q &&
-                           lwacm::march_thermal_supported(c->p);
+        const bool tfuse = march && !two && fuses_thermal(c);
         if (tfuse) {
             pl.T_in = c->T_buf[c->tcur];
             pl.T_out = c->T_buf[c->tcur ^ 1];
