@@ -22,7 +22,7 @@ struct lwacm_ctx {
     int lattice;
     int storage;
     int variant;  // requested LWACM_KERNEL_*
-    int ncu;      // compute units of the device (tile-kernel problems)
+    int ncu;      // compute units of the device
     bool force;
     double omega;
     double omega_p;  // relaxation of the density update (== omega: single relaxation)
@@ -467,8 +467,16 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
     unforced.has_force = 0;
     unforced.qd = nullptr;  // interpolated walls run on the tiles with the wall correction
     size_t nb = lwacm::kGenericMaxBlocks;
+    c->ncu = device_cus();
+    if (lattice == LWACM_D2Q9) {
+        p.multi_tile = 16;  // the most blocks: link velocities, which may be set later
+        const size_t qb = d_mask ? lwacm::d2q9_multi_num_blocks(p) : 0;
+        p.multi_tile = lwacm::d2q9_multi_choose_tile(p, c->ncu);
+        const size_t tb = lwacm::d2q9_multi_num_blocks(p);
+        nb = qb > nb ? qb : nb;
+        nb = tb > nb ? tb : nb;
+    }
     if (lwacm::march_supported(unforced)) {
-        c->ncu = device_cus();
         p.march_nzc = unforced.march_nzc = lwacm::march_choose_depth(p, c->ncu);
         const size_t sb = lwacm::march_aligned(p) ? lwacm::march_scratch_blocks(p, c->ncu) : 0;
         if (sb > nb) nb = sb;
@@ -1273,11 +1281,12 @@ int lwacm_step_static(int lattice, int nx, int ny, int nz, double omega, float *
     else if (mb > nb)
         nb = mb;
     if (nb > kStaticMaxBlocks) return LWACM_ESCRATCH;
+    if (lattice == LWACM_D2Q9) p.multi_tile = lwacm::d2q9_multi_choose_tile(p, device_cus());
     double *base = nullptr;
     const int rc = static_scratch(&base);
     if (rc != LWACM_OK) return rc;
     c.d_partials = base;
-    c.n_partial_blocks = nb;
+    c.n_partial_blocks = kStaticMaxBlocks;
     c.d_diag = d_diag ? d_diag : base + 8 * kStaticMaxBlocks;
     c.n_fluid = (unsigned long long)p.n;
     const int code = lwacm_step(&c, nsteps);

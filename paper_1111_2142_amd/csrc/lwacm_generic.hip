@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kGenericBlock) void k_fwd_generic(ProblemArgs p, co
             B = node_B(u);
         };
         float out[D + 1], e;
-        link_update<Q, MASK, FORCE, SPLIT>(p, idx, drx, ux, node_B(ux), fmask, fstate, out, e);
+        link_update<Q, MASK, FORCE, SPLIT>(p, GlobalSite<Q>{p, idx}, drx, ux, node_B(ux), fmask, fstate, out, e);
         if (std::is_same<T, __half>::value && p.fp16_sr) {
             NodeState<T, D + 1>::store_sr(dst, idx, out, p.st_scale,
                                           sr_words((uint32_t)idx, p.sr_word));

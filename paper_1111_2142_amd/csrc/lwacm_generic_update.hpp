@@ -48,8 +48,67 @@ __device__ __forceinline__ void accum(float &acc, bool &set, float t)
     set = true;
 }
 
+// The new (rho - 1, u) of a node and |u|^2 from its link sums (36 w_i times 1
+// and v_i): post-combine and normalisation.
+template <int D>
+__device__ __forceinline__ void finish_node(const ProblemArgs &p, float rx, const float (&ux)[3],
+                                            float D36, const float (&J36)[D], float (&out)[D + 1],
+                                            float &e)
+{
+    const float Dsum = div36(D36);
+    // post-combine: sum_i v_i a f^(e,o)_i(x) = a rho_x u_x
+    float J[3];
+#pragma unroll
+    for (int k = 0; k < D; ++k) J[k] = fmaf(p.a * rx, ux[k], div36(J36[k]));
+    // u = J / (1 + D) evaluated as J - J * (D / (1 + D)): the rounding of
+    // 1 + D then only touches the small correction term, which keeps the
+    // FP32 error from accumulating over long runs.
+    const float q = normalisation_factor(Dsum);
+    e = 0.0f;
+    out[0] = Dsum;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        out[k + 1] = fmaf(-J[k], q, J[k]);
+        e = fmaf(out[k + 1], out[k + 1], e);
+    }
+}
+
+// What link_update needs besides the states: the acceleration at the node,
+// the wall-motion term v_i . uw of link i whose upstream node is solid (id m;
+// ib its opposite, the link into the wall), the same for a separate omega_p,
+// and the link-wall distance q of link ib (has_q: interpolated walls).  Here
+// from global memory; the multi-step D2Q9 kernel has them in LDS.
+template <int Q>
+struct GlobalSite {
+    const ProblemArgs &p;
+    long long idx;
+    __device__ __forceinline__ float g(int k) const
+    {
+        return p.g_field ? p.g_field[(long long)k * p.n + idx] : p.g[k];
+    }
+    __device__ __forceinline__ float wall(int i, int ib, uint8_t m) const
+    {
+        float uw[3] = {p.wall_term[m][0], p.wall_term[m][1], p.wall_term[m][2]};
+        if (p.uwl) {
+            // the wall's velocity where the link x -> x + v_ib crosses it
+#pragma unroll
+            for (int k = 0; k < Lattice<Q>::D; ++k)
+                uw[k] = p.wall_scale * p.uwl[((long long)ib * Lattice<Q>::D + k) * p.n + idx];
+        }
+        return vdot<Q>(i, uw);
+    }
+    __device__ __forceinline__ float wall_p(int i, uint8_t m) const
+    {
+        const float uw[3] = {p.wall_term_p[m][0], p.wall_term_p[m][1], p.wall_term_p[m][2]};
+        return vdot<Q>(i, uw);
+    }
+    __device__ __forceinline__ bool has_q() const { return p.qd != nullptr; }
+    __device__ __forceinline__ float q(int ib) const { return p.qd[(long long)ib * p.n + idx]; }
+};
+
 // The update of one fluid node x (Eq. ACM2.0 in pull form with the wall,
-// forcing and omega_p rules below), given its state (drx, ux, Bx = node_B(ux))
+// forcing and omega_p rules below), given its state (drx, ux, Bx = node_B(ux)),
+// its site (see above)
 // and two accessors of the nodes x + (dx, dy, dz): fmask(dx, dy, dz) returns
 // the mask value, fstate(dx, dy, dz, dr, u, B) the state and its node_B.  Writes the new (rho - 1, u) to
 // out and |u|^2 to e.  Shared by the one-step kernel (accessors read global
@@ -60,15 +119,14 @@ __device__ __forceinline__ void accum(float &acc, bool &set, float t)
 // "finite-difference formulation", item 3; Appendix E).  The density sums the
 // same link terms with Ap = 3 (2/omega_p - 1) in place of A (and the moving
 // wall's omega_p term); the momentum keeps A.
-template <int Q, bool MASK, bool FORCE, bool SPLIT, class FMask, class FState>
-__device__ __forceinline__ void link_update(const ProblemArgs &p, long long idx, float drx,
+template <int Q, bool MASK, bool FORCE, bool SPLIT, class FSite, class FMask, class FState>
+__device__ __forceinline__ void link_update(const ProblemArgs &p, const FSite &site, float drx,
                                             const float (&ux)[3], float Bx, const FMask &fmask,
                                             const FState &fstate,
                                             float (&out)[Lattice<Q>::D + 1], float &e)
 {
     using L = Lattice<Q>;
     constexpr int D = L::D;
-    const long long n = p.n;
     const float rx = 1.0f + drx;
     // Forcing (Eq. force) adds the odd part 3 w_i rho_x (v_i . g) to every
     // population.  It enters each link term through the addend of its FMA,
@@ -79,7 +137,7 @@ __device__ __forceinline__ void link_update(const ProblemArgs &p, long long idx,
     if (FORCE)
 #pragma unroll
         for (int k = 0; k < D; ++k)
-            g3[k] = 3.0f * rx * (p.g_field ? p.g_field[(long long)k * n + idx] : p.g[k]);
+            g3[k] = 3.0f * rx * site.g(k);
     float D36 = 0.0f, J36[3] = {0.0f, 0.0f, 0.0f};
     bool dset = false, jset[3] = {false, false, false};
 #pragma unroll
@@ -98,21 +156,14 @@ __device__ __forceinline__ void link_update(const ProblemArgs &p, long long idx,
         } else if (MASK && m != 0) {
             // bounce-back: own term of the opposite link + moving wall
             const int ib = link_opp(i);
-            float uw[3] = {p.wall_term[m][0], p.wall_term[m][1], p.wall_term[m][2]};
-            if (p.uwl) {
-                // the wall's velocity where the link x -> x + v_ib crosses it
-#pragma unroll
-                for (int k = 0; k < D; ++k)
-                    uw[k] = p.wall_scale * p.uwl[((long long)ib * D + k) * n + idx];
-            }
             const float cb = vdot<Q>(ib, ux);
             float sb = link_term_unweighted(addf(drx), rx, cb, Bx, p.A);
             float wsc = 1.0f;  // scale of the halfway moving-wall term
-            if (p.qd) {
+            if (site.has_q()) {
                 // interpolated bounce-back (Eq. ACM2.0cc): the wall cuts the
                 // link x -> x + v_ib at the fraction q; the terms are in
                 // deviation form, whose mixing weights sum to one
-                const float qv = p.qd[(long long)ib * n + idx];
+                const float qv = site.q(ib);
                 if (qv < 0.5f) {
                     if (fmask(link_cx(i), link_cy(i), link_cz(i)) == 0) {  // x - v_ib fluid
                         float drz, uz[3], Bz;
@@ -128,11 +179,9 @@ __device__ __forceinline__ void link_update(const ProblemArgs &p, long long idx,
                     wsc = h;  // Eq. ACM2.0move: 1/q in place of 2
                 }
             }
-            s = fmaf(wsc, vdot<Q>(i, uw), sb);
+            s = fmaf(wsc, site.wall(i, ib, m), sb);
             if (SPLIT) {
-                const float uwp[3] = {p.wall_term_p[m][0], p.wall_term_p[m][1],
-                                      p.wall_term_p[m][2]};
-                sp = link_term_unweighted(addf(drx), rx, cb, Bx, p.Ap) + vdot<Q>(i, uwp);
+                sp = link_term_unweighted(addf(drx), rx, cb, Bx, p.Ap) + site.wall_p(i, m);
             }
         } else {
             float dry, uy[3], By;
@@ -147,22 +196,10 @@ __device__ __forceinline__ void link_update(const ProblemArgs &p, long long idx,
         if (link_cy(i) != 0) accum(J36[1], jset[1], link_cy(i) > 0 ? s : -s);
         if (link_cz(i) != 0) accum(J36[2], jset[2], link_cz(i) > 0 ? s : -s);
     }
-    const float Dsum = div36(D36);
-    // post-combine: sum_i v_i a f^(e,o)_i(x) = a rho_x u_x
-    float J[3];
+    float Jd[D];
 #pragma unroll
-    for (int k = 0; k < D; ++k) J[k] = fmaf(p.a * rx, ux[k], div36(J36[k]));
-    // u = J / (1 + D) evaluated as J - J * (D / (1 + D)): the rounding of
-    // 1 + D then only touches the small correction term, which keeps the
-    // FP32 error from accumulating over long runs.
-    const float q = normalisation_factor(Dsum);
-    e = 0.0f;
-    out[0] = Dsum;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        out[k + 1] = fmaf(-J[k], q, J[k]);
-        e = fmaf(out[k + 1], out[k + 1], e);
-    }
+    for (int k = 0; k < D; ++k) Jd[k] = J36[k];
+    finish_node<D>(p, rx, ux, D36, Jd, out, e);
 }
 
 // The reverse step at one fluid node y (the exact derivative of link_update,

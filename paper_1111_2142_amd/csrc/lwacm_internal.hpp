@@ -45,6 +45,7 @@ struct ProblemArgs {
     // moving-wall sums
     const float4 *corr;
     int march_nzc;           // planes per workgroup of the forward tile kernels (0: unused)
+    int multi_tile;          // tile side of the multi-step D2Q9 kernels (0: unused)
     // the temperature step fused into the single-step tile kernel (thermal
     // problems, march_thermal_supported): T at the step's time and one step
     // later, h = 2/omega_t - 1 and kap = 2 - 2/omega_t; T_in null: no fusion
@@ -178,11 +179,12 @@ hipError_t launch_fwd_march2(const ProblemArgs &p, const float *src, float *dst,
                              const unsigned *bb_bits, const float4 *wallg, const ReduceArgs &r,
                              hipStream_t stream);
 
-// Several D2Q9 steps per launch (FP32 storage; no link-wall distances, link
-// velocities, omega_p or force field): 32 x 32 output tiles, up to
-// kMultiSteps steps per launch in LDS, one partial pair per tile.
-constexpr int kMultiTile = 32;
+// Several D2Q9 steps per launch (FP32 storage): tiles of p.multi_tile output
+// nodes a side (8, 16 or 32; at most 16 with link-wall distances or link
+// velocities), up to kMultiSteps steps per launch in LDS, one partial pair per
+// tile.
 constexpr int kMultiSteps = 8;
+int d2q9_multi_choose_tile(const ProblemArgs &p, int ncu);  // for a device of ncu CUs
 bool d2q9_multi_supported(const ProblemArgs &p);
 unsigned d2q9_multi_num_blocks(const ProblemArgs &p);
 // Up to kMultiSteps D2Q9 reverse steps per launch (FP32, the forward
