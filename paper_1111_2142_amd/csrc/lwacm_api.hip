@@ -192,6 +192,28 @@ bool use_march(const lwacm_ctx *c)
            (c->storage == LWACM_FP32 && fuses_thermal(c) && (c->p.mask || c->p.n >= 100000));
 }
 
+// The other D3Q19 problems: column-marching gathers, with walls once the wall
+// list is there (a step at 33x17x8 7.8 us against the generic kernel's 13.2, at
+// 150x84x75 with link distances and a force 19 against 73).  Without walls the
+// generic kernel is the faster one on small grids: 6.1 against 6.0 us at 33x17x8,
+// 7.9 / 6.6 at 50^3, 11.8 / 9.0 at 75^3; FP16 6.7 / 7.4 at 50^3, 13.5 / 11.5 at 75^3; reverse
+// 6.3 / 7.9 at 33^3, 9.1 / 8.6 at 50^3, 16.0 / 13.0 at 75^3 (generic / columns).
+bool use_column(const lwacm_ctx *c)
+{
+    return c->variant == LWACM_KERNEL_AUTO && !c->semi_implicit && !use_march(c) &&
+           lwacm::column_supported(c->p) &&
+           (c->p.mask ? c->d_cls && c->wlist_built
+                      : c->p.n >= (c->storage == LWACM_FP32 ? 100000 : 250000)) &&
+           lwacm::column_num_blocks(c->p, c->n_wlist) <= c->n_partial_blocks;
+}
+
+bool use_adj_column(const lwacm_ctx *c)
+{
+    return c->variant == LWACM_KERNEL_AUTO && !lwacm::adj_march_supported(c->p) && !c->p.mask &&
+           lwacm::column_supported(c->p) && c->p.n >= 100000 &&
+           lwacm::column_num_blocks(c->p, 0) <= c->n_partial_blocks;
+}
+
 bool use_adj_march(const lwacm_ctx *c)
 {
     return c->variant != LWACM_KERNEL_GENERIC && lwacm::adj_march_supported(c->p);
@@ -293,7 +315,8 @@ int enable_wall_correction(lwacm_ctx *c)
     g.qd = nullptr;
     g.uwl = nullptr;
     g.corr = nullptr;
-    if (!c->p.mask || !c->d_bits || !lwacm::march_supported(g)) return LWACM_OK;
+    if (!c->p.mask || !c->d_bits || !lwacm::march_supported(g) || !lwacm::march_aligned(g))
+        return LWACM_OK;
     const int rc = ensure_wall_list(c);
     if (rc != LWACM_OK) return rc == LWACM_EUNSUPPORTED ? LWACM_OK : rc;
     // the correction kernel addresses the packed q (18 per listed node) and
@@ -468,6 +491,7 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
     unforced.qd = nullptr;  // interpolated walls run on the tiles with the wall correction
     size_t nb = lwacm::kGenericMaxBlocks;
     c->ncu = device_cus();
+    if (lattice == LWACM_D3Q19) p.col_nzc = lwacm::column_choose_depth(p, c->ncu);
     if (lattice == LWACM_D2Q9) {
         p.multi_tile = 16;  // the most blocks: link velocities, which may be set later
         const size_t qb = d_mask ? lwacm::d2q9_multi_num_blocks(p) : 0;
@@ -481,6 +505,9 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
         const size_t sb = lwacm::march_aligned(p) ? lwacm::march_scratch_blocks(p, c->ncu) : 0;
         if (sb > nb) nb = sb;
     }
+    const size_t cb = !d_mask && lwacm::column_supported(p) && !lwacm::march_aligned(p)
+                          ? lwacm::column_num_blocks(p, 0) : 0;
+    if (cb > nb) nb = cb;
     const size_t mb = lwacm::march_num_blocks(unforced);
     if (mb > nb) nb = mb;
     const size_t ab = lwacm::adj_march_num_blocks(unforced);
@@ -521,8 +548,7 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
             }
             c->n_fluid = scan[1];
         }
-        if (e == hipSuccess &&
-            (lwacm::march_supported(unforced) || lwacm::adj_march_supported(unforced))) {
+        if (e == hipSuccess && lwacm::column_supported(p)) {  // D3Q19
             bool moving = false;
             for (int m = 1; m < lwacm::kMaxWallIds; ++m)
                 for (int k = 0; k < 3; ++k) moving = moving || p.wall_u[m][k] != 0.0f;
@@ -549,6 +575,21 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
             free_scratch(c);
             delete c;
             return rc;
+        }
+    }
+    if (d_mask && lwacm::column_supported(p) &&
+        (!lwacm::march_aligned(p) || !lwacm::march_supported(unforced))) {
+        // the column kernels' list of nodes next to a wall (without it the
+        // problem runs on the generic kernel)
+        const int rc = ensure_wall_list(c);
+        const size_t lb = rc == LWACM_OK ? lwacm::column_num_blocks(p, c->n_wlist) : 0;
+        if (lb > c->n_partial_blocks) {
+            double *grown = nullptr;
+            if (hipMalloc(&grown, 8 * lb * sizeof(double)) == hipSuccess) {
+                (void)hipFree(c->d_partials);
+                c->d_partials = grown;
+                c->n_partial_blocks = lb;
+            }
         }
     }
     *out = c;
@@ -836,10 +877,12 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
     if (!c || nsteps < 0) return LWACM_EINVAL;
     const bool march = use_march(c);
     const bool fuse = march && use_march2(c);
+    const bool column = !march && use_column(c);
     const bool multi = !march && use_multi(c);
     const unsigned nb1 = march ? lwacm::march_num_blocks(c->p)
-                               : (multi ? lwacm::d2q9_multi_num_blocks(c->p)
-                                        : lwacm::generic_grid(c->p.n));
+                         : column ? lwacm::column_num_blocks(c->p, c->n_wlist)
+                         : multi  ? lwacm::d2q9_multi_num_blocks(c->p)
+                                  : lwacm::generic_grid(c->p.n);
     const unsigned nb2 = fuse ? lwacm::march2_num_blocks(c->p) : 0u;
     const size_t set = 2 * c->n_partial_blocks;  // doubles per partial set
     // Steps whose partials are stored but not yet added up (oldest first): the
@@ -909,6 +952,9 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
         else if (march)
             e = lwacm::launch_fwd_march(pl, c->storage, src, dst, c->d_cls, c->d_bits,
                                         c->d_wallg, r, c->stream);
+        else if (column)
+            e = lwacm::launch_fwd_column(c->p, c->storage, src, dst, c->d_cls, c->d_wlist,
+                                         c->n_wlist, r, c->stream);
         else if (multi)
             e = lwacm::launch_fwd_d2q9_multi(c->p, static_cast<const float *>(src),
                                              static_cast<float *>(dst), kk, r, c->stream);
@@ -1033,6 +1079,9 @@ int lwacm_adjoint_step(lwacm_ctx *c, const void *d_state_t, const float *d_mu_in
     if (use_adj_march(c))
         return dev_err(lwacm::launch_adj_march(c->p, c->storage, d_state_t, d_mu_in, d_mu_out,
                                                c->d_bits, c->d_wallg, final_t0, r, c->stream));
+    if (use_adj_column(c))
+        return dev_err(lwacm::launch_adj_column(c->p, c->storage, d_state_t, d_mu_in, d_mu_out,
+                                                final_t0, r, c->stream));
     return dev_err(lwacm::launch_adj_generic(c->p, c->storage, d_state_t, d_mu_in, d_mu_out,
                                              final_t0, r, lwacm::generic_grid(c->p.n), c->stream));
 }
@@ -1065,10 +1114,9 @@ int lwacm_forward_states(lwacm_ctx *c, const void *d_state0, long long t0, int n
     const char *s0 = static_cast<const char *>(d_state0);
     if (s0 + sb > lo && s0 < lo + (size_t)nsteps * sb) return LWACM_EINVAL;  // overlap
     const bool march = use_march(c);
+    const bool column = !march && use_column(c);
     const bool multi = !march && use_multi(c);
-    const unsigned nb1 = march ? lwacm::march_num_blocks(c->p)
-                               : (multi ? lwacm::d2q9_multi_num_blocks(c->p)
-                                        : lwacm::generic_grid(c->p.n));
+    const unsigned nb1 = lwacm::generic_grid(c->p.n);
     // The masked tile kernels leave solid nodes unwritten (the context's two
     // buffers both hold them): the slots get them from d_state0 first.
     if (march && c->p.mask)
@@ -1105,9 +1153,9 @@ int lwacm_forward_states(lwacm_ctx *c, const void *d_state0, long long t0, int n
             if (march)
                 e = lwacm::launch_fwd_march(pl, c->storage, src, dst, c->d_cls, c->d_bits,
                                             c->d_wallg, r, c->stream);
-            else if (multi)
-                e = lwacm::launch_fwd_d2q9_multi(pl, static_cast<const float *>(src),
-                                                 static_cast<float *>(dst), 1, r, c->stream);
+            else if (column)
+                e = lwacm::launch_fwd_column(pl, c->storage, src, dst, c->d_cls, c->d_wlist,
+                                             c->n_wlist, r, c->stream);
             else
                 e = lwacm::launch_fwd_generic(pl, c->storage, pl.has_force != 0, src, dst, r, nb1,
                                               c->stream);
@@ -1149,9 +1197,11 @@ int lwacm_adjoint_sweep(lwacm_ctx *c, const void *d_states, long long t0, int ns
                        lwacm::d2q9_multi_num_blocks(c->p) <= c->n_partial_blocks;
     // blocks of the launches that take two steps and of those that take one
     const unsigned nb2 = two_ok ? lwacm::adj_march2_num_blocks(c->p) : 0u;
-    const unsigned nb1 = multi ? lwacm::d2q9_multi_num_blocks(c->p)
-                               : (tile ? lwacm::adj_march_num_blocks(c->p)
-                                       : lwacm::generic_grid(c->p.n));
+    const bool column = use_adj_column(c);
+    const unsigned nb1 = multi    ? lwacm::d2q9_multi_num_blocks(c->p)
+                         : tile   ? lwacm::adj_march_num_blocks(c->p)
+                         : column ? lwacm::column_num_blocks(c->p, 0)
+                                  : lwacm::generic_grid(c->p.n);
     // Tile kernels whose chunks leave compute units idle (96^3: 36 workgroups):
     // chunks that fill the chip instead, the factors of the nodes' dL/da written
     // out, and the same dL/domega sums by launch_adj_dadomega after each launch.
@@ -1198,6 +1248,9 @@ int lwacm_adjoint_sweep(lwacm_ctx *c, const void *d_states, long long t0, int ns
         } else if (tile) {
             e = lwacm::launch_adj_march(c->p, c->storage, st + (size_t)(t - t0) * sb, mu_in, mu_out,
                                         c->d_bits, c->d_wallg, t == 0, r, c->stream, x);
+        } else if (column) {
+            e = lwacm::launch_adj_column(c->p, c->storage, st + (size_t)(t - t0) * sb, mu_in,
+                                         mu_out, t == 0, r, c->stream);
         } else {
             e = lwacm::launch_adj_generic(c->p, c->storage, st + (size_t)(t - t0) * sb, mu_in,
                                           mu_out, t == 0, r, nb1, c->stream);
@@ -1269,19 +1322,17 @@ int lwacm_step_static(int lattice, int nx, int ny, int nz, double omega, float *
     set_wall_terms(&c);
     // the partial sets of the kernels lwacm_step may launch must fit the scratch
     size_t nb = lwacm::generic_grid(p.n);
-    if (lwacm::march_supported(p)) {
-        const int ncu = device_cus();
+    const int ncu = device_cus();
+    if (lwacm::march_supported(p) && lwacm::march_aligned(p)) {
         p.march_nzc = lwacm::march_choose_depth(p, ncu);
-        const size_t sb = lwacm::march_aligned(p) ? lwacm::march_scratch_blocks(p, ncu) : 0;
+        const size_t sb = lwacm::march_scratch_blocks(p, ncu);
         if (sb > nb) nb = sb;
+        const size_t mb = lwacm::march_num_blocks(p);
+        if (mb > nb) nb = mb;
     }
-    const size_t mb = lwacm::march_num_blocks(p);
-    if (mb > kStaticMaxBlocks && !lwacm::march_aligned(p))
-        c.variant = LWACM_KERNEL_GENERIC;  // ragged sides: the gather kernel's blocks always fit
-    else if (mb > nb)
-        nb = mb;
     if (nb > kStaticMaxBlocks) return LWACM_ESCRATCH;
-    if (lattice == LWACM_D2Q9) p.multi_tile = lwacm::d2q9_multi_choose_tile(p, device_cus());
+    if (lattice == LWACM_D2Q9) p.multi_tile = lwacm::d2q9_multi_choose_tile(p, ncu);
+    else p.col_nzc = lwacm::column_choose_depth(p, ncu);
     double *base = nullptr;
     const int rc = static_scratch(&base);
     if (rc != LWACM_OK) return rc;

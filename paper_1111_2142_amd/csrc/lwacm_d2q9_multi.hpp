@@ -534,15 +534,13 @@ __global__ __launch_bounds__(multi_threads(MT, kAdjRows)) void k_adj_d2q9_multi(
                 auto fmask = [&](int dx, int dy, int) -> uint8_t {
                     return MASK ? (uint8_t)w[rr + 1 + dy][1 + dx].w : (uint8_t)0;
                 };
-                auto fmu = [&](int dx, int dy, int, float &mr, float (&mt)[3]) {
-                    const float4 q = w[rr + 1 + dy][1 + dx];
-                    mr = q.x;
-                    mt[0] = q.y;
-                    mt[1] = q.z;
-                    mt[2] = 0.0f;
+                auto fm = [&](int k) {
+                    const float4 q = w[rr + 1 + link_cy(k)][1 + link_cx(k)];
+                    const float mt[3] = {q.y, q.z, 0.0f};
+                    return q.x + vdot<9>(k, mt);
                 };
                 float lr, lu[3], da;
-                adj_node_update<9, MASK>(p, dry, uy, own.x, muJ, fmask, fmu, lr, lu, da);
+                adj_node_update<9, MASK>(p, dry, uy, own.x, muJ, fmask, fm, lr, lu, da);
                 if (tile) da_sum += (double)da;
                 if (fin) {
                     if (tile) {

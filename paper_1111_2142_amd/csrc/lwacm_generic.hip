@@ -235,11 +235,13 @@ __global__ __launch_bounds__(kGenericBlock) void k_adj_generic(ProblemArgs p, co
                            wrap_add(c.z, dz, p.nz));
         };
         auto fmask = [&](int dx, int dy, int dz) -> uint8_t { return p.mask[at(dx, dy, dz)]; };
-        auto fmu = [&](int dx, int dy, int dz, float &mr, float (&mt)[3]) {
-            load_mu<D>(mu_in, at(dx, dy, dz), mr, mt);
+        auto fm = [&](int k) {
+            float mr, mt[3];
+            load_mu<D>(mu_in, at(link_cx(k), link_cy(k), link_cz(k)), mr, mt);
+            return mr + vdot<Q>(k, mt);
         };
         float lr, lu[3], da;
-        adj_node_update<Q, MASK>(p, dry, uy, muR_y, muJ_y, fmask, fmu, lr, lu, da);
+        adj_node_update<Q, MASK>(p, dry, uy, muR_y, muJ_y, fmask, fm, lr, lu, da);
         if (final_t0) {
             // the gradient with respect to the initial state, field-major
             mu_out[idx] = lr;

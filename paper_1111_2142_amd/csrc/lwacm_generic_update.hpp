@@ -205,16 +205,17 @@ __device__ __forceinline__ void link_update(const ProblemArgs &p, const FSite &s
 // The reverse step at one fluid node y (the exact derivative of link_update,
 // in the gather form of its transpose): given y's state (dry, uy), its own
 // mu_t (muR_y, muJ_y) and two accessors of the nodes y + (dx, dy, dz) --
-// fmask returns the mask value, fmu(dx, dy, dz, mr, mt) their mu_t -- the
+// fmask returns the mask value; fm(k) the cotangent m_k = mu_R + v_k . mu_J of
+// the node y + v_k -- the
 // cotangents of y's state lambda_t = (lr, lu) and y's share da of dL/da.
 // Shared by the one-step reverse kernel (accessors read global memory) and
 // the multi-step D2Q9 reverse kernel (accessors read its LDS tile), so both
 // round every operation alike.
-template <int Q, bool MASK, class FMask, class FMu>
+template <int Q, bool MASK, class FMask, class FM>
 __device__ __forceinline__ void adj_node_update(const ProblemArgs &p, float dry,
                                                 const float (&uy)[3], float muR_y,
                                                 const float (&muJ_y)[3], const FMask &fmask,
-                                                const FMu &fmu, float &lr, float (&lu)[3],
+                                                const FM &fm, float &lr, float (&lu)[3],
                                                 float &da)
 {
     using L = Lattice<Q>;
@@ -235,9 +236,7 @@ __device__ __forceinline__ void adj_node_update(const ProblemArgs &p, float dry,
             const float wd[3] = {p.wall_da[wm][0], p.wall_da[wm][1], p.wall_da[wm][2]};
             da = fmaf(L::w36(k) * (1.0f / 36.0f) * vdot<Q>(k, wd), m, da);
         } else {
-            float mr, mt[3];
-            fmu(link_cx(k), link_cy(k), link_cz(k), mr, mt);
-            m = mr + vdot<Q>(k, mt);
+            m = fm(k);
         }
         const float cc = vdot<Q>(k, uy);
         const float wm_ = L::w36(k) * (1.0f / 36.0f) * m;

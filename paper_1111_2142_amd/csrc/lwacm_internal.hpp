@@ -45,6 +45,7 @@ struct ProblemArgs {
     // moving-wall sums
     const float4 *corr;
     int march_nzc;           // planes per workgroup of the forward tile kernels (0: unused)
+    int col_nzc;             // planes per workgroup of the column kernels (0: unused)
     int multi_tile;          // tile side of the multi-step D2Q9 kernels (0: unused)
     // the temperature step fused into the single-step tile kernel (thermal
     // problems, march_thermal_supported): T at the step's time and one step
@@ -105,6 +106,19 @@ hipError_t launch_density_si(const ProblemArgs &p, const float *src, float *dst,
 hipError_t launch_adj_generic(const ProblemArgs &p, int storage, const void *state,
                               const float *mu_in, float *mu_out, int final_t0,
                               const ReduceArgs &r, unsigned nblocks, hipStream_t stream);
+// D3Q19 steps as column-marching gathers (lwacm_column.hip): any grid, mask and
+// force, no separate omega_p, bitwise the generic kernels' results.  Masked
+// problems need the node classes of launch_classify and the list of fluid nodes
+// next to a wall; the reverse step takes problems without walls.
+bool column_supported(const ProblemArgs &p);
+int column_choose_depth(const ProblemArgs &p, int ncu);  // planes per chunk
+unsigned column_num_blocks(const ProblemArgs &p, unsigned nlist);
+hipError_t launch_fwd_column(const ProblemArgs &p, int storage, const void *src, void *dst,
+                             const uint8_t *cls, const unsigned *list, unsigned nlist,
+                             const ReduceArgs &r, hipStream_t stream);
+hipError_t launch_adj_column(const ProblemArgs &p, int storage, const void *state,
+                             const float *mu_in, float *mu_out, int final_t0, const ReduceArgs &r,
+                             hipStream_t stream);
 hipError_t launch_adj_seed(const ProblemArgs &p, int storage, const void *state,
                            const float *lambda, float *mu, hipStream_t stream);
 hipError_t launch_set_state(const ProblemArgs &p, int storage, const float *drho,
