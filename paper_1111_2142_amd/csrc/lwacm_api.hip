@@ -850,16 +850,12 @@ int lwacm_set_state(lwacm_ctx *c, const float *d_drho, const float *d_u)
 {
     if (!c || !d_drho || !d_u) return LWACM_EINVAL;
     set_scales(c);
-    hipError_t e = lwacm::launch_set_state(c->p, c->storage, d_drho, d_u, c->buf[c->cur], c->stream);
-    if (e != hipSuccess) return LWACM_EDEVICE;
-    // both buffers hold the state: a step leaves solid nodes as they are
-    e = hipMemcpyAsync(c->buf[c->cur ^ 1], c->buf[c->cur], state_bytes(c),
-                       hipMemcpyDeviceToDevice, c->stream);
-    if (e != hipSuccess) return LWACM_EDEVICE;
+    // both buffers hold the solid nodes: a step leaves them as they are.
     // rho0 = mean fluid density of the stored state (moving-wall term)
-    ReduceArgs r = reduce_args(c, c->d_scratch, nullptr);
-    e = lwacm::launch_moments(c->p, c->storage, c->buf[c->cur], nullptr, nullptr, r,
-                              lwacm::generic_grid(c->p.n), c->stream);
+    hipError_t e = lwacm::launch_set_state(c->p, c->storage, d_drho, d_u, c->buf[c->cur],
+                                           c->buf[c->cur ^ 1],
+                                           reduce_args(c, c->d_scratch, nullptr), c->stream);
+    if (e != hipSuccess) return LWACM_EDEVICE;
     double h[2] = {0.0, 0.0};
     if (e == hipSuccess) e = hipMemcpyAsync(h, c->d_scratch, sizeof(h), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -1013,11 +1009,12 @@ int lwacm_set_diag_history(lwacm_ctx *c, double *d_hist, int capacity)
 int lwacm_moments(lwacm_ctx *c, float *d_drho, float *d_u, double *h_mass, double *h_energy)
 {
     if (!c) return LWACM_EINVAL;
-    ReduceArgs r = reduce_args(c, c->d_scratch, nullptr);
+    const bool sums = h_mass || h_energy;
+    ReduceArgs r = reduce_args(c, sums ? c->d_scratch : nullptr, nullptr);
     hipError_t e = lwacm::launch_moments(c->p, c->storage, c->buf[c->cur], d_drho, d_u, r,
                                          lwacm::generic_grid(c->p.n), c->stream);
     if (e != hipSuccess) return LWACM_EDEVICE;
-    if (!h_mass && !h_energy) return LWACM_OK;
+    if (!sums) return LWACM_OK;
     double h[2];
     e = hipMemcpyAsync(h, c->d_scratch, sizeof(h), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -1039,7 +1036,7 @@ int lwacm_load_state(lwacm_ctx *c, const void *d_src, long long step)
     if (!c || !d_src || step < 0) return LWACM_EINVAL;
     const size_t bytes = lwacm_state_bytes(c->lattice, c->p.nx, c->p.ny, c->p.nz, c->storage);
     hipError_t e = hipMemcpyAsync(c->buf[c->cur], d_src, bytes, hipMemcpyDeviceToDevice, c->stream);
-    if (e == hipSuccess)
+    if (e == hipSuccess && c->p.mask)  // both buffers hold the solid nodes
         e = hipMemcpyAsync(c->buf[c->cur ^ 1], d_src, bytes, hipMemcpyDeviceToDevice, c->stream);
     if (e != hipSuccess) return LWACM_EDEVICE;
     c->steps = step;

@@ -280,22 +280,44 @@ __global__ __launch_bounds__(kGenericBlock) void k_adj_seed(ProblemArgs p, const
     }
 }
 
+// The state from field-major FP32 fields, with the (mass deviation, energy)
+// sums of the stored values over the fluid nodes (as k_moments sums them).
+// other: the second state buffer of a masked problem, which holds the solid
+// nodes' values too (a step may leave them unwritten).  One pass, bound by HBM:
+// at 256^3 FP32 the fields read and the state written once, where a copy of the
+// state and a pass for the sums took as long again each (270 us, now 105).
 template <int D, class T>
 __global__ __launch_bounds__(kGenericBlock) void k_set_state(ProblemArgs p, const float *__restrict__ drho,
                                                              const float *__restrict__ u,
-                                                             T *__restrict__ dst)
+                                                             T *__restrict__ dst,
+                                                             T *__restrict__ other, ReduceArgs r)
 {
     const long long n = p.n;
+    double acc[2] = {0.0, 0.0};
     for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < n;
          idx += (long long)gridDim.x * blockDim.x) {
         float v[D + 1];
         v[0] = drho[idx];
         for (int k = 0; k < D; ++k) v[k + 1] = u[k * n + idx];
         NodeState<T, D + 1>::store(dst, idx, v, p.st_scale);
+        if (p.mask && p.mask[idx] != 0) {
+            NodeState<T, D + 1>::store(other, idx, v, p.st_scale);
+            continue;
+        }
+        if constexpr (std::is_same<T, __half>::value)  // the values as stored
+#pragma unroll
+            for (int f = 0; f <= D; ++f)
+                v[f] = __half2float(__float2half_rn(v[f] * p.st_scale[f > 0])) * p.ld_scale[f > 0];
+        float e = 0.0f;
+        for (int k = 0; k < D; ++k) e = fmaf(v[k + 1], v[k + 1], e);
+        acc[0] += (double)v[0];
+        acc[1] += 0.5 * (double)e;
     }
+    store_block_partials<2>(acc, r.partials, blockIdx.x);
 }
 
-template <int D, class T>
+// SUMS: the (mass deviation, energy) sums too.
+template <int D, class T, bool SUMS>
 __global__ __launch_bounds__(kGenericBlock) void k_moments(ProblemArgs p, const T *__restrict__ src,
                                                            float *__restrict__ drho,
                                                            float *__restrict__ u, ReduceArgs r)
@@ -309,13 +331,13 @@ __global__ __launch_bounds__(kGenericBlock) void k_moments(ProblemArgs p, const 
         if (drho) drho[idx] = dr;
         if (u)
             for (int k = 0; k < D; ++k) u[k * n + idx] = uu[k];
-        if (p.mask && p.mask[idx] != 0) continue;
+        if (!SUMS || (p.mask && p.mask[idx] != 0)) continue;
         float e = 0.0f;
         for (int k = 0; k < D; ++k) e = fmaf(uu[k], uu[k], e);
         acc[0] += (double)dr;
         acc[1] += 0.5 * (double)e;
     }
-    store_block_partials<2>(acc, r.partials, blockIdx.x);
+    if (SUMS) store_block_partials<2>(acc, r.partials, blockIdx.x);
 }
 
 // Largest mask value and number of fluid nodes (integer atomics: exact).
@@ -535,39 +557,45 @@ hipError_t launch_adj_seed(const ProblemArgs &p, int storage, const void *state,
 }
 
 hipError_t launch_set_state(const ProblemArgs &p, int storage, const float *drho,
-                            const float *u, void *dst, hipStream_t s)
+                            const float *u, void *dst, void *other, const ReduceArgs &r,
+                            hipStream_t s)
 {
     const unsigned nb = grid_for(p.n);
+    __half *dh = (__half *)dst, *oh = (__half *)other;
+    float *df = (float *)dst, *of = (float *)other;
     if (p.D == 2) {
-        if (storage)
-            k_set_state<2, __half><<<nb, kGenericBlock, 0, s>>>(p, drho, u, (__half *)dst);
-        else
-            k_set_state<2, float><<<nb, kGenericBlock, 0, s>>>(p, drho, u, (float *)dst);
+        if (storage) k_set_state<2, __half><<<nb, kGenericBlock, 0, s>>>(p, drho, u, dh, oh, r);
+        else k_set_state<2, float><<<nb, kGenericBlock, 0, s>>>(p, drho, u, df, of, r);
     } else {
-        if (storage)
-            k_set_state<3, __half><<<nb, kGenericBlock, 0, s>>>(p, drho, u, (__half *)dst);
-        else
-            k_set_state<3, float><<<nb, kGenericBlock, 0, s>>>(p, drho, u, (float *)dst);
+        if (storage) k_set_state<3, __half><<<nb, kGenericBlock, 0, s>>>(p, drho, u, dh, oh, r);
+        else k_set_state<3, float><<<nb, kGenericBlock, 0, s>>>(p, drho, u, df, of, r);
     }
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_reduce(r, 2, nb, s);
+}
+
+template <int D, class T>
+static void moments_t(const ProblemArgs &p, const void *src, float *drho, float *u,
+                      const ReduceArgs &r, unsigned nb, hipStream_t s)
+{
+    if (r.out)
+        k_moments<D, T, true><<<nb, kGenericBlock, 0, s>>>(p, (const T *)src, drho, u, r);
+    else
+        k_moments<D, T, false><<<nb, kGenericBlock, 0, s>>>(p, (const T *)src, drho, u, r);
 }
 
 hipError_t launch_moments(const ProblemArgs &p, int storage, const void *src, float *drho,
                           float *u, const ReduceArgs &r, unsigned nb, hipStream_t s)
 {
     if (p.D == 2) {
-        if (storage)
-            k_moments<2, __half><<<nb, kGenericBlock, 0, s>>>(p, (const __half *)src, drho, u, r);
-        else
-            k_moments<2, float><<<nb, kGenericBlock, 0, s>>>(p, (const float *)src, drho, u, r);
+        if (storage) moments_t<2, __half>(p, src, drho, u, r, nb, s);
+        else moments_t<2, float>(p, src, drho, u, r, nb, s);
     } else {
-        if (storage)
-            k_moments<3, __half><<<nb, kGenericBlock, 0, s>>>(p, (const __half *)src, drho, u, r);
-        else
-            k_moments<3, float><<<nb, kGenericBlock, 0, s>>>(p, (const float *)src, drho, u, r);
+        if (storage) moments_t<3, __half>(p, src, drho, u, r, nb, s);
+        else moments_t<3, float>(p, src, drho, u, r, nb, s);
     }
     const hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : launch_reduce(r, 2, nb, s);
+    return e != hipSuccess || !r.out ? e : launch_reduce(r, 2, nb, s);
 }
 
 hipError_t launch_mask_scan(const ProblemArgs &p, unsigned *d_out2, hipStream_t s)

@@ -121,8 +121,12 @@ hipError_t launch_adj_column(const ProblemArgs &p, int storage, const void *stat
                              hipStream_t stream);
 hipError_t launch_adj_seed(const ProblemArgs &p, int storage, const void *state,
                            const float *lambda, float *mu, hipStream_t stream);
+// Writes the state to dst, the solid nodes' values to other as well (masked
+// problems), and the (mass deviation, energy) sums to r.out.
 hipError_t launch_set_state(const ProblemArgs &p, int storage, const float *drho,
-                            const float *u, void *dst, hipStream_t stream);
+                            const float *u, void *dst, void *other, const ReduceArgs &r,
+                            hipStream_t stream);
+// Fields and, where r.out is set, the (mass deviation, energy) sums.
 hipError_t launch_moments(const ProblemArgs &p, int storage, const void *src, float *drho,
                           float *u, const ReduceArgs &r, unsigned nblocks, hipStream_t stream);
 hipError_t launch_mask_scan(const ProblemArgs &p, unsigned *d_out2, hipStream_t stream);
