@@ -85,11 +85,12 @@ struct Lattice<19> {
 
 // x / 36 with a double-word constant: the result is the nearest float in
 // all but rare ties, and, unlike x * fl(1/36), carries no systematic bias.
-__device__ __forceinline__ float div36(float x)
+// scale: a power of two to multiply the result by, exactly.
+__device__ __forceinline__ float div36(float x, float scale = 1.0f)
 {
     constexpr float c_hi = 1.0f / 36.0f;
     constexpr float c_lo = (float)(1.0 / 36.0 - (double)(1.0f / 36.0f));
-    return fmaf(x, c_hi, x * c_lo);
+    return fmaf(x, c_hi * scale, x * (c_lo * scale));
 }
 
 // ------------------------------------------------------ the link term
@@ -129,9 +130,15 @@ struct U32x4 {
     uint32_t x, y, z, w;
 };
 
-__device__ __forceinline__ U32x4 sr_words(uint32_t idx, uint32_t step_word)
+// The LCG step of the node index, from which a kernel that walks nodes at a
+// fixed distance d goes on by adding d * kSrMul (a 32-bit multiply takes four
+// times as long as an addition).
+constexpr uint32_t kSrMul = 1664525u;
+
+__device__ __forceinline__ uint32_t sr_first(uint32_t idx) { return idx * kSrMul + 1013904223u; }
+
+__device__ __forceinline__ U32x4 sr_words_from(uint32_t a, uint32_t step_word)
 {
-    uint32_t a = idx * 1664525u + 1013904223u;
     uint32_t b = step_word * 1664525u + 1013904223u;
 #pragma unroll
     for (int round = 0; round < 2; ++round) {
@@ -141,6 +148,11 @@ __device__ __forceinline__ U32x4 sr_words(uint32_t idx, uint32_t step_word)
         b ^= b >> 16;
     }
     return U32x4{a, b, a << 13, b << 13};
+}
+
+__device__ __forceinline__ U32x4 sr_words(uint32_t idx, uint32_t step_word)
+{
+    return sr_words_from(sr_first(idx), step_word);
 }
 
 // FP32 -> FP16 with stochastic rounding, two values into one packed word

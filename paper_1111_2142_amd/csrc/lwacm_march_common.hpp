@@ -314,18 +314,28 @@ __device__ __forceinline__ void push_bounce_back(unsigned bits, float Lpx, float
     bb[3] = sz;
 }
 
+// Velocities in units of us, a power of two (FP16 storage keeps them in units
+// of 2^-k_u): with A, k15 and k45 scaled to match, every product and sum below is
+// that of the plain velocities, exactly, except the post-combine term, which is
+// in units of us; finish() then returns the new velocity in units of us, ready
+// to be stored, and no value is multiplied by its storage scale.
+struct VelUnits {
+    float k15 = -1.5f, k45 = 4.5f;  // -3/2 us^2, 9/2 us^2
+};
+
 // bounce: sum the halfway bounced-back terms here; false where a per-step
 // wall correction brings the whole wall term instead (interpolated walls,
 // link velocities).
 template <bool MASK>
 __device__ __forceinline__ void push_column(float dr, float ux, float uy, float uz, int cls,
                                             unsigned bits, float A, float a, Acc &A1, Acc &A0,
-                                            Acc &Am, bool bounce = true)
+                                            Acc &Am, bool bounce = true,
+                                            const VelUnits &vu = VelUnits{})
 {
     const float rho = 1.0f + dr;
     const float usq = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
-    float E0 = fmaf(rho, -1.5f * usq, dr);
-    float r45 = 4.5f * rho;
+    float E0 = fmaf(rho, vu.k15 * usq, dr);
+    float r45 = vu.k45 * rho;
     float rA = A * rho;
     if (MASK && cls >= 2) {  // solid: push nothing
         E0 = 0.0f;
@@ -453,7 +463,7 @@ __device__ __forceinline__ Gathered gather(const Xchg<NS> &X, int slot)
 template <bool MASK, bool SPLIT = false>
 __device__ __forceinline__ NodeOut finish(const Gathered &g, const Acc &Am, const ProblemArgs &p,
                                           const float4 *wallg, long long widx, float qsum = 0.0f,
-                                          const f32x4 *cw = nullptr)
+                                          const f32x4 *cw = nullptr, float per_us = 1.0f)
 {
     float D36 = Am.d + ((g.pE + g.pW) + (g.pN + g.pS)) + ((g.dNE + g.dNW) + (g.dSE + g.dSW));
     float Jx = (g.pE - g.pW) + ((g.dNE - g.dNW) + (g.dSE - g.dSW));
@@ -496,9 +506,9 @@ __device__ __forceinline__ NodeOut finish(const Gathered &g, const Acc &Am, cons
     }
     // separate omega_p: the density takes its link terms with Ap in place of A
     if (SPLIT) D36 += qsum;
-    Jx = div36(Jx) + Am.post[0];
-    Jy = div36(Jy) + Am.post[1];
-    Jz = div36(Jz) + Am.post[2];
+    Jx = div36(Jx, per_us) + Am.post[0];  // per_us = 1 / us (VelUnits)
+    Jy = div36(Jy, per_us) + Am.post[1];
+    Jz = div36(Jz, per_us) + Am.post[2];
     NodeOut o;
     o.D = div36(D36);
     const float q = normalisation_factor(o.D);
@@ -512,9 +522,9 @@ template <bool MASK, int NS, int SXP, bool SPLIT = false>
 __device__ __forceinline__ NodeOut finalize(const Xchg<NS> &X, int slot, const Acc &Am,
                                             const ProblemArgs &p, const float4 *wallg,
                                             long long widx, float qsum = 0.0f,
-                                            const f32x4 *cw = nullptr)
+                                            const f32x4 *cw = nullptr, float per_us = 1.0f)
 {
-    return finish<MASK, SPLIT>(gather<NS, SXP>(X, slot), Am, p, wallg, widx, qsum, cw);
+    return finish<MASK, SPLIT>(gather<NS, SXP>(X, slot), Am, p, wallg, widx, qsum, cw, per_us);
 }
 
 // ---- separate omega_p for the density (Section "finite-difference
@@ -761,12 +771,13 @@ __device__ __forceinline__ float gather_split(const XchgQ<NS> &X, int slot)
 template <bool MASK>
 __device__ __forceinline__ void push_halo(float dr, float ux, float uy, float uz, int cls,
                                           float A, bool isY, float sgn, float &p1, float &z1,
-                                          float &p0, float &d1, float &d2, float &pm, float &zm)
+                                          float &p0, float &d1, float &d2, float &pm, float &zm,
+                                          const VelUnits &vu = VelUnits{})
 {
     const float rho = 1.0f + dr;
     const float usq = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
-    float E0 = fmaf(rho, -1.5f * usq, dr);
-    float r45 = 4.5f * rho;
+    float E0 = fmaf(rho, vu.k15 * usq, dr);
+    float r45 = vu.k45 * rho;
     float rA = A * rho;
     if (MASK && cls >= 2) {
         E0 = 0.0f;
