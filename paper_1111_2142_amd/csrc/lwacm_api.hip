@@ -41,6 +41,7 @@ struct lwacm_ctx {
     double *d_scratch;  // [2] for lwacm_moments
     unsigned *d_scan;   // [2] mask scan
     uint8_t *d_cls;     // node classes for the march kernel (masked problems)
+    int4 *h_plan;       // the forward tile kernels' chunks (p.march_plan), as copied to d_cls
     unsigned *d_bits;   // solid-upstream link bits for the march kernel
     float4 *d_wallg;    // moving-wall geometry sums for the march kernel (moving walls only)
     double *d_hist;
@@ -262,12 +263,43 @@ void free_scratch(lwacm_ctx *c)
     c->p.corr = nullptr;
     c->wlist_built = false;
     c->d_force = nullptr;
+    c->p.march_plan = nullptr;
+    free(c->h_plan);
+    c->h_plan = nullptr;
     c->d_cls = nullptr;
     c->d_bits = nullptr;
     c->d_wallg = nullptr;
     c->d_partials = nullptr;
     c->d_diag = c->d_scratch = nullptr;
     c->d_scan = nullptr;
+}
+
+// The forward tile kernels' chunks (lwacm::march_plan), at d (room for ncu
+// entries): the tiles' wall counts come back (one synchronisation), the list
+// goes out from memory the context keeps.
+hipError_t make_march_plan(lwacm_ctx *c, void *d)
+{
+    const size_t words = 2 * lwacm::march_tiles(c->p);  // 8 bytes a tile: fits
+    unsigned *counts = static_cast<unsigned *>(malloc(words * sizeof(unsigned)));
+    c->h_plan = static_cast<int4 *>(malloc((size_t)c->ncu * sizeof(int4)));
+    if (!counts || !c->h_plan) {  // chunks of one depth then
+        free(counts);
+        return hipSuccess;
+    }
+    hipError_t e = hipMemsetAsync(d, 0, words * sizeof(unsigned), c->stream);
+    if (e == hipSuccess)
+        e = lwacm::launch_tile_walls(c->p, c->d_bits, static_cast<unsigned *>(d), c->stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(counts, d, words * sizeof(unsigned), hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    const int nb = e == hipSuccess ? lwacm::march_plan(c->p, c->ncu, counts, c->h_plan) : 0;
+    free(counts);
+    if (nb == 0 || (size_t)nb > c->n_partial_blocks) return e;
+    e = hipMemcpyAsync(d, c->h_plan, (size_t)nb * sizeof(int4), hipMemcpyHostToDevice, c->stream);
+    c->p.march_plan = static_cast<const int4 *>(d);
+    c->p.march_plan_blocks = nb;
+    c->p.march_plan_depth = c->h_plan[0].w;
+    return e;
 }
 
 // The list of fluid nodes next to a wall (lwacm_walls.hip), built once:
@@ -552,7 +584,10 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
             bool moving = false;
             for (int m = 1; m < lwacm::kMaxWallIds; ++m)
                 for (int k = 0; k < 3; ++k) moving = moving || p.wall_u[m][k] != 0.0f;
-            e = hipMalloc(&c->d_cls, (size_t)p.n);
+            // behind the classes: the tiles' wall counts, then the list of chunks
+            const bool planned = lwacm::march_plan_fits(unforced, c->ncu);
+            const size_t at = ((size_t)p.n + 15) / 16 * 16;
+            e = hipMalloc(&c->d_cls, planned ? at + (size_t)c->ncu * sizeof(int4) : (size_t)p.n);
             if (e == hipSuccess) e = hipMalloc(&c->d_bits, (size_t)p.n * sizeof(unsigned));
             if (e == hipSuccess && moving)
                 e = hipMalloc(&c->d_wallg, (size_t)p.n * sizeof(float4));
@@ -562,6 +597,7 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
                 return LWACM_ENOMEM;
             }
             e = lwacm::launch_classify(p, c->d_cls, c->d_bits, c->d_wallg, stream);
+            if (e == hipSuccess && planned) e = make_march_plan(c, c->d_cls + at);
         }
     }
     if (e != hipSuccess) {
@@ -627,10 +663,13 @@ int lwacm_set_march_chunk(lwacm_ctx *c, int planes)
     if (!c || (planes != 32 && planes != 64 && planes != 128)) return LWACM_EINVAL;
     if (!lwacm::march_supported(c->p) || !lwacm::march_aligned(c->p)) return LWACM_EUNSUPPORTED;
     const int keep = c->p.march_nzc;
+    const int4 *plan = c->p.march_plan;
+    c->p.march_plan = nullptr;
     c->p.march_nzc = planes;
     if (lwacm::march_num_blocks(c->p) > c->n_partial_blocks ||
         lwacm::march2_num_blocks(c->p) > c->n_partial_blocks) {  // reduction scratch too small
         c->p.march_nzc = keep;
+        c->p.march_plan = plan;
         return LWACM_EUNSUPPORTED;
     }
     return LWACM_OK;

@@ -45,6 +45,11 @@ struct ProblemArgs {
     // moving-wall sums
     const float4 *corr;
     int march_nzc;           // planes per workgroup of the forward tile kernels (0: unused)
+    // with walls: the workgroups of the forward tile kernels one by one (null:
+    // march_nzc planes each): {xs, ys, zs, depth}, the depths of one residue
+    // modulo 3 (march_plan)
+    const int4 *march_plan;
+    int march_plan_blocks, march_plan_depth;  // their number; the first one's depth
     int col_nzc;             // planes per workgroup of the column kernels (0: unused)
     int multi_tile;          // tile side of the multi-step D2Q9 kernels (0: unused)
     // the temperature step fused into the single-step tile kernel (thermal
@@ -140,7 +145,18 @@ int march_choose_depth(const ProblemArgs &p, int ncu);  // chunk depth for a dev
 // Blocks a context's reduction scratch holds at least, whatever depth is
 // chosen: those of the best of the depths a caller may set (32, 64, 128).
 size_t march_scratch_blocks(const ProblemArgs &p, int ncu);
-unsigned march_num_blocks(const ProblemArgs &p);       // uses p.march_nzc
+unsigned march_num_blocks(const ProblemArgs &p);       // uses p.march_nzc or p.march_plan
+// Chunks of unequal depth for a masked problem, where the tiles next to walls
+// cost more than the others: march_plan_fits tells whether they could pay (no
+// more tiles than CUs), launch_tile_walls counts each tile's work at walls
+// (two words a tile, cleared before), and march_plan makes the list of
+// workgroups from the counts and returns their number, at most ncu (0: chunks
+// of march_nzc planes are as good, or no memory for it).
+bool march_plan_fits(const ProblemArgs &p, int ncu);
+size_t march_tiles(const ProblemArgs &p);
+hipError_t launch_tile_walls(const ProblemArgs &p, const unsigned *bits, unsigned *counts,
+                             hipStream_t s);
+int march_plan(const ProblemArgs &p, int ncu, const unsigned *counts, int4 *plan);
 // Moving walls also need a per-node float4 of geometry sums (wallg, n
 // entries; may be null when every wall is at rest).
 constexpr unsigned kMovingWallFlag = 1u << 31;  // in bits: node sees a moving wall

@@ -32,6 +32,10 @@
 // Link terms are kept unweighted and summed with the exact integer weights
 // 12, 2, 1 (= 36 w_i for rest, axis and diagonal links of D3Q19); the sums
 // are divided by 36 once at the end (div36: no systematic rounding bias).
+#include <stdlib.h>
+
+#include <algorithm>
+
 #include "lwacm_march_common.hpp"
 
 namespace lwacm {
@@ -279,7 +283,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march(ProblemArgs p, const T *
 // the new T (p.T_out): 4 + 4 bytes more per node instead of a pass of its own
 // (with walls 8 more: the node's fixed-temperature wall links and their sum).
 template <class T, int TAIL, bool SR, bool MASK, bool SPLIT, int FRC, bool CORR, bool THERM>
-__global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, int nzc,
+__global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, int depth,
                                                                const T *__restrict__ src,
                                                                T *__restrict__ dst,
                                                                const unsigned *__restrict__ bb_bits,
@@ -304,8 +308,10 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
     const long long n = p.n;
     const long long plane = (long long)nx * ny;
 
-    const TileIdx ti = tile_of_block(nx, ny, TX, TY);
-    const int zs = ti.zc * nzc;
+    const TileChunk tc = chunk_of_block<MASK>(p, depth, TX, TY);
+    const TileIdx ti = tc.t;
+    const int nzc = tc.nzc;
+    const int zs = tc.zs;
     const int z0 = min(zs, nz - nzc);
 
     const int role = tid < NINT ? INTERIOR : (tid < NINT + kWave ? HALO_Y : HALO_X);
@@ -562,6 +568,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
 int rolled_nzc(const ProblemArgs &p)
 {
     if (p.nz < 8) return 0;
+    if (p.march_plan) return p.march_plan_depth;
     return p.march_nzc < p.nz ? p.march_nzc : p.nz;
 }
 
@@ -618,6 +625,26 @@ __global__ __launch_bounds__(256) void k_classify(ProblemArgs p, uint8_t *cls, u
         cls[idx] = bb ? 1 : 0;
         bits[idx] = bb;
     }
+}
+
+// Work at walls of each tile, from the bit sets: counts[2 t] its rows of 64
+// nodes (one wave's) with a bounce-back link, counts[2 t + 1] its planes with one.
+__global__ __launch_bounds__(NINT) void k_tile_walls(ProblemArgs p, const unsigned *bits,
+                                                     unsigned *counts)
+{
+    const int tiles_x = (p.nx + TX - 1) / TX;
+    const int x0 = min((int)(blockIdx.x % tiles_x) * TX, p.nx - TX);
+    const int y0 = min((int)(blockIdx.x / tiles_x) * TY, p.ny - TY);
+    const long long col = (long long)(y0 + (int)threadIdx.x / TX) * p.nx + x0 + (int)threadIdx.x % TX;
+    unsigned rows = 0, planes = 0;
+    for (int z = blockIdx.y; z < p.nz; z += gridDim.y) {
+        const unsigned b = bits[(long long)z * p.nx * p.ny + col];
+        const bool wall = b != 0u && !(b & 1u);
+        rows += __any(wall) ? 1u : 0u;
+        planes += __syncthreads_or(wall) ? 1u : 0u;
+    }
+    if (threadIdx.x % kWave == 0 && rows) atomicAdd(&counts[2 * blockIdx.x], rows);
+    if (threadIdx.x == 0 && planes) atomicAdd(&counts[2 * blockIdx.x + 1], planes);
 }
 
 // c: planes per workgroup; its loop of c + 2 iterations has a tail of 3 + (c + 2) % 3
@@ -756,6 +783,117 @@ int march_choose_depth(const ProblemArgs &p, int ncu)
     return best;
 }
 
+size_t march_tiles(const ProblemArgs &p)
+{
+    return (size_t)((p.nx + TX - 1) / TX) * (size_t)((p.ny + TY - 1) / TY);
+}
+
+bool march_plan_fits(const ProblemArgs &p, int ncu)
+{
+    return p.mask && march_supported(p) && p.march_nzc > 0 && p.nz >= 16 &&
+           (long long)march_tiles(p) <= ncu;
+}
+
+// One round of workgroups ends with its slowest, and the tiles next to walls
+// are the slow ones: a plane of a tile with no wall, with walls across y and
+// across x takes 46.8, 50.8 and 57.7 (two steps per launch) or 57.7, 59.4 and
+// 65.0 (one step) in units of one workgroup's time, which
+//     1 + (planes with a wall) / 16 + (rows of 64 nodes with a wall) / 6,
+// both as fractions, follows.  Starting from the deepest chunks, the tile whose
+// chunks cost most is cut into one more until every CU has a workgroup.  All
+// depths have one residue modulo 3 (the kernels' loop tail is a template
+// parameter); the best of the three is taken, if it beats chunks of one depth.
+// The lid-driven cavity at 192^3: 256 chunks of 49 and 64 planes against 216 of
+// 64, 111 -> 90 us for two steps; 160 x 96 x 100 with a temperature 25.0 -> 24.6
+// us a step; at 128^3 and 256^3 (all CUs busy, depths a third apart) one depth.
+int march_plan(const ProblemArgs &p, int ncu, const unsigned *counts, int4 *plan)
+{
+    constexpr int extra = 10;  // planes' time a chunk costs besides its own (march_choose_depth)
+    const int tiles = (int)march_tiles(p);
+    const int tiles_x = (p.nx + TX - 1) / TX;
+    // per tile: its weight and depth, and the best depth so far
+    struct Tile {
+        double w;
+        int depth, best;
+    };
+    Tile *tile = static_cast<Tile *>(malloc((size_t)tiles * sizeof(Tile)));
+    if (!tile) return 0;
+    double wmax = 0.0, wsum = 0.0;
+    for (int t = 0; t < tiles; ++t) {
+        const double w = 1.0 + (double)counts[2 * t + 1] / p.nz / 16.0 +
+                         (double)counts[2 * t] / p.nz / (NINT / kWave) / 6.0;
+        tile[t].w = w;
+        tile[t].best = 0;
+        wmax = w > wmax ? w : wmax;
+        wsum += w;
+    }
+    const int c0 = rolled_nzc(p);
+    const long long nb0 = march_blocks_for(p, c0);
+    double best = nb0 <= ncu ? wmax * (c0 + extra)
+                             : (double)((nb0 + ncu - 1) / ncu) * (c0 + extra) * wsum / tiles;
+    best *= 0.98;  // not for a gain too small to tell
+    auto chunks = [&](int c) { return (p.nz + c - 1) / c; };
+    for (int residue = 0; residue < 3; ++residue) {
+        auto valid = [&](int c) { return c >= 8 && c % 3 == residue; };
+        int deepest = p.nz;
+        while (!valid(deepest)) --deepest;  // nz >= 16
+        for (int t = 0; t < tiles; ++t) tile[t].depth = deepest;
+        long long nb = (long long)tiles * chunks(deepest);
+        if (nb > ncu) continue;
+        auto cost = [&](int t) { return tile[t].w * (tile[t].depth + extra); };
+        int worst;
+        for (;;) {
+            worst = 0;
+            for (int t = 1; t < tiles; ++t)
+                if (cost(t) > cost(worst)) worst = t;
+            // one more chunk (or the next number that a shallower depth makes),
+            // at the smallest depth that makes that number
+            const int m = chunks(tile[worst].depth);
+            int c = tile[worst].depth - 3;
+            while (valid(c) && chunks(c) == m) c -= 3;
+            if (!valid(c) || nb + chunks(c) - m > ncu) break;
+            while (valid(c - 3) && chunks(c - 3) == chunks(c)) c -= 3;
+            nb += chunks(c) - m;
+            tile[worst].depth = c;
+        }
+        if (cost(worst) >= best) continue;
+        best = cost(worst);
+        for (int t = 0; t < tiles; ++t) tile[t].best = tile[t].depth;
+    }
+    int nb = 0;
+    if (tile[0].best)
+        for (int t = 0; t < tiles; ++t) nb += chunks(tile[t].best);
+    // workgroup b runs on XCD b modulo 8: neighbours in z, then in the plane,
+    // go to one XCD, whose L2 then holds the halos they share
+    int4 *order = nb ? static_cast<int4 *>(malloc((size_t)nb * sizeof(int4))) : nullptr;
+    if (!order) nb = 0;
+    if (nb) {
+        int k = 0;
+        for (int t = 0; t < tiles; ++t)
+            for (int j = 0; j < chunks(tile[t].best); ++j)
+                order[k++] = make_int4(t % tiles_x * TX, t / tiles_x * TY, j * tile[t].best,
+                                       tile[t].best);
+        auto middle = [](const int4 &c) { return 2 * c.z + c.w; };
+        std::sort(order, order + nb, [&](const int4 &a, const int4 &b) {
+            if (middle(a) != middle(b)) return middle(a) < middle(b);
+            return a.y != b.y ? a.y < b.y : a.x < b.x;
+        });
+        k = 0;
+        for (int xcd = 0; xcd < 8; ++xcd)
+            for (int b = xcd; b < nb; b += 8) plan[b] = order[k++];
+    }
+    free(order);
+    free(tile);
+    return nb;
+}
+
+hipError_t launch_tile_walls(const ProblemArgs &p, const unsigned *bits, unsigned *counts,
+                             hipStream_t s)
+{
+    k_tile_walls<<<dim3((unsigned)march_tiles(p), 16), NINT, 0, s>>>(p, bits, counts);
+    return hipGetLastError();
+}
+
 size_t march_scratch_blocks(const ProblemArgs &p, int ncu)
 {
     long long best = 0, best_cost = -1;
@@ -773,6 +911,7 @@ size_t march_scratch_blocks(const ProblemArgs &p, int ncu)
 unsigned march_num_blocks(const ProblemArgs &p)
 {
     if (!march_supported(p) || p.march_nzc <= 0) return 0;
+    if (p.march_plan) return (unsigned)p.march_plan_blocks;
     const int c = rolled_nzc(p);  // the kernel dispatch() launches
     return (unsigned)march_blocks_for(p, c > 0 ? c : 32);
 }

@@ -87,7 +87,7 @@ __device__ __forceinline__ void finish_previous_sums2(const ReduceArgs &r)
 }
 
 template <int TAIL, bool MASK>
-__global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int nzc,
+__global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int depth,
                                                          const float *__restrict__ src,
                                                          float *__restrict__ dst,
                                                          const unsigned *__restrict__ bb_bits,
@@ -107,13 +107,15 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int nzc,
     const long long n = p.n;
     const long long plane = (long long)nx * ny;
 
-    const TileIdx ti = tile_of_block(nx, ny, TX, TY);
+    const TileChunk tc = chunk_of_block<MASK>(p, depth, TX, TY);
+    const TileIdx ti = tc.t;
+    const int nzc = tc.nzc;
     // Every chunk is nzc planes deep (nz >= nzc): a ragged last chunk is moved
     // down to end at nz.  Planes it shares with the chunk below are written
     // twice with bitwise the same values and counted in the sums only once,
     // from zs on, so each block sums the planes the single-step kernel's
     // block of the same index sums.
-    const int zs = ti.zc * nzc;
+    const int zs = tc.zs;
     const int z0 = min(zs, nz - nzc);
     const int z1 = z0 + nzc;
 
@@ -291,7 +293,11 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int nzc,
 }
 
 // Chunk depth: the single-step kernel's (nz >= 8).
-int march2_nzc(const ProblemArgs &p) { return p.march_nzc < p.nz ? p.march_nzc : p.nz; }
+int march2_nzc(const ProblemArgs &p)
+{
+    if (p.march_plan) return p.march_plan_depth;
+    return p.march_nzc < p.nz ? p.march_nzc : p.nz;
+}
 
 }  // namespace
 

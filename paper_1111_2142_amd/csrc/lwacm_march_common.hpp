@@ -927,6 +927,33 @@ __device__ __forceinline__ TileIdx tile_of_block(int nx, int ny, int TXv, int TY
     return t;
 }
 
+// The tile and chunk of this workgroup: chunks of nzc planes, or with walls the
+// problem's list (march_plan).  zs is the first plane it counts in the sums.
+struct TileChunk {
+    TileIdx t;
+    int zs, nzc;
+};
+
+template <bool MASK>
+__device__ __forceinline__ TileChunk chunk_of_block(const ProblemArgs &p, int nzc, int TXv, int TYv)
+{
+    TileChunk c;
+    if (MASK && p.march_plan) {
+        const int4 e = p.march_plan[blockIdx.x];
+        c.t.xs = __builtin_amdgcn_readfirstlane(e.x);
+        c.t.ys = __builtin_amdgcn_readfirstlane(e.y);
+        c.t.x0 = min(c.t.xs, p.nx - TXv);
+        c.t.y0 = min(c.t.ys, p.ny - TYv);
+        c.zs = __builtin_amdgcn_readfirstlane(e.z);
+        c.nzc = __builtin_amdgcn_readfirstlane(e.w);
+        return c;
+    }
+    c.t = tile_of_block(p.nx, p.ny, TXv, TYv);
+    c.nzc = nzc;
+    c.zs = c.t.zc * nzc;
+    return c;
+}
+
 __device__ __forceinline__ int wrap_index(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
 }  // namespace
