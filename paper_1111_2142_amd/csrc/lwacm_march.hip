@@ -583,28 +583,33 @@ int rolled_nzc(const ProblemArgs &p)
 __global__ __launch_bounds__(256) void k_classify(ProblemArgs p, uint8_t *cls, unsigned *bits,
                                                   float4 *wallg)
 {
-    for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < p.n;
-         idx += (long long)gridDim.x * blockDim.x) {
-        if (p.mask[idx] != 0) {
+    for (unsigned idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (unsigned)p.n;  // n < 2^28
+         idx += gridDim.x * blockDim.x) {
+        const unsigned t = idx / (unsigned)p.nx;
+        const int x = (int)(idx - t * p.nx);
+        const int z = (int)(t / (unsigned)p.ny);
+        const int y = (int)(t - (unsigned)z * p.ny);
+        uint8_t ms[19];  // the 19 loads in flight together (192^3: 87 us one by one, now 48)
+#pragma unroll
+        for (int i = 0; i < 19; ++i) {
+            int ux = x - link_cx(i), uy = y - link_cy(i), uz = z - link_cz(i);
+            ux = ux < 0 ? ux + p.nx : (ux >= p.nx ? ux - p.nx : ux);
+            uy = uy < 0 ? uy + p.ny : (uy >= p.ny ? uy - p.ny : uy);
+            uz = uz < 0 ? uz + p.nz : (uz >= p.nz ? uz - p.nz : uz);
+            ms[i] = p.mask[((unsigned)uz * p.ny + uy) * p.nx + ux];
+        }
+        if (ms[0] != 0) {
             cls[idx] = 2;
             bits[idx] = 1u;  // bit 0 (the rest link, never a bounce-back link): solid
             continue;
         }
-        const long long t = idx / p.nx;
-        const int x = (int)(idx - t * p.nx);
-        const int z = (int)(t / p.ny);
-        const int y = (int)(t - (long long)z * p.ny);
         unsigned bb = 0u;
         float g[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         bool moving = false;
 #pragma unroll
         for (int i = 1; i < 19; ++i) {
             const int cx = link_cx(i), cy = link_cy(i), cz = link_cz(i);
-            int ux = x - cx, uy = y - cy, uz = z - cz;
-            ux = ux < 0 ? ux + p.nx : (ux >= p.nx ? ux - p.nx : ux);
-            uy = uy < 0 ? uy + p.ny : (uy >= p.ny ? uy - p.ny : uy);
-            uz = uz < 0 ? uz + p.nz : (uz >= p.nz ? uz - p.nz : uz);
-            const int m = p.mask[((long long)uz * p.ny + uy) * p.nx + ux];
+            const int m = ms[i];
             if (m != 0) {
                 bb |= 1u << i;
                 const float vu = cx * p.wall_u[m][0] + cy * p.wall_u[m][1] + cz * p.wall_u[m][2];

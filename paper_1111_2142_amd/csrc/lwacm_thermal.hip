@@ -137,26 +137,36 @@ __global__ __launch_bounds__(kThermalBX *kThermalBY) void k_thermal_step(Thermal
     t.T_out[idx] = fmaf(t.kap, Tx, div36(acc));
 }
 
-__global__ __launch_bounds__(256) void k_thermal_wall_table(ThermalArgs t, uint2 *out)
+// Nodes away from walls (no solid upstream link in their bit set) only write
+// zeros: 160 x 96 x 100 24.7 us with a chain of 18 mask loads in every node, 13.5 us now.
+__global__ __launch_bounds__(256) void k_thermal_wall_table(ThermalArgs t, const unsigned *bits,
+                                                            uint2 *out)
 {
-    const long long n = (long long)t.nx * t.ny * t.nz;
-    for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < n;
-         idx += (long long)gridDim.x * blockDim.x) {
+    const unsigned n = (unsigned)t.nx * t.ny * t.nz;  // < 2^28, as the bit sets' problems
+    for (unsigned idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n;
+         idx += gridDim.x * blockDim.x) {
         unsigned fb = 0u;
         float tw = 0.0f;
-        if (t.mask[idx] == 0) {
-            const long long r = idx / t.nx;
+        const unsigned b = bits[idx];
+        if (b != 0u && !(b & 1u)) {  // fluid, next to a solid node
+            const unsigned r = idx / (unsigned)t.nx;
             const int x = (int)(idx - r * t.nx);
-            const int z = (int)(r / t.ny);
-            const int y = (int)(r - (long long)z * t.ny);
+            const int z = (int)(r / (unsigned)t.ny);
+            const int y = (int)(r - (unsigned)z * t.ny);
+            uint8_t ms[19];  // all loads in flight together
 #pragma unroll
             for (int i = 1; i < 19; ++i) {
                 const int xs = wrap_step(x, link_cx(i), t.nx);
                 const int ys = wrap_step(y, link_cy(i), t.ny);
                 const int zs = wrap_step(z, link_cz(i), t.nz);
-                const uint8_t m = t.mask[((long long)zs * t.ny + ys) * t.nx + xs];
+                ms[i] = t.mask[((unsigned)zs * t.ny + ys) * t.nx + xs];
+            }
+#pragma unroll
+            for (int i = 1; i < 19; ++i) {
+                const uint8_t m = ms[i];
+                if (m == 0) continue;
                 const float Tw = m < kMaxThermalWallIds ? t.wall_T[m] : __builtin_nanf("");
-                if (m != 0 && Tw == Tw) {
+                if (Tw == Tw) {
                     fb |= 1u << i;
                     tw = fmaf(Lattice<19>::w36(i), Tw, tw);
                 }
@@ -478,12 +488,13 @@ hipError_t launch_adj_q(const ThermalAdjArgs &a, hipStream_t stream)
 
 }  // namespace
 
-hipError_t launch_thermal_wall_table(const ThermalArgs &t, uint2 *out, hipStream_t stream)
+hipError_t launch_thermal_wall_table(const ThermalArgs &t, const unsigned *bits, uint2 *out,
+                                     hipStream_t stream)
 {
-    if (t.Q != 19 || !t.mask || !out) return hipErrorInvalidValue;
+    if (t.Q != 19 || !t.mask || !bits || !out) return hipErrorInvalidValue;
     long long nb = ((long long)t.nx * t.ny * t.nz + 255) / 256;
     if (nb > 4096) nb = 4096;
-    k_thermal_wall_table<<<(unsigned)nb, 256, 0, stream>>>(t, out);
+    k_thermal_wall_table<<<(unsigned)nb, 256, 0, stream>>>(t, bits, out);
     return hipGetLastError();
 }
 

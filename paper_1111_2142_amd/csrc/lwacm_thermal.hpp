@@ -31,7 +31,9 @@ hipError_t launch_thermal_step(const ThermalArgs &t, hipStream_t stream);
 // node, the links i whose upstream node x - v_i is a wall held at a fixed
 // temperature (bit i, the flow kernels' link order) and the FP32 bits of the
 // sum of 36 w_i T_w over them; zero for solid nodes and away from such walls.
-hipError_t launch_thermal_wall_table(const ThermalArgs &t, uint2 *out, hipStream_t stream);
+// bits: the flow kernels' solid upstream links (launch_classify).
+hipError_t launch_thermal_wall_table(const ThermalArgs &t, const unsigned *bits, uint2 *out,
+                                     hipStream_t stream);
 
 // Reverse mode of one temperature step (lwacm_adjoint_thermal_step).
 struct ThermalAdjArgs {
