@@ -189,8 +189,14 @@ __device__ __forceinline__ void wall_nodes(const ProblemArgs &p, const WallList 
 // with stochastic rounding.  Both are template parameters so that the plane
 // loop has no branches: with one around the rounding the loads no longer
 // overlapped the planes' arithmetic and a step took twice as long.
+// Three waves a SIMD (168 VGPRs): with walls and a force it took 170 and ran two
+// (150x84x75, sphere in a duct with distances and a uniform force 18.7 us a
+// step, now 15.8; force field 19.8, now 18.7).  Not for the force field
+// without walls, which would spill eight VGPRs in the plane loop (14.5, held to
+// 168 16.7; 250^3 176, 209), nor the reverse step (19.7, held 22.1).
+constexpr int fwd_waves(bool MASK, int FORCE) { return MASK || FORCE < 2 ? 3 : 2; }
 template <class T, bool SR, bool MASK, int FORCE>
-__global__ __launch_bounds__(NT) void k_fwd_column(ProblemArgs p, int nzc, WallList wl,
+__global__ __launch_bounds__((NT), (fwd_waves(MASK, FORCE))) void k_fwd_column(ProblemArgs p, int nzc, WallList wl,
                                                    const uint8_t *__restrict__ cls,
                                                    const T *__restrict__ src, T *__restrict__ dst,
                                                    ReduceArgs r)
