@@ -171,6 +171,13 @@ bool use_multi(const lwacm_ctx *c)
            lwacm::d2q9_multi_num_blocks(c->p) <= c->n_partial_blocks;
 }
 
+// kMultiSteps of them at a time as marching strips (lwacm_d2q9_strip.hip).
+bool use_strip(const lwacm_ctx *c)
+{
+    return use_multi(c) && lwacm::d2q9_strip_supported(c->p) &&
+           lwacm::d2q9_strip_num_blocks(c->p) <= c->n_partial_blocks;
+}
+
 // The temperature step rides in the flow's tile kernel (the flow's own
 // temperature lattice).
 bool fuses_thermal(const lwacm_ctx *c)
@@ -528,6 +535,7 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
         p.multi_tile = 16;  // the most blocks: link velocities, which may be set later
         const size_t qb = d_mask ? lwacm::d2q9_multi_num_blocks(p) : 0;
         p.multi_tile = lwacm::d2q9_multi_choose_tile(p, c->ncu);
+        p.strip_rows = lwacm::d2q9_strip_choose_rows(p, c->ncu);
         const size_t tb = lwacm::d2q9_multi_num_blocks(p);
         nb = qb > nb ? qb : nb;
         nb = tb > nb ? tb : nb;
@@ -914,6 +922,7 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
     const bool fuse = march && use_march2(c);
     const bool column = !march && use_column(c);
     const bool multi = !march && use_multi(c);
+    const bool strip = multi && use_strip(c);
     const unsigned nb1 = march ? lwacm::march_num_blocks(c->p)
                          : column ? lwacm::column_num_blocks(c->p, c->n_wlist)
                          : multi  ? lwacm::d2q9_multi_num_blocks(c->p)
@@ -930,10 +939,11 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
     int s = 0;
     for (int launch = 0; s < nsteps; ++launch) {
         // an odd step count starts with one single step, then pairs; the
-        // multi-step D2Q9 kernel takes up to kMultiSteps steps at a time
+        // multi-step D2Q9 kernels take up to kMultiSteps steps at a time
         const bool two = fuse && (nsteps - s) % 2 == 0;
         const int kk = multi ? (nsteps - s < lwacm::kMultiSteps ? nsteps - s : lwacm::kMultiSteps)
                              : (two ? 2 : 1);
+        const bool stripped = strip && kk == lwacm::kMultiSteps;
         double *part = c->d_partials + 2 * set * (size_t)(launch & 1);
         ReduceArgs r = reduce_args(c, c->d_diag, hist_slot(c, c->steps + 1));
         r.partials = part;
@@ -990,6 +1000,9 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
         else if (column)
             e = lwacm::launch_fwd_column(c->p, c->storage, src, dst, c->d_cls, c->d_wlist,
                                          c->n_wlist, r, c->stream);
+        else if (stripped)
+            e = lwacm::launch_fwd_d2q9_strip(c->p, static_cast<const float *>(src),
+                                             static_cast<float *>(dst), r, c->stream);
         else if (multi)
             e = lwacm::launch_fwd_d2q9_multi(c->p, static_cast<const float *>(src),
                                              static_cast<float *>(dst), kk, r, c->stream);
@@ -1005,7 +1018,7 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
                                          static_cast<float *>(dst), r2, nb1, c->stream);
         }
         if (e != hipSuccess) return LWACM_EDEVICE;
-        const unsigned nb = two ? nb2 : nb1;
+        const unsigned nb = two ? nb2 : stripped ? lwacm::d2q9_strip_num_blocks(c->p) : nb1;
         npend = 0;
         pend[npend++] = {r.partials, r.out, r.out2, nb};
         if (two) pend[npend++] = {r.partials_b, c->d_diag, hist_slot(c, c->steps + 2), nb};
@@ -1367,8 +1380,10 @@ int lwacm_step_static(int lattice, int nx, int ny, int nz, double omega, float *
         if (mb > nb) nb = mb;
     }
     if (nb > kStaticMaxBlocks) return LWACM_ESCRATCH;
-    if (lattice == LWACM_D2Q9) p.multi_tile = lwacm::d2q9_multi_choose_tile(p, ncu);
-    else p.col_nzc = lwacm::column_choose_depth(p, ncu);
+    if (lattice == LWACM_D2Q9) {
+        p.multi_tile = lwacm::d2q9_multi_choose_tile(p, ncu);
+        p.strip_rows = lwacm::d2q9_strip_choose_rows(p, ncu);
+    } else p.col_nzc = lwacm::column_choose_depth(p, ncu);
     double *base = nullptr;
     const int rc = static_scratch(&base);
     if (rc != LWACM_OK) return rc;

@@ -20,6 +20,9 @@
 // the chip with them; smaller grids take tiles of 16 (2.1) or 8 (3.8), which
 // spread the same nodes over more compute units (d2q9_multi_choose_tile).
 //
+// Large grids without walls or force take eight steps at a time as strips in
+// registers instead (lwacm_d2q9_strip.hip).
+//
 // FP32 storage, one to eight steps per launch.  What the steps need beyond the
 // states is put into LDS with them: a force field (two floats a node), the
 // wall-motion terms of the per-id table (one float per id and link), and for
