@@ -534,7 +534,7 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
     if (lattice == LWACM_D2Q9) {
         p.multi_tile = 16;  // the most blocks: link velocities, which may be set later
         const size_t qb = d_mask ? lwacm::d2q9_multi_num_blocks(p) : 0;
-        p.multi_tile = lwacm::d2q9_multi_choose_tile(p, c->ncu);
+        lwacm::d2q9_multi_choose_tile(p, c->ncu);
         p.strip_rows = lwacm::d2q9_strip_choose_rows(p, c->ncu);
         const size_t tb = lwacm::d2q9_multi_num_blocks(p);
         nb = qb > nb ? qb : nb;
@@ -1381,7 +1381,7 @@ int lwacm_step_static(int lattice, int nx, int ny, int nz, double omega, float *
     }
     if (nb > kStaticMaxBlocks) return LWACM_ESCRATCH;
     if (lattice == LWACM_D2Q9) {
-        p.multi_tile = lwacm::d2q9_multi_choose_tile(p, ncu);
+        lwacm::d2q9_multi_choose_tile(p, ncu);
         p.strip_rows = lwacm::d2q9_strip_choose_rows(p, ncu);
     } else p.col_nzc = lwacm::column_choose_depth(p, ncu);
     double *base = nullptr;

@@ -28,9 +28,10 @@ static long long tiles_of(const ProblemArgs &p, int mt)
 // 11.2 / 16.1 us at 128^2 (256 / 64 / 16 workgroups), 12.1 / 11.5 / 16.2 at
 // 164^2, 19.1 / 11.5 / 16.3 at 256^2, 15.2 (16) against 16.5 (32) at 324^2, 22 /
 // 16.8 at 512^2, 93 / 63 at 1501 x 1003.
-int d2q9_multi_choose_tile(const ProblemArgs &p, int ncu)
+void d2q9_multi_choose_tile(ProblemArgs &p, int ncu)
 {
-    return tiles_of(p, 8) <= ncu ? 8 : (4 * tiles_of(p, 16) <= 7 * ncu ? 16 : 32);
+    p.multi_tile = tiles_of(p, 8) <= ncu ? 8 : (4 * tiles_of(p, 16) <= 7 * ncu ? 16 : 32);
+    p.multi_many = tiles_of(p, 32) > ncu;
 }
 
 // the tile of a launch: link data fit the small tiles' LDS only

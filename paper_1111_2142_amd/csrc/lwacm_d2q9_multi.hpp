@@ -60,6 +60,14 @@ constexpr int multi_threads(int MT, int rows)
                : 1024;
 }
 
+// With walls or a separate omega_p a workgroup of 1024 threads takes more than
+// half of a CU's registers, and one runs at a time.  Where tiles of 32 come in
+// more than one round, workgroups of 512 run in pairs, and one's arithmetic
+// fills the other's barriers and LDS reads (eight steps with walls at 520^2 38.2
+// -> 31.3 us, at 1501 x 1003 107 -> 82; omega_p at 1024^2 62.8 -> 50.7; a single
+// round is as fast with 1024, and the plain update fits twice as it is).
+constexpr bool fwd_pair(int MT, bool MASK, bool SPLIT) { return MT == 32 && (MASK || SPLIT); }
+
 // v in [-MK, n + MT + MK) wrapped into [0, n)
 template <int MT>
 __device__ __forceinline__ int wrap_region(int v, int n)
@@ -174,15 +182,16 @@ __device__ __forceinline__ void wall_update(const ProblemArgs &p, const FSite &s
 }
 
 // FORCE: 0 none, 1 uniform, 2 field; SPLIT: a separate omega_p; QW: link-wall
-// distances or wall velocities given link by link (with MASK).
-template <int MT, bool MASK, int FORCE, bool SPLIT, bool QW>
-__global__ __launch_bounds__(multi_threads(MT, fwd_rows(MT, MASK))) void k_fwd_d2q9_multi(
+// distances or wall velocities given link by link (with MASK); PAIR: half the
+// threads, so that two workgroups share a CU (fwd_pair).
+template <int MT, bool MASK, int FORCE, bool SPLIT, bool QW, bool PAIR>
+__global__ __launch_bounds__((multi_threads(MT, fwd_rows(MT, MASK)) >> PAIR)) void k_fwd_d2q9_multi(
     ProblemArgs p, const float *__restrict__ src, float *__restrict__ dst, int ksteps, ReduceArgs r,
     float *__restrict__ slots, size_t slot_floats)
 {
     static_assert(!QW || (MASK && !SPLIT && MT <= 16), "link data: walls, one omega, small tiles");
     constexpr int MR = fwd_rows(MT, MASK);
-    constexpr int NT = multi_threads(MT, MR);
+    constexpr int NT = multi_threads(MT, MR) >> PAIR;
     constexpr int MW = MT + 2 * MK;      // region side
     constexpr int NREG = MW * MW;
     // per node of the region, two steps' buffers: (rho - 1, u_x, u_y, w) with
@@ -617,7 +626,14 @@ template <int MT, bool MASK, int FORCE, bool SPLIT, bool QW>
 void fwd_multi(const ProblemArgs &p, unsigned nb, const MultiFwd &f, const ReduceArgs &r,
                hipStream_t s)
 {
-    k_fwd_d2q9_multi<MT, MASK, FORCE, SPLIT, QW><<<nb, multi_threads(MT, fwd_rows(MT, MASK)), 0, s>>>(
+    constexpr int nt = multi_threads(MT, fwd_rows(MT, MASK));
+    if constexpr (fwd_pair(MT, MASK, SPLIT))
+        if (p.multi_many) {
+            k_fwd_d2q9_multi<MT, MASK, FORCE, SPLIT, QW, true><<<nb, nt / 2, 0, s>>>(
+                p, f.src, f.dst, f.ksteps, r, f.slots, f.slot_floats);
+            return;
+        }
+    k_fwd_d2q9_multi<MT, MASK, FORCE, SPLIT, QW, false><<<nb, nt, 0, s>>>(
         p, f.src, f.dst, f.ksteps, r, f.slots, f.slot_floats);
 }
 

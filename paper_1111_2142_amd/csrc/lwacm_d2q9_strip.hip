@@ -203,11 +203,11 @@ bool d2q9_strip_supported(const ProblemArgs &p)
 // (the levels' start costs about eight), so the least ceil(waves / SIMDs) *
 // (rows + 8).  Eight steps take 10.6 + 1.085 us times that (with omega_p 10.7 +
 // 1.55); on tiles of 32, which run a round of one per CU at a time, 6 + 10 us
-// times the rounds (with omega_p 3.8 + 14.9), so strips are taken where
+// times the rounds (with omega_p 5 + 11.4), so strips are taken where
 // cost + 5 < 9 rounds.  Tiles / strips: 512^2 17.5 / 24.9, 600^2 26.3 / 27.7,
 // 1024 x 512 25.2 / 32.3, 724^2 36.6 / 32.3, 1024^2 44.3 / 44.5, 1501 x 1003 63.0
-// / 54.0, 2000^2 156 / 114, 4096^2 608 / 392; with omega_p 724^2 48.6 / 42.0,
-// 1501 x 1003 93 / 73.
+// / 54.0, 2000^2 156 / 114, 4096^2 608 / 392; with omega_p 1501 x
+// 1003 71 / 73, 2000^2 183 / 158.
 int d2q9_strip_choose_rows(const ProblemArgs &p, int ncu)
 {
     if (ncu < 1) ncu = 1;

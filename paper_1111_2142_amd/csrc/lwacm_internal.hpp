@@ -52,6 +52,7 @@ struct ProblemArgs {
     int march_plan_blocks, march_plan_depth;  // their number; the first one's depth
     int col_nzc;             // planes per workgroup of the column kernels (0: unused)
     int multi_tile;          // tile side of the multi-step D2Q9 kernels (0: unused)
+    int multi_many;          // more such tiles than CUs
     int strip_rows;          // rows per wave of the D2Q9 strip kernel (0: unused)
     // the temperature step fused into the single-step tile kernel (thermal
     // problems, march_thermal_supported): T at the step's time and one step
@@ -219,7 +220,7 @@ hipError_t launch_fwd_march2(const ProblemArgs &p, const float *src, float *dst,
 // velocities), up to kMultiSteps steps per launch in LDS, one partial pair per
 // tile.
 constexpr int kMultiSteps = 8;
-int d2q9_multi_choose_tile(const ProblemArgs &p, int ncu);  // for a device of ncu CUs
+void d2q9_multi_choose_tile(ProblemArgs &p, int ncu);  // for a device of ncu CUs
 bool d2q9_multi_supported(const ProblemArgs &p);
 unsigned d2q9_multi_num_blocks(const ProblemArgs &p);
 // Up to kMultiSteps D2Q9 reverse steps per launch (FP32, the forward
