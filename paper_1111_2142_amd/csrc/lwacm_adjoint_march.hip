@@ -44,8 +44,16 @@ enum Role { INTERIOR = 0, HALO_Y = 1, HALO_X = 2 };
 // XOUT (no walls): the factors (rho, x) of the nodes' dL/da = rho x go to xout
 // (n pairs) instead of into block partials; chunks of any depth then give the same sums
 // (k_adj_dadomega adds them).
-template <class T, int TAIL, bool MASK, bool FINAL, bool XOUT>
-__global__ __launch_bounds__(NTHREADS) void k_adj_march(ProblemArgs p, int nzc,
+//
+// PAIR: held to 80 VGPRs (six waves a SIMD; 7 to 23 spilled).  The 88 to 93 it
+// takes otherwise allow five, 20 waves a CU, which two workgroups of ten fill
+// exactly, and not on every CU do the second one's waves find their SIMDs: where
+// the grid is one full round of two workgroups a CU, the ones left over make a
+// round of their own (256^3, 512 workgroups: 189 us, held 170).  On other grids the
+// spills cost more (224^3, 392 workgroups: 121, held 133; 288 x 256 x 256, 576:
+// 208, held 221; 192^3, one a CU: 67, held 82).
+template <class T, int TAIL, bool MASK, bool FINAL, bool XOUT, bool PAIR>
+__global__ __launch_bounds__((NTHREADS), (PAIR ? 6 : 1)) void k_adj_march(ProblemArgs p, int nzc,
                                                         const T *__restrict__ state,
                                                         const float *__restrict__ mu_in,
                                                         float *__restrict__ mu_out,
@@ -233,18 +241,16 @@ __global__ __launch_bounds__(NINT) void k_adj_dadomega(ProblemArgs p, int nzc,
     store_block_partials<1>(v, partials + blockIdx.y * stride, blockIdx.x);
 }
 
-template <class T, bool MASK, bool FINAL, bool XOUT>
-void launch_t(const ProblemArgs &p, const T *st, const float *mu_in, float *mu_out,
-              const unsigned *bits, const float4 *wallg, float2 *x, const ReduceArgs &r,
-              hipStream_t s)
+template <class T, bool MASK, bool FINAL, bool XOUT, bool PAIR>
+void launch_t(const ProblemArgs &p, int c, unsigned nb, const T *st, const float *mu_in,
+              float *mu_out, const unsigned *bits, const float4 *wallg, float2 *x,
+              const ReduceArgs &r, hipStream_t s)
 {
     // a loop of c + 2 iterations, its tail 3 + (c + 2) % 3
-    const int c = XOUT ? adj_split_depth(p) : adj_depth(p);
-    const unsigned nb = adj_blocks(p, c);
     switch ((c + 2) % 3) {
-    case 0: k_adj_march<T, 3, MASK, FINAL, XOUT><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
-    case 1: k_adj_march<T, 4, MASK, FINAL, XOUT><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
-    default: k_adj_march<T, 5, MASK, FINAL, XOUT><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
+    case 0: k_adj_march<T, 3, MASK, FINAL, XOUT, PAIR><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
+    case 1: k_adj_march<T, 4, MASK, FINAL, XOUT, PAIR><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
+    default: k_adj_march<T, 5, MASK, FINAL, XOUT, PAIR><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
     }
 }
 
@@ -254,9 +260,21 @@ void dispatch(const ProblemArgs &p, const void *state, const float *mu_in, float
               hipStream_t s)
 {
     const T *st = static_cast<const T *>(state);
-    if (p.mask) launch_t<T, true, FINAL, false>(p, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
-    else if (x) launch_t<T, false, FINAL, true>(p, st, mu_in, mu_out, bits, wallg, x, r, s);
-    else launch_t<T, false, FINAL, false>(p, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
+    const int c = x ? adj_split_depth(p) : adj_depth(p);
+    const unsigned nb = adj_blocks(p, c);
+    if (x) {
+        launch_t<T, false, FINAL, true, false>(p, c, nb, st, mu_in, mu_out, bits, wallg, x, r, s);
+        return;
+    }
+    // one round of two workgroups a CU, a sixteenth of it or less empty
+    const bool pair = 8LL * nb > 15LL * p.ncu && nb <= 2LL * p.ncu;
+    if (p.mask) {
+        if (pair) launch_t<T, true, FINAL, false, true>(p, c, nb, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
+        else launch_t<T, true, FINAL, false, false>(p, c, nb, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
+    } else {
+        if (pair) launch_t<T, false, FINAL, false, true>(p, c, nb, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
+        else launch_t<T, false, FINAL, false, false>(p, c, nb, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
+    }
 }
 
 }  // namespace

@@ -529,7 +529,7 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
     unforced.has_force = 0;
     unforced.qd = nullptr;  // interpolated walls run on the tiles with the wall correction
     size_t nb = lwacm::kGenericMaxBlocks;
-    c->ncu = device_cus();
+    c->ncu = p.ncu = device_cus();
     if (lattice == LWACM_D3Q19) p.col_nzc = lwacm::column_choose_depth(p, c->ncu);
     if (lattice == LWACM_D2Q9) {
         p.multi_tile = 16;  // the most blocks: link velocities, which may be set later

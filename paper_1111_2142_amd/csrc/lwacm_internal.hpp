@@ -44,6 +44,7 @@ struct ProblemArgs {
     // before normalisation; nullptr: the halfway rule with the per-id
     // moving-wall sums
     const float4 *corr;
+    int ncu;                 // compute units of the device (0: not asked)
     int march_nzc;           // planes per workgroup of the forward tile kernels (0: unused)
     // with walls: the workgroups of the forward tile kernels one by one (null:
     // march_nzc planes each): {xs, ys, zs, depth}, the depths of one residue
