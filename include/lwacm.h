@@ -181,8 +181,9 @@ int lwacm_set_variant(lwacm_ctx *c, int variant);
  * (LWACM_EINVAL otherwise; LWACM_EUNSUPPORTED if the tile kernel cannot run
  * this problem).  lwacm_init picks the depth (any number of planes from 8 on)
  * that minimises the plane steps per compute unit, ceil(workgroups / CUs) *
- * (depth + 10); this call overrides it (tuning, tests).  Results do not
- * depend on the depth. */
+ * (depth + 10), with walls tile by tile (tiles next to walls cost more and take
+ * shallower chunks); this call sets one depth for all (tuning, tests).  The
+ * state does not depend on the depth. */
 int lwacm_set_march_chunk(lwacm_ctx *c, int planes);
 
 /* Separate relaxation frequency omega_p of the continuity (density) update
@@ -373,11 +374,11 @@ int lwacm_set_state(lwacm_ctx *c, const float *d_drho, const float *d_u);
  * reproducible); see lwacm_diagnostics.  Where LWACM_KERNEL_MARCH2 applies,
  * pairs of steps run as one launch (an odd count starts with a single step);
  * the state, the diagnostics and the history are the same as with single
- * steps.  D2Q9 problems in FP32 storage without a diagnostics history,
- * link-wall distances, link velocities, a separate omega_p, a force field, a
- * temperature or the semi-implicit update run up to 8 steps per launch in
- * LDS (variant AUTO): the state is bitwise that of single steps, the mass and
- * energy equal to FP64 rounding.  Asynchronous. */
+ * steps.  D2Q9 problems in FP32 storage without a diagnostics history, a
+ * temperature or the semi-implicit update run up to 8 steps per launch in LDS
+ * or, on large grids without walls or force, in registers (variant AUTO): the
+ * state is bitwise that of single steps, the mass and energy equal to FP64
+ * rounding.  Asynchronous. */
 int lwacm_step(lwacm_ctx *c, int nsteps);
 
 /* Mass and energy of the state after the most recent lwacm_step (host

@@ -249,7 +249,7 @@ struct Xchg {
 // link instead of three, and no lane masks in SGPRs: 505 -> 481 VALU a plane
 // and 168 -> 134 VGPRs in the two-step kernel; tiles at the x walls (all five
 // masked links of a side at work) 60.2 -> 57.7 us a step at 192^3, the cavity
-// there 1575 -> 1506 us for 24 steps.
+// there 1575 -> 1506 us for 25 steps.
 __device__ __forceinline__ float select_link(unsigned bits, int i, float lo)
 {
     int one = 1;
