@@ -15,6 +15,8 @@
 // seven 16-byte LDS reads in the tile kernels.  The halo costs 64 / 48 in x (8
 // columns a side, one a step) and, with the levels started as their first rows
 // arrive, (rows + 7) / rows in y.  d2q9_strip_choose_rows has the times.
+#include <type_traits>
+
 #include "lwacm_device.hpp"
 #include "lwacm_generic_update.hpp"
 #include "lwacm_internal.hpp"
@@ -134,7 +136,7 @@ __global__ __launch_bounds__(NT) void k_fwd_d2q9_strip(ProblemArgs p, const floa
         yl = yl < 0 ? yl + p.ny : yl;
         float in[2][3];
         auto load = [&](float (&v)[3]) {
-            const float *a = src + 3 * (size_t)yl * p.nx + 3 * gx;
+            const float *a = src + 3 * (size_t)yl * p.nx + 3 * (size_t)gx;
             v[0] = a[0];
             v[1] = a[1];
             v[2] = a[2];
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(NT) void k_fwd_d2q9_strip(ProblemArgs p, const floa
             if (last == K) {
                 const int y = y0 + j - 2 * K;
                 if (put && y < y0 + nout) {
-                    float *o = dst + 3 * (size_t)y * p.nx + 3 * x;
+                    float *o = dst + 3 * (size_t)y * p.nx + 3 * (size_t)x;
                     o[0] = dr;
                     o[1] = ux;
                     o[2] = uy;
