@@ -182,11 +182,12 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march(ProblemArgs p, const T *
                 Acc &Am = acc[(j + 2) % 3];  // target plane pz - 1 (finalised now)
 
                 // ---- consume the ring slot of plane pz, refill it with pz + 3
-                const float dr = BufIO<T>::value(ring[rj].v, 0, p.ld_scale[0]);
-                const float ux = BufIO<T>::value(ring[rj].v, 1, p.ld_scale[1]);
-                const float uy = BufIO<T>::value(ring[rj].v, 2, p.ld_scale[1]);
-                const float uz = BufIO<T>::value(ring[rj].v, 3, p.ld_scale[1]);
+                float dr = BufIO<T>::value(ring[rj].v, 0, p.ld_scale[0]);
+                float ux = BufIO<T>::value(ring[rj].v, 1, p.ld_scale[1]);
+                float uy = BufIO<T>::value(ring[rj].v, 2, p.ld_scale[1]);
+                float uz = BufIO<T>::value(ring[rj].v, 3, p.ld_scale[1]);
                 const int cls = MASK ? (int)ring[rj].cls : 0;
+                if (MASK) zero_if_solid((unsigned)cls >> 1, dr, ux, uy, uz);  // class 2
                 // refill with plane pz + RING (unconditional; past the chunk it
                 // re-reads plane z1, which is cached and never consumed)
                 if (k + RING < NZC + 2) issue(ring[rj], min(pz + RING, z1));
@@ -233,16 +234,17 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march(ProblemArgs p, const T *
                 const int rj = k % RING;
                 const int pz = z0 - 1 + k;
                 const int j1 = (j + 1) % 3, jm = (j + 2) % 3;
-                const float dr = BufIO<T>::value(ring[rj].v, 0, p.ld_scale[0]);
-                const float ux = BufIO<T>::value(ring[rj].v, 1, p.ld_scale[1]);
-                const float uy = BufIO<T>::value(ring[rj].v, 2, p.ld_scale[1]);
-                const float uz = BufIO<T>::value(ring[rj].v, 3, p.ld_scale[1]);
+                float dr = BufIO<T>::value(ring[rj].v, 0, p.ld_scale[0]);
+                float ux = BufIO<T>::value(ring[rj].v, 1, p.ld_scale[1]);
+                float uy = BufIO<T>::value(ring[rj].v, 2, p.ld_scale[1]);
+                float uz = BufIO<T>::value(ring[rj].v, 3, p.ld_scale[1]);
                 const int cls = MASK ? (int)ring[rj].cls : 0;
+                if (MASK) zero_if_solid((unsigned)cls >> 1, dr, ux, uy, uz);  // class 2
                 // refill with plane pz + RING (unconditional; past the chunk it
                 // re-reads plane z1, which is cached and never consumed)
                 if (k + RING < NZC + 2) issue(ring[rj], min(pz + RING, z1));
-                push_halo<MASK>(dr, ux, uy, uz, cls, A, role == HALO_Y, sgn, hp[j1], hz[j1], hp[j],
-                                hd1[j], hd2[j], hp[jm], hz[jm]);
+                push_halo(dr, ux, uy, uz, A, role == HALO_Y, sgn, hp[j1], hz[j1], hp[j], hd1[j],
+                          hd2[j], hp[jm], hz[jm]);
                 if (k < 2) return;
                 if (NBUF == 1 && k > 2) __syncthreads();
                 if (active)
@@ -440,16 +442,20 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
             float dr, ux, uy, uz;
             value(ring[j], dr, ux, uy, uz);
             const unsigned b = bw[j];
+            float Tz = THERM ? __builtin_bit_cast(float, tw[j]) : 0.0f;  // the T it pushes
+            if (MASK) zero_if_solid(b, dr, ux, uy, uz);
+            if (MASK && THERM) zero_if_solid(b, Tz);
             Acc &Am = acc[(j + 2) % 3];  // target plane pz - 1 (finalised now)
             // the correction of plane pz - 1, loaded in the previous iteration
             const f32x4 cw = cwr[(j + 2) % 3];
             push_column<MASK>(dr, ux, uy, uz, MASK ? class_of(b) : 0, b, A, a, acc[(j + 1) % 3],
                               acc[j], Am, !corr, vu);
             if (SPLIT) push_split_column(1.0f + dr, ux, uy, uz, dA, acc[(j + 1) % 3], acc[j], Am);
-            if (THERM)
-                push_temp_column<MASK>(__builtin_bit_cast(float, tw[j]), ux, uy, uz, p.t_h,
-                                       acc[(j + 1) % 3], acc[j], Am, MASK ? class_of(b) : 0, b,
+            if (THERM) {
+                push_temp_column<MASK>(Tz, ux, uy, uz, p.t_h, acc[(j + 1) % 3], acc[j], Am, b,
                                        twb[j]);
+                acc[j].tx = __builtin_bit_cast(float, tw[j]);  // a solid node keeps its own
+            }
             if (FRC) {  // post-combine a rho u plus the forcing rho g
                 const float rho = 1.0f + dr, arho = a * rho;
                 const float gx = FRC == 2 ? __builtin_bit_cast(float, gq[j][0]) : p.g[0];
@@ -535,14 +541,17 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
             __builtin_amdgcn_sched_barrier(0);
             float dr, ux, uy, uz;
             value(ring[j], dr, ux, uy, uz);
-            push_halo<MASK>(dr, ux, uy, uz, MASK ? class_of(bw[j]) : 0, A, isY, sgn, hp[j1],
-                            hz[j1], hp[j], hd1[j], hd2[j], hp[jm], hz[jm], vu);
+            float Tz = THERM ? __builtin_bit_cast(float, tw[j]) : 0.0f;
+            if (MASK) zero_if_solid(bw[j], dr, ux, uy, uz);
+            if (MASK && THERM) zero_if_solid(bw[j], Tz);
+            push_halo(dr, ux, uy, uz, A, isY, sgn, hp[j1], hz[j1], hp[j], hd1[j], hd2[j], hp[jm],
+                      hz[jm], vu);
             if (SPLIT)
                 push_split_halo(1.0f + dr, ux, uy, uz, dA, isY, sgn, hq[j1], hq[j], hq1[j], hq2[j],
                                 hq[jm]);
             if (THERM)
-                push_temp_halo(__builtin_bit_cast(float, tw[j]), ux, uy, uz, p.t_h, isY, sgn, hq[j1],
-                               hq[j], hq1[j], hq2[j], hq[jm], MASK && class_of(bw[j]) >= 2);
+                push_temp_halo(Tz, ux, uy, uz, p.t_h, isY, sgn, hq[j1], hq[j], hq1[j], hq2[j],
+                               hq[jm]);
             __builtin_amdgcn_sched_barrier(0);
             if (I::refill) issue(j, ring[j], z0 + 2 + k);
             if (I::phase < 2) return;

@@ -197,7 +197,9 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
         __builtin_amdgcn_sched_barrier(0);  // no work of this iteration moves up
         const f32x4 v = ring[I::j].v;
         const unsigned b = bw[I::j];
-        push_column<MASK>(v.x, v.y, v.z, v.w, MASK ? class_of(b) : 0, b, A, a,
+        float dr = v.x, ux = v.y, uy = v.z, uz = v.w;
+        if (MASK) zero_if_solid(b, dr, ux, uy, uz);
+        push_column<MASK>(dr, ux, uy, uz, MASK ? class_of(b) : 0, b, A, a,
                           acc1[(I::j + 1) % 3], acc1[I::j], acc1[(I::j + 2) % 3]);
         refill(k, It);
     };
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
         put_slot(X1, wslot1, Am);
         __syncthreads();
         const int tq = z0 - 3 + k;
-        const NodeOut o = finalize<MASK, NS1 + 1, SX1>(X1, slot1, Am, p, wallg,
+        NodeOut o = finalize<MASK, NS1 + 1, SX1>(X1, slot1, Am, p, wallg,
                                                        (long long)wrapz(tq) * plane + col);
         // the node's class and link set at plane tq, kept by its first push
         const int cls = MASK ? Am.cls : 0;
@@ -219,14 +221,15 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
             m1 += count ? o.D : 0.0f;
             e1 = count ? fmaf(o.vx, o.vx, fmaf(o.vy, o.vy, fmaf(o.vz, o.vz, e1))) : e1;
         }
+        if (MASK) zero_if_solid(bits, o.D, o.vx, o.vy, o.vz);
         if (tile) {
             push_column<MASK>(o.D, o.vx, o.vy, o.vz, cls, bits, A, a, acc2[(I::j + 1) % 3],
                               acc2[I::j], acc2[(I::j + 2) % 3]);
             if (I::phase >= 4) put_slot(X2, wslot2, acc2[(I::j + 2) % 3]);
         } else {
             constexpr int j = I::j, j1 = (j + 1) % 3, jm = (j + 2) % 3;
-            push_halo<MASK>(o.D, o.vx, o.vy, o.vz, cls, A, isY2, sgn2, hp[j1], hz[j1], hp[j],
-                            hd1[j], hd2[j], hp[jm], hz[jm]);
+            push_halo(o.D, o.vx, o.vy, o.vz, A, isY2, sgn2, hp[j1], hz[j1], hp[j], hd1[j], hd2[j],
+                      hp[jm], hz[jm]);
             if (I::phase >= 4) put_halo(X2, wslot2, isY2, sgn2, hp[jm], hz[jm], hd1[jm], hd2[jm]);
         }
         __syncthreads();
@@ -269,8 +272,10 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
             constexpr int j = I::j, j1 = (j + 1) % 3, jm = (j + 2) % 3;
             __builtin_amdgcn_sched_barrier(0);
             const f32x4 v = ring[j].v;
-            push_halo<MASK>(v.x, v.y, v.z, v.w, MASK ? class_of(bw[j]) : 0, A, isY, sgn, hp[j1],
-                            hz[j1], hp[j], hd1[j], hd2[j], hp[jm], hz[jm]);
+            float dr = v.x, ux = v.y, uy = v.z, uz = v.w;
+            if (MASK) zero_if_solid(bw[j], dr, ux, uy, uz);
+            push_halo(dr, ux, uy, uz, A, isY, sgn, hp[j1], hz[j1], hp[j], hd1[j], hd2[j], hp[jm],
+                      hz[jm]);
             refill(k, I{});
             if (I::phase < 2) return;
             put_halo(X1, wslot1, isY, sgn, hp[jm], hz[jm], hd1[jm], hd2[jm]);

@@ -258,6 +258,20 @@ __device__ __forceinline__ float select_link(unsigned bits, int i, float lo)
     return __builtin_bit_cast(float, __builtin_bit_cast(int, lo) & m);
 }
 
+// Zeros in place of the fields of a solid node (bit 0 of b), which may hold
+// anything: a link term of zero fields is zero, while zeroed coefficients let a
+// NaN or infinity through as 0 * NaN.  Cleared by a mask, as in select_link: out
+// of selects the compiler makes a branch (the step with a temperature and walls
+// grew by 7 % in instructions, 22.9 -> 23.5 us a step at 160 x 96 x 100; by the mask 23.0).
+template <class... F>
+__device__ __forceinline__ void zero_if_solid(unsigned b, F &...v)
+{
+    int one = 1;
+    asm("" : "+s"(one));
+    const int m = ~__builtin_amdgcn_sbfe((int)b, 0, one);
+    ((v = __builtin_bit_cast(float, __builtin_bit_cast(int, v) & m)), ...);
+}
+
 // The 18 moving links of a node with state (drho, u) on source plane pz,
 // pre-combined (Eq. ACM2.0b) and pushed, with integer weights 36 w_i folded
 // in, into the accumulators of its column: links with v_z = +1 start A1
@@ -265,7 +279,7 @@ __device__ __forceinline__ float select_link(unsigned bits, int i, float lo)
 // pz) together with the rest link and the post-combine term a rho u, links
 // with v_z = -1 finish Am (plane pz - 1).  Opposite links share the even part
 // m(c) = E0 + 4.5 rho c^2 with E0 = drho - 1.5 rho |u|^2; a solid node pushes
-// zeros.  With MASK, A0 also keeps the class and the coefficients that the
+// zeros (the caller passes zero fields, zero_if_solid).  With MASK, A0 also keeps the class and the coefficients that the
 // bounce-back of its own links needs (its bit set is the caller's).
 // Halfway bounce-back (Eq. ACM2.0cbb): when the upstream node x - v_i of a
 // fluid node is solid (bit i of its link set), link i brings the node's own
@@ -347,14 +361,9 @@ __device__ __forceinline__ void push_column(float dr, float ux, float uy, float 
 {
     const float rho = 1.0f + dr;
     const float usq = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
-    float E0 = fmaf(rho, vu.k15 * usq, dr);
-    float r45 = vu.k45 * rho;
-    float rA = A * rho;
-    if (MASK && cls >= 2) {  // solid: push nothing
-        E0 = 0.0f;
-        r45 = 0.0f;
-        rA = 0.0f;
-    }
+    const float E0 = fmaf(rho, vu.k15 * usq, dr);
+    const float r45 = vu.k45 * rho;
+    const float rA = A * rho;
     auto pair = [&](float c, float &lp, float &lm) {
         const float m = fmaf(r45 * c, c, E0);  // = lterm's even part
         lp = fmaf(rA, c, m);                   // = lterm(c)
@@ -611,7 +620,8 @@ __device__ __forceinline__ void push_split_halo(float rho, float ux, float uy, f
 // problem with a temperature does not use.  Opposite links share the even
 // part, as in push_column.
 //
-// Walls (MASK): a solid node pushes nothing and keeps its T.  Where the
+// Walls (MASK): a solid node pushes nothing (zero fields, as in push_column) and
+// keeps its T.  Where the
 // upstream node x - v_i of a fluid node is solid (bit i of its link set), the
 // node's own term for the opposite link comes back along i: with its sign kept
 // at an adiabatic wall, reversed at a wall held at T_w, which also adds
@@ -621,17 +631,12 @@ __device__ __forceinline__ void push_split_halo(float rho, float ux, float uy, f
 // flow's bounce-back.
 template <bool MASK>
 __device__ __forceinline__ void push_temp_column(float T, float ux, float uy, float uz, float h,
-                                                 Acc &A1, Acc &A0, Acc &Am, int cls = 0,
-                                                 unsigned bits = 0u, uint2 tw = {0u, 0u})
+                                                 Acc &A1, Acc &A0, Acc &Am, unsigned bits = 0u,
+                                                 uint2 tw = {0u, 0u})
 {
     const float usq = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
-    float AT = h * fmaf(-1.5f, usq, T);
-    float H = 4.5f * h, T3 = 3.0f * T;
-    if (MASK && cls >= 2) {  // solid: push nothing
-        AT = 0.0f;
-        H = 0.0f;
-        T3 = 0.0f;
-    }
+    const float AT = h * fmaf(-1.5f, usq, T);
+    const float H = 4.5f * h, T3 = 3.0f * T;
     auto pair = [&](float c, float &lp, float &lm) {
         const float m = fmaf(H * c, c, AT);
         lp = fmaf(T3, c, m);
@@ -664,7 +669,6 @@ __device__ __forceinline__ void push_temp_column(float T, float ux, float uy, fl
     A0.qse = Tpm0;
     A0.qsw = Tmm0;
     A0.qd = fmaf(12.0f, AT, A0.qd);
-    A0.tx = T;
     if (MASK && __builtin_amdgcn_ballot_w64(bits > 1u) != 0ull) {
         // returned terms: all wall links, and again (twice, negated) the
         // fixed-temperature ones
@@ -714,17 +718,11 @@ __device__ __forceinline__ void push_temp_column(float T, float ux, float uy, fl
 // push_halo; the same operations as push_temp_column's pairs)
 __device__ __forceinline__ void push_temp_halo(float T, float ux, float uy, float uz, float h,
                                                bool isY, float sgn, float &q1, float &q0,
-                                               float &qd1, float &qd2, float &qm,
-                                               bool solid = false)
+                                               float &qd1, float &qd2, float &qm)
 {
     const float usq = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
-    float AT = h * fmaf(-1.5f, usq, T);
-    float H = 4.5f * h, T3 = 3.0f * T;
-    if (solid) {  // a solid node pushes nothing
-        AT = 0.0f;
-        H = 0.0f;
-        T3 = 0.0f;
-    }
+    const float AT = h * fmaf(-1.5f, usq, T);
+    const float H = 4.5f * h, T3 = 3.0f * T;
     auto lt = [&](float c) { return fmaf(T3, c, fmaf(H * c, c, AT)); };
     const float ua = isY ? uy : ux;
     const float ub = isY ? ux : uy;
@@ -781,22 +779,16 @@ __device__ __forceinline__ float gather_split(const XchgQ<NS> &X, int slot)
 // diagonals d1 = across +1, d2 = across -1) and pz - 1 (pm, zm).  The same
 // operations as push_column's pairs, so interior and halo produce bitwise
 // the same term for a given link.
-template <bool MASK>
-__device__ __forceinline__ void push_halo(float dr, float ux, float uy, float uz, int cls,
-                                          float A, bool isY, float sgn, float &p1, float &z1,
-                                          float &p0, float &d1, float &d2, float &pm, float &zm,
+__device__ __forceinline__ void push_halo(float dr, float ux, float uy, float uz, float A, bool isY,
+                                          float sgn, float &p1, float &z1, float &p0, float &d1,
+                                          float &d2, float &pm, float &zm,
                                           const VelUnits &vu = VelUnits{})
 {
     const float rho = 1.0f + dr;
     const float usq = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
-    float E0 = fmaf(rho, vu.k15 * usq, dr);
-    float r45 = vu.k45 * rho;
-    float rA = A * rho;
-    if (MASK && cls >= 2) {
-        E0 = 0.0f;
-        r45 = 0.0f;
-        rA = 0.0f;
-    }
+    const float E0 = fmaf(rho, vu.k15 * usq, dr);
+    const float r45 = vu.k45 * rho;
+    const float rA = A * rho;
     const float ua = isY ? uy : ux;  // along the halo direction
     const float ub = isY ? ux : uy;  // across it, in plane
     const float cs = sgn * ua;
