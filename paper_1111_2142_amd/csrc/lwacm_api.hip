@@ -39,7 +39,7 @@ struct lwacm_ctx {
     size_t n_partial_blocks;
     double *d_diag;     // [2] mass deviation, energy of the last step's output
     double *d_scratch;  // [2] for lwacm_moments
-    unsigned *d_scan;   // [2] mask scan
+    unsigned *d_scan;   // [2] mask scan, [1] the mask was edited since (launch_mask_check)
     uint8_t *d_cls;     // node classes for the march kernel (masked problems)
     int4 *h_plan;       // the forward tile kernels' chunks (p.march_plan), as copied to d_cls
     unsigned *d_bits;   // solid-upstream link bits for the march kernel
@@ -62,10 +62,13 @@ struct lwacm_ctx {
     double *d_sweep;
     size_t sweep_cap;
     double *h_force;  // pinned host memory the wall-force sum kernel writes its six results to
-    // fluid nodes next to a wall, in node order (built on first use)
+    // fluid nodes next to a wall, in node order (made by lwacm_init or on first use)
     unsigned *d_wlist;
     unsigned n_wlist;
     bool wlist_built;
+    unsigned *d_flist;  // lwacm_wall_force's own, where it has one (ensure_force_list)
+    unsigned n_flist;
+    bool force_listed;
     float4 *d_corr;   // per-step wall correction of the tile kernels (interpolated walls)
     float *d_wqc;     // packed q of the listed nodes' wall links (18 per node, link-major)
     unsigned *d_wsec; // per listed node: links whose q < 1/2 rule takes the second node
@@ -255,6 +258,9 @@ void free_scratch(lwacm_ctx *c)
     if (c->h_force) (void)hipHostFree(c->h_force);
     c->h_force = nullptr;
     if (c->d_wlist) (void)hipFree(c->d_wlist);
+    if (c->d_flist) (void)hipFree(c->d_flist);
+    c->d_flist = nullptr;
+    c->force_listed = false;
     if (c->d_corr) (void)hipFree(c->d_corr);
     if (c->d_wqc) (void)hipFree(c->d_wqc);
     if (c->d_wsec) (void)hipFree(c->d_wsec);
@@ -309,12 +315,11 @@ hipError_t make_march_plan(lwacm_ctx *c, void *d)
     return e;
 }
 
-// The list of fluid nodes next to a wall (lwacm_walls.hip), built once:
-// counts per block, their scan, the total read back (one synchronisation),
-// then the scatter.  Masked problems with fewer than 2^32 nodes.
-int ensure_wall_list(lwacm_ctx *c)
+// A list of the fluid nodes next to a wall (lwacm_walls.hip): counts per block,
+// their scan, the total read back (one synchronisation), then the scatter.
+// Masked problems with fewer than 2^32 nodes.
+int make_wall_list(lwacm_ctx *c, unsigned **list, unsigned *n)
 {
-    if (c->wlist_built) return LWACM_OK;
     if (!c->p.mask || c->p.n >= (1LL << 32)) return LWACM_EUNSUPPORTED;
     const size_t nb = lwacm::wall_list_count_blocks(c->p.n);
     unsigned *counts = nullptr;
@@ -329,19 +334,47 @@ int ensure_wall_list(lwacm_ctx *c)
     if (e == hipSuccess)
         e = hipMemcpyAsync(&total, d_total, sizeof(total), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e == hipSuccess) e = hipMalloc(&c->d_wlist, (total ? total : 1) * sizeof(unsigned));
-    if (e == hipSuccess) e = lwacm::launch_wall_list_scatter(c->p, counts, c->d_wlist, c->stream);
+    if (e == hipSuccess) e = hipMalloc(list, (total ? total : 1) * sizeof(unsigned));
+    if (e == hipSuccess) e = lwacm::launch_wall_list_scatter(c->p, counts, *list, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     (void)hipFree(counts);
     (void)hipFree(d_total);
     if (e != hipSuccess) {
-        if (c->d_wlist) (void)hipFree(c->d_wlist);
-        c->d_wlist = nullptr;
+        if (*list) (void)hipFree(*list);
+        *list = nullptr;
         return LWACM_EDEVICE;
     }
-    c->n_wlist = (unsigned)total;
-    c->wlist_built = true;
+    *n = (unsigned)total;
     return LWACM_OK;
+}
+
+// The context's list, made once.
+int ensure_wall_list(lwacm_ctx *c)
+{
+    if (c->wlist_built) return LWACM_OK;
+    const int rc = make_wall_list(c, &c->d_wlist, &c->n_wlist);
+    c->wlist_built = rc == LWACM_OK;
+    return rc;
+}
+
+// The list of lwacm_wall_force, made at its first call: the context's, or one of
+// its own where lwacm_init made that one for the column kernels and the mask has
+// been edited since.
+int ensure_force_list(lwacm_ctx *c)
+{
+    if (c->force_listed) return LWACM_OK;
+    unsigned edited = 0;
+    if (c->wlist_built && !lwacm::march_aligned(c->p)) {
+        hipError_t e = lwacm::launch_mask_check(c->p, c->d_cls, c->d_scan + 2, c->stream);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(&edited, c->d_scan + 2, sizeof(edited), hipMemcpyDeviceToHost,
+                               c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return LWACM_EDEVICE;
+    }
+    const int rc = edited ? make_wall_list(c, &c->d_flist, &c->n_flist) : ensure_wall_list(c);
+    c->force_listed = rc == LWACM_OK;
+    return rc;
 }
 
 // Interpolated walls or link velocities on the D3Q19 tile kernels: the wall
@@ -563,7 +596,7 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
     hipError_t e = hipMalloc(&c->d_partials, 8 * nb * sizeof(double));
     if (e == hipSuccess) e = hipMalloc(&c->d_diag, 2 * sizeof(double));
     if (e == hipSuccess) e = hipMalloc(&c->d_scratch, 2 * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc(&c->d_scan, 2 * sizeof(unsigned));
+    if (e == hipSuccess) e = hipMalloc(&c->d_scan, 3 * sizeof(unsigned));
     if (e != hipSuccess) {
         free_scratch(c);
         delete c;
@@ -573,7 +606,7 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
 
     c->n_fluid = (unsigned long long)p.n;
     if (e == hipSuccess && d_mask) {
-        e = hipMemsetAsync(c->d_scan, 0, 2 * sizeof(unsigned), stream);
+        e = hipMemsetAsync(c->d_scan, 0, 3 * sizeof(unsigned), stream);
         if (e == hipSuccess) e = lwacm::launch_mask_scan(p, c->d_scan, stream);
         unsigned scan[2] = {0, 0};
         if (e == hipSuccess)
@@ -845,12 +878,12 @@ int lwacm_wall_force(lwacm_ctx *c, int wall_id, const double *h_center, double *
     f.list = nullptr;
     f.nlist = 0;
     long long items = (long long)c->p.nx * c->p.ny * c->p.nz;
-    const int lrc = ensure_wall_list(c);
+    const int lrc = ensure_force_list(c);
     if (lrc == LWACM_OK) {
         // only the fluid nodes next to a wall carry links into one
-        f.list = c->d_wlist;
-        f.nlist = c->n_wlist;
-        items = c->n_wlist;
+        f.list = c->d_flist ? c->d_flist : c->d_wlist;
+        f.nlist = c->d_flist ? c->n_flist : c->n_wlist;
+        items = f.nlist;
     } else if (lrc != LWACM_EUNSUPPORTED) {
         return lrc;
     }
@@ -929,6 +962,10 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
                                   : lwacm::generic_grid(c->p.n);
     const unsigned nb2 = fuse ? lwacm::march2_num_blocks(c->p) : 0u;
     const size_t set = 2 * c->n_partial_blocks;  // doubles per partial set
+    // the column kernels' classes and list are lwacm_init's, the mask the caller's
+    if (column && c->p.mask && nsteps > 0 &&
+        lwacm::launch_mask_check(c->p, c->d_cls, c->d_scan + 2, c->stream) != hipSuccess)
+        return LWACM_EDEVICE;
     // Steps whose partials are stored but not yet added up (oldest first): the
     // next launch's block 0 adds them, or the final passes after the loop.
     struct Pending {
@@ -999,7 +1036,7 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
                                         c->d_wallg, r, c->stream);
         else if (column)
             e = lwacm::launch_fwd_column(c->p, c->storage, src, dst, c->d_cls, c->d_wlist,
-                                         c->n_wlist, r, c->stream);
+                                         c->n_wlist, c->d_scan + 2, r, c->stream);
         else if (stripped)
             e = lwacm::launch_fwd_d2q9_strip(c->p, static_cast<const float *>(src),
                                              static_cast<float *>(dst), r, c->stream);
@@ -1166,6 +1203,9 @@ int lwacm_forward_states(lwacm_ctx *c, const void *d_state0, long long t0, int n
     const bool column = !march && use_column(c);
     const bool multi = !march && use_multi(c);
     const unsigned nb1 = lwacm::generic_grid(c->p.n);
+    if (column && c->p.mask && nsteps > 0 &&
+        lwacm::launch_mask_check(c->p, c->d_cls, c->d_scan + 2, c->stream) != hipSuccess)
+        return LWACM_EDEVICE;
     // The masked tile kernels leave solid nodes unwritten (the context's two
     // buffers both hold them): the slots get them from d_state0 first.
     if (march && c->p.mask)
@@ -1204,7 +1244,7 @@ int lwacm_forward_states(lwacm_ctx *c, const void *d_state0, long long t0, int n
                                             c->d_wallg, r, c->stream);
             else if (column)
                 e = lwacm::launch_fwd_column(pl, c->storage, src, dst, c->d_cls, c->d_wlist,
-                                             c->n_wlist, r, c->stream);
+                                             c->n_wlist, c->d_scan + 2, r, c->stream);
             else
                 e = lwacm::launch_fwd_generic(pl, c->storage, pl.has_force != 0, src, dst, r, nb1,
                                               c->stream);

@@ -21,6 +21,11 @@
 // workgroups of the same launch: all of a node's neighbours, masks and link
 // distances are loaded before the first is used, so a node costs one memory
 // latency instead of one per link.
+//
+// The classes and the list are those of lwacm_init, but the mask is the
+// caller's, who may edit it between calls: launch_mask_check compares the two at
+// the start of a call, and once they differ every node goes through link_update
+// with the mask as it is.
 #include "lwacm_device.hpp"
 #include "lwacm_generic_update.hpp"
 #include "lwacm_internal.hpp"
@@ -109,7 +114,35 @@ __device__ __forceinline__ void sum_links(const float (&term)[19], float &D36, f
 struct WallList {
     const unsigned *list;  // fluid nodes next to a wall
     unsigned n, blocks;    // entries, and workgroups that take them
+    const unsigned *edited;  // not zero: the mask is no longer the list's
 };
+
+// Solid or fluid in the mask where the classes say otherwise?  Bound by the
+// launch: 3.5 us a call (not a step) at 33x17x8 and at 150x84x75, where the flag's
+// read takes another 0.3 us a step (8.2 -> 8.6, 16.9 -> 17.2).
+__global__ __launch_bounds__(NT) void k_mask_check(const uint8_t *__restrict__ mask,
+                                                   const uint8_t *__restrict__ cls, unsigned n,
+                                                   unsigned *edited)
+{
+    const unsigned first = blockIdx.x * NT + threadIdx.x, threads = gridDim.x * NT;
+    unsigned diff = 0u;
+    const unsigned body = ((uintptr_t)mask & 15u) ? 0u : n / 16u;  // 16 bytes at a time
+    const uint4 *m4 = reinterpret_cast<const uint4 *>(mask);
+    const uint4 *c4 = reinterpret_cast<const uint4 *>(cls);
+    for (unsigned i = first; i < body; i += threads) {
+        const uint4 m = m4[i], c = c4[i];
+        const unsigned mw[4] = {m.x, m.y, m.z, m.w}, cw[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            // bit 7 of each byte: mask not zero, class 2 (the classes are 0 to 2)
+            const unsigned solid = ((mw[k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | mw[k];
+            diff |= (solid ^ (cw[k] << 6)) & 0x80808080u;
+        }
+    }
+    for (unsigned i = 16u * body + first; i < n; i += threads)
+        diff |= (mask[i] != 0) != (cls[i] == 2) ? 1u : 0u;
+    if (diff) *edited = 1u;
+}
 
 // Site of a listed node: distances loaded ahead, the wall table in LDS.
 struct ListSite {
@@ -129,11 +162,9 @@ struct ListSite {
     __device__ __forceinline__ float q(int ib) const { return qv[ib]; }
 };
 
-template <class T, bool SR, bool FORCE>
-__device__ __forceinline__ void wall_nodes(const ProblemArgs &p, const WallList &wl, const T *src,
-                                           T *dst, double (&acc)[2])
+// The wall-motion terms by mask id into LDS; false: every wall at rest.
+__device__ __forceinline__ bool load_wall_table(const ProblemArgs &p, float (&table)[kMaxWallIds][3])
 {
-    __shared__ float table[kMaxWallIds][3];
     bool moving = false;
 #pragma unroll
     for (int m = 1; m < kMaxWallIds; ++m)
@@ -142,9 +173,15 @@ __device__ __forceinline__ void wall_nodes(const ProblemArgs &p, const WallList 
     if (threadIdx.x < 3 * kMaxWallIds)
         table[threadIdx.x / 3][threadIdx.x % 3] = p.wall_term[threadIdx.x / 3][threadIdx.x % 3];
     __syncthreads();
-    const unsigned k = blockIdx.x * NT + threadIdx.x;
-    if (k >= wl.n) return;
-    const unsigned idx = wl.list[k];
+    return moving;
+}
+
+// Fluid node idx by link_update; out: its new state, e: |u|^2.  SOLID: the node
+// may be solid (then false, nothing done).
+template <class T, bool FORCE, bool SOLID>
+__device__ __forceinline__ bool gather_node(const ProblemArgs &p, const float (*table)[3],
+                                            const T *src, unsigned idx, float (&out)[4], float &e)
+{
     const unsigned t = idx / (unsigned)p.nx;
     const int x = (int)(idx - t * (unsigned)p.nx);
     const int z = (int)(t / (unsigned)p.ny), y = (int)(t - (unsigned)z * (unsigned)p.ny);
@@ -158,8 +195,9 @@ __device__ __forceinline__ void wall_nodes(const ProblemArgs &p, const WallList 
              (unsigned)wrap_index(y + link_cy(i), p.ny)) * (unsigned)p.nx +
             (unsigned)wrap_index(x + link_cx(i), p.nx);
         NodeState<T, 4>::load(src, at, p.ld_scale, st[i]);
-        mk[i] = i ? p.mask[at] : (uint8_t)0;
+        mk[i] = i || SOLID ? p.mask[at] : (uint8_t)0;
     }
+    if (SOLID && mk[0]) return false;
 #pragma unroll
     for (int i = 0; i < 19; ++i)
         q[i] = (p.qd && mk[i]) ? p.qd[(long long)i * p.n + idx] : 0.5f;
@@ -173,9 +211,15 @@ __device__ __forceinline__ void wall_nodes(const ProblemArgs &p, const WallList 
         u[2] = v[3];
         B = node_B(u);
     };
-    const ListSite site{{p, (long long)idx}, moving ? table : nullptr, q};
-    float out[4], e;
+    const ListSite site{{p, (long long)idx}, table, q};
     link_update<19, true, FORCE, false>(p, site, st[0][0], ux, node_B(ux), fmask, fstate, out, e);
+    return true;
+}
+
+template <class T, bool SR>
+__device__ __forceinline__ void store_gathered(const ProblemArgs &p, T *dst, unsigned idx,
+                                               const float (&out)[4], float e, double (&acc)[2])
+{
     if (SR)
         NodeState<T, 4>::store_sr(dst, idx, out, p.st_scale, sr_words(idx, p.sr_word));
     else
@@ -202,12 +246,39 @@ __global__ __launch_bounds__((NT), (fwd_waves(MASK, FORCE))) void k_fwd_column(P
                                                    ReduceArgs r)
 {
     double acc[2] = {0.0, 0.0};
-    if (MASK && blockIdx.x < wl.blocks) {
-        wall_nodes<T, SR, FORCE != 0>(p, wl, src, dst, acc);
-    } else {
-        const unsigned first = MASK ? wl.blocks : 0u;
+    const unsigned first = MASK ? wl.blocks : 0u;
+    const unsigned plane = (unsigned)(p.nx * p.ny);
+    const unsigned edited = MASK ? *wl.edited : 0u;
+    if (MASK && blockIdx.x < first) {
+        // the listed nodes, unless the mask is no longer the list's (asked last:
+        // the answer arrives beside the nodes' own loads)
+        __shared__ float table[kMaxWallIds][3];
+        const bool moving = load_wall_table(p, table);
+        const unsigned k = blockIdx.x * NT + threadIdx.x;
+        if (k < wl.n) {
+            const unsigned idx = wl.list[k];
+            float out[4], e;
+            gather_node<T, FORCE != 0, false>(p, moving ? table : nullptr, src, idx, out, e);
+            if (!edited) store_gathered<T, SR>(p, dst, idx, out, e, acc);
+        }
+    } else if (MASK && __builtin_amdgcn_readfirstlane(edited) != 0u) {
+        // every node of the columns by the mask as it is
+        __shared__ float table[kMaxWallIds][3];
+        const bool moving = load_wall_table(p, table);
         const ColumnIdx ci = column_of(p, nzc, blockIdx.x - first, gridDim.x - first);
-        const unsigned plane = (unsigned)(p.nx * p.ny);
+#pragma unroll 1
+        for (int z = ci.z0; z < ci.z1 && ci.active; ++z) {
+            const unsigned idx = (unsigned)z * plane + ci.col[0];
+            float out[4], e;
+            if (gather_node<T, FORCE != 0, true>(p, moving ? table : nullptr, src, idx, out, e)) {
+                store_gathered<T, SR>(p, dst, idx, out, e, acc);
+            } else {  // solid: written through
+                using Raw = typename BufIO<T>::Raw;
+                reinterpret_cast<Raw *>(dst)[idx] = reinterpret_cast<const Raw *>(src)[idx];
+            }
+        }
+    } else {
+        const ColumnIdx ci = column_of(p, nzc, blockIdx.x - first, gridDim.x - first);
         constexpr unsigned NB = BufIO<T>::kNodeBytes;
         const Rsrc rs = make_rsrc(src, (unsigned long long)p.n * NB);
         const Rsrc rd = make_rsrc(dst, (unsigned long long)p.n * NB);
@@ -528,13 +599,22 @@ unsigned column_num_blocks(const ProblemArgs &p, unsigned nlist)
 
 hipError_t launch_fwd_column(const ProblemArgs &p, int storage, const void *src, void *dst,
                              const uint8_t *cls, const unsigned *list, unsigned nlist,
-                             const ReduceArgs &r, hipStream_t stream)
+                             const unsigned *edited, const ReduceArgs &r, hipStream_t stream)
 {
-    if (!column_supported(p) || (p.mask && (!cls || !list))) return hipErrorNotSupported;
-    const WallList wl{list, nlist, p.mask ? wall_blocks(nlist) : 0u};
+    if (!column_supported(p) || (p.mask && (!cls || !list || !edited))) return hipErrorNotSupported;
+    const WallList wl{list, nlist, p.mask ? wall_blocks(nlist) : 0u, edited};
     if (!storage) return fwd<float, false>(p, src, dst, cls, wl, r, stream);
     return p.fp16_sr ? fwd<__half, true>(p, src, dst, cls, wl, r, stream)
                      : fwd<__half, false>(p, src, dst, cls, wl, r, stream);
+}
+
+hipError_t launch_mask_check(const ProblemArgs &p, const uint8_t *cls, unsigned *edited,
+                             hipStream_t stream)
+{
+    if (!p.mask || !cls || !edited || p.n >= (1LL << 28)) return hipErrorInvalidValue;
+    const unsigned nb = (unsigned)((p.n + 16 * NT - 1) / (16 * NT));
+    k_mask_check<<<nb < 1024u ? nb : 1024u, NT, 0, stream>>>(p.mask, cls, (unsigned)p.n, edited);
+    return hipGetLastError();
 }
 
 hipError_t launch_adj_column(const ProblemArgs &p, int storage, const void *state,

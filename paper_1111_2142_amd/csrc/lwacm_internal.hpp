@@ -123,7 +123,11 @@ int column_choose_depth(const ProblemArgs &p, int ncu);  // planes per chunk
 unsigned column_num_blocks(const ProblemArgs &p, unsigned nlist);
 hipError_t launch_fwd_column(const ProblemArgs &p, int storage, const void *src, void *dst,
                              const uint8_t *cls, const unsigned *list, unsigned nlist,
-                             const ReduceArgs &r, hipStream_t stream);
+                             const unsigned *edited, const ReduceArgs &r, hipStream_t stream);
+// Sets *edited where the mask's solid nodes are not those of the classes (else
+// leaves it as it is); launch_fwd_column then takes every node by the mask.
+hipError_t launch_mask_check(const ProblemArgs &p, const uint8_t *cls, unsigned *edited,
+                             hipStream_t stream);
 hipError_t launch_adj_column(const ProblemArgs &p, int storage, const void *state,
                              const float *mu_in, float *mu_out, int final_t0, const ReduceArgs &r,
                              hipStream_t stream);
