@@ -237,6 +237,21 @@ bool use_march2(const lwacm_ctx *c)
     return c->storage == LWACM_FP32 && !c->thermal && lwacm::march2_supported(c->p);
 }
 
+// Grids whose sides are no multiples of the tile follow the caller's mask, who may
+// edit it between calls: what the tile kernel knows of the walls is made anew
+// at the start of each (20 us a call at 100^3, 7 at 33x17x8; set_thermal leaves its
+// table to it).
+bool follow_mask(lwacm_ctx *c)
+{
+    lwacm::FollowMask f;
+    f.T_wall = c->d_twall;
+    f.state = static_cast<const float4 *>(c->buf[c->cur]);
+    f.other = static_cast<float4 *>(c->buf[c->cur ^ 1]);
+    static_assert(sizeof(f.wall_T) == sizeof(c->targs.wall_T), "one temperature per mask id");
+    memcpy(f.wall_T, c->targs.wall_T, sizeof(f.wall_T));
+    return lwacm::launch_follow_mask(c->p, c->d_bits, c->d_wallg, f, c->stream) == hipSuccess;
+}
+
 double *hist_slot(lwacm_ctx *c, long long step)
 {
     return c->d_hist ? c->d_hist + 2 * (size_t)(step % c->hist_cap) : nullptr;
@@ -799,7 +814,9 @@ int lwacm_set_thermal(lwacm_ctx *c, double omega_t, float *d_T_a, float *d_T_b,
             c->d_twall = nullptr;
             return LWACM_ENOMEM;
         }
-        if (lwacm::launch_thermal_wall_table(t, c->d_bits, c->d_twall, c->stream) != hipSuccess)
+        // (sides that are no multiples of the tile: made by lwacm_step, follow_mask)
+        if (lwacm::march_aligned(c->p) &&
+            lwacm::launch_thermal_wall_table(t, c->d_bits, c->d_twall, c->stream) != hipSuccess)
             return LWACM_EDEVICE;
         c->p.T_wall = c->d_twall;
     }
@@ -965,6 +982,8 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
     // the column kernels' classes and list are lwacm_init's, the mask the caller's
     if (column && c->p.mask && nsteps > 0 &&
         lwacm::launch_mask_check(c->p, c->d_cls, c->d_scan + 2, c->stream) != hipSuccess)
+        return LWACM_EDEVICE;
+    if (march && c->p.mask && !lwacm::march_aligned(c->p) && nsteps > 0 && !follow_mask(c))
         return LWACM_EDEVICE;
     // Steps whose partials are stored but not yet added up (oldest first): the
     // next launch's block 0 adds them, or the final passes after the loop.

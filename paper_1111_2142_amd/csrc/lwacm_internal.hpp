@@ -169,6 +169,17 @@ int march_plan(const ProblemArgs &p, int ncu, const unsigned *counts, int4 *plan
 constexpr unsigned kMovingWallFlag = 1u << 31;  // in bits: node sees a moving wall
 hipError_t launch_classify(const ProblemArgs &p, uint8_t *cls, unsigned *bits, float4 *wallg,
                            hipStream_t s);
+// The tables of the fused temperature step with walls for the mask as it is
+// (FP32 states): bit sets, moving-wall sums, fixed-temperature wall links; other
+// gets the state of the solid nodes, which the step does not write.
+struct FollowMask {
+    uint2 *T_wall;
+    const float4 *state;
+    float4 *other;
+    float wall_T[16];  // by mask id (NaN: adiabatic), as ThermalArgs has them
+};
+hipError_t launch_follow_mask(const ProblemArgs &p, unsigned *bits, float4 *wallg,
+                              const FollowMask &f, hipStream_t s);
 // D3Q19 reverse step as a z-marching tile kernel (any mask, with or without
 // force, nz >= 8); mu_in / mu_out node-interleaved, or field-major output when
 // final_t0.  Masked problems need the bit sets (and wallg for moving walls)

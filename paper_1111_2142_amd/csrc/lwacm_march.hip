@@ -37,6 +37,7 @@
 #include <algorithm>
 
 #include "lwacm_march_common.hpp"
+#include "lwacm_thermal.hpp"
 
 namespace lwacm {
 
@@ -589,8 +590,12 @@ int rolled_nzc(const ProblemArgs &p)
 // flag bit is set and wallg holds sum_i 36 w_i (v_i . u_w(x - v_i)) times
 // (1, v_i) over its bounce-back links: the moving-wall term per unit of
 // (1 - a) 6 rho0, which depends on the geometry only.
+// FOLLOW (launch_follow_mask): all but the classes, for the mask as it is: also
+// the fixed-temperature wall links (the sums of k_thermal_wall_table), and the
+// solid nodes' state in the buffer that the next step writes.
+template <bool FOLLOW>
 __global__ __launch_bounds__(256) void k_classify(ProblemArgs p, uint8_t *cls, unsigned *bits,
-                                                  float4 *wallg)
+                                                  float4 *wallg, FollowMask f)
 {
     for (unsigned idx = blockIdx.x * blockDim.x + threadIdx.x; idx < (unsigned)p.n;  // n < 2^28
          idx += gridDim.x * blockDim.x) {
@@ -608,8 +613,12 @@ __global__ __launch_bounds__(256) void k_classify(ProblemArgs p, uint8_t *cls, u
             ms[i] = p.mask[((unsigned)uz * p.ny + uy) * p.nx + ux];
         }
         if (ms[0] != 0) {
-            cls[idx] = 2;
+            if (!FOLLOW) cls[idx] = 2;
             bits[idx] = 1u;  // bit 0 (the rest link, never a bounce-back link): solid
+            if (FOLLOW) {
+                f.T_wall[idx] = make_uint2(0u, 0u);
+                f.other[idx] = f.state[idx];
+            }
             continue;
         }
         unsigned bb = 0u;
@@ -621,7 +630,9 @@ __global__ __launch_bounds__(256) void k_classify(ProblemArgs p, uint8_t *cls, u
             const int m = ms[i];
             if (m != 0) {
                 bb |= 1u << i;
-                const float vu = cx * p.wall_u[m][0] + cy * p.wall_u[m][1] + cz * p.wall_u[m][2];
+                const float vu = m < kMaxWallIds ? cx * p.wall_u[m][0] + cy * p.wall_u[m][1] +
+                                                       cz * p.wall_u[m][2]
+                                                 : 0.0f;
                 if (vu != 0.0f) {
                     moving = true;
                     const float s = Lattice<19>::w36(i) * vu;
@@ -636,7 +647,23 @@ __global__ __launch_bounds__(256) void k_classify(ProblemArgs p, uint8_t *cls, u
             bb |= kMovingWallFlag;
             wallg[idx] = make_float4(g[0], g[1], g[2], g[3]);
         }
-        cls[idx] = bb ? 1 : 0;
+        if (FOLLOW) {
+            unsigned fb = 0u;
+            float tw = 0.0f;
+#pragma unroll
+            for (int i = 1; i < 19; ++i) {
+                const int m = ms[i];
+                if (m == 0) continue;
+                const float Tw = m < kMaxThermalWallIds ? f.wall_T[m] : __builtin_nanf("");
+                if (Tw == Tw) {
+                    fb |= 1u << i;
+                    tw = fmaf(Lattice<19>::w36(i), Tw, tw);
+                }
+            }
+            f.T_wall[idx] = make_uint2(fb, __builtin_bit_cast(unsigned, tw));
+        } else {
+            cls[idx] = bb ? 1 : 0;
+        }
         bits[idx] = bb;
     }
 }
@@ -935,7 +962,18 @@ hipError_t launch_classify(const ProblemArgs &p, uint8_t *cls, unsigned *bits, f
 {
     long long nb = (p.n + 255) / 256;
     if (nb > 4096) nb = 4096;
-    k_classify<<<(unsigned)nb, 256, 0, s>>>(p, cls, bits, wallg);
+    k_classify<false><<<(unsigned)nb, 256, 0, s>>>(p, cls, bits, wallg, FollowMask{});
+    return hipGetLastError();
+}
+
+hipError_t launch_follow_mask(const ProblemArgs &p, unsigned *bits, float4 *wallg,
+                              const FollowMask &f, hipStream_t s)
+{
+    if (!p.mask || !bits || !f.T_wall || !f.state || !f.other || p.n >= (1LL << 28))
+        return hipErrorInvalidValue;
+    long long nb = (p.n + 255) / 256;
+    if (nb > 4096) nb = 4096;
+    k_classify<true><<<(unsigned)nb, 256, 0, s>>>(p, nullptr, bits, wallg, f);
     return hipGetLastError();
 }
 
