@@ -486,10 +486,9 @@ int lwacm_adjoint_step2(lwacm_ctx *c, const void *d_state_t, const void *d_state
  *   steps per launch, whose per-step sums run over tiles of 8 to 32 nodes instead
  *   (equal to FP64 rounding).
  *   The first call for a longer sweep allocates the library's per-step
- *   partials (nsteps x blocks doubles).  D3Q19 sweeps without walls may use
- *   the state buffer that does not hold the current state as scratch.
- *   Unsupported cases as
- *   lwacm_adjoint_step.  Asynchronous.
+ *   partials (nsteps x blocks doubles) and, on D3Q19 grids without walls that
+ *   leave compute units idle, 16 bytes per node for the terms of dL/domega.
+ *   Unsupported cases as lwacm_adjoint_step.  Asynchronous.
  */
 int lwacm_forward_states(lwacm_ctx *c, const void *d_state0, long long t0, int nsteps,
                          void *d_states);

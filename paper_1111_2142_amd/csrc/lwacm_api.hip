@@ -57,8 +57,8 @@ struct lwacm_ctx {
     int tcur;
     lwacm::ThermalArgs targs;
     double *d_force;  // wall-force partials (allocated on first use)
-    // reverse sweeps (lwacm_adjoint_sweep): the steps' block partials and
-    // totals, allocated on first use and grown as needed (doubles)
+    // reverse sweeps (lwacm_adjoint_sweep): the steps' block partials and totals
+    // and the factors of dL/da, allocated on first use and grown as needed (doubles)
     double *d_sweep;
     size_t sweep_cap;
     double *h_force;  // pinned host memory the wall-force sum kernel writes its six results to
@@ -147,6 +147,21 @@ ReduceArgs reduce_args(lwacm_ctx *c, double *out, double *out2)
     r.accumulate = 0;
     r.out_scale = 1.0;
     return r;
+}
+
+// Room for `doubles` doubles in the sweeps' scratch (contents are not kept).
+bool sweep_scratch(lwacm_ctx *c, size_t doubles)
+{
+    if (doubles <= c->sweep_cap) return true;
+    if (c->d_sweep) (void)hipFree(c->d_sweep);
+    c->d_sweep = nullptr;
+    c->sweep_cap = 0;
+    if (hipMalloc(&c->d_sweep, doubles * sizeof(double)) != hipSuccess) {
+        (void)hipGetLastError();  // the caller may go on without
+        return false;
+    }
+    c->sweep_cap = doubles;
+    return true;
 }
 
 // Compute units of the current device.
@@ -1287,15 +1302,6 @@ int lwacm_adjoint_sweep(lwacm_ctx *c, const void *d_states, long long t0, int ns
     if (nsteps == 0) return LWACM_OK;
     const size_t sb = state_bytes(c);
     const char *st = static_cast<const char *>(d_states);
-    const size_t stride = c->n_partial_blocks;  // doubles per slice
-    const size_t need = (size_t)nsteps * (stride + 1);  // slices, then their totals
-    if (need > c->sweep_cap) {
-        if (c->d_sweep) (void)hipFree(c->d_sweep);
-        c->d_sweep = nullptr;
-        c->sweep_cap = 0;
-        if (hipMalloc(&c->d_sweep, need * sizeof(double)) != hipSuccess) return LWACM_ENOMEM;
-        c->sweep_cap = need;
-    }
     const bool tile = use_adj_march(c);
     const bool two_ok = tile && c->variant != LWACM_KERNEL_MARCH &&
                         lwacm::adj_march2_supported(c->p);
@@ -1312,26 +1318,22 @@ int lwacm_adjoint_sweep(lwacm_ctx *c, const void *d_states, long long t0, int ns
                                   : lwacm::generic_grid(c->p.n);
     // Tile kernels whose chunks leave compute units idle (96^3: 36 workgroups):
     // chunks that fill the chip instead, the factors of the nodes' dL/da written
-    // out, and the same dL/domega sums by launch_adj_dadomega after each launch.
-    // The factors (8 bytes a node and step) go to the context's other state
-    // buffer, which without walls holds nothing until the next forward step:
-    // room for the two steps of a launch, or with FP16 storage for one, and then
-    // the steps run one per launch.  (Arguments of the call that lie in that
-    // buffer keep the deep chunks.)  A reverse step of a sweep, sums included:
-    // 96^3 62 -> 18 us, 128^3 119 -> 30, 192^3 124 -> 90.
+    // out (8 bytes a node and step, for the two steps of a launch), and the same
+    // dL/domega sums by launch_adj_dadomega after each launch.  A reverse step of a
+    // sweep, sums included: 96^3 62 -> 18 us, 128^3 119 -> 30, 192^3 124 -> 90.
     const unsigned nb_deep = two_ok ? nb2 : nb1;
-    const char *other = static_cast<const char *>(c->buf[c->cur ^ 1]);
-    const size_t mu_bytes = (size_t)(c->p.D + 1) * (size_t)c->p.n * sizeof(float);
-    auto in_other = [&](const void *q, size_t bytes) {
-        const char *a = static_cast<const char *>(q);
-        return a < other + sb && other < a + bytes;
-    };
-    const bool split = tile && !c->p.mask && nb_deep < (unsigned)c->ncu &&
-                       lwacm::adj_blocks(c->p, lwacm::adj_split_depth(c->p)) > nb_deep &&
-                       !in_other(st, (size_t)nsteps * sb) && !in_other(d_mu, mu_bytes) &&
-                       !in_other(d_mu_tmp, mu_bytes) && !in_other(d_dL_domega, sizeof(double));
-    float2 *const x = split ? static_cast<float2 *>(c->buf[c->cur ^ 1]) : nullptr;
-    const bool pair_launch = two_ok && (!split || c->storage == LWACM_FP32);
+    bool split = tile && !c->p.mask && nb_deep < (unsigned)c->ncu &&
+                 lwacm::adj_blocks(c->p, lwacm::adj_split_depth(c->p)) > nb_deep;
+    // scratch: a slice of block partials per step, the steps' totals, the factors
+    const size_t stride = c->n_partial_blocks;  // doubles per slice
+    const size_t sums = (size_t)nsteps * (stride + 1);
+    const size_t factors = 2 * (size_t)c->p.n;
+    if (!sweep_scratch(c, sums + (split ? factors : 0))) {
+        // no room for the factors: the deep chunks
+        if (!split || !sweep_scratch(c, sums)) return LWACM_ENOMEM;
+        split = false;
+    }
+    float2 *const x = split ? reinterpret_cast<float2 *>(c->d_sweep + sums) : nullptr;
     // two_ok: steps are summed in pairs' chunks, an odd last one by itself
     const unsigned pair_slices = two_ok ? (unsigned)nsteps & ~1u : 0u;
     float *mu_in = d_mu, *mu_out = d_mu_tmp;
@@ -1347,7 +1349,7 @@ int lwacm_adjoint_sweep(lwacm_ctx *c, const void *d_states, long long t0, int ns
             e = lwacm::launch_adj_d2q9_multi(c->p, reinterpret_cast<const float *>(st), sb / 4,
                                              (int)(t - t0), k, t - k + 1 == 0, mu_in, mu_out,
                                              c->d_sweep, stride, slice, c->stream);
-        } else if (pair_launch && t - 1 >= t0) {
+        } else if (two_ok && t - 1 >= t0) {
             k = 2;
             r.partials_b = r.partials + stride;
             e = lwacm::launch_adj_march2(c->p, c->storage, st + (size_t)(t - t0) * sb,
