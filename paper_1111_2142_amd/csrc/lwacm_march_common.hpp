@@ -262,7 +262,7 @@ __device__ __forceinline__ float select_link(unsigned bits, int i, float lo)
 // anything: a link term of zero fields is zero, while zeroed coefficients let a
 // NaN or infinity through as 0 * NaN.  Cleared by a mask, as in select_link: out
 // of selects the compiler makes a branch (the step with a temperature and walls
-// grew by 7 % in instructions, 22.9 -> 23.5 us a step at 160 x 96 x 100; by the mask 23.0).
+// grew by 7 % in instructions).
 template <class... F>
 __device__ __forceinline__ void zero_if_solid(unsigned b, F &...v)
 {
@@ -620,7 +620,7 @@ __device__ __forceinline__ void push_split_halo(float rho, float ux, float uy, f
 // problem with a temperature does not use.  Opposite links share the even
 // part, as in push_column.
 //
-// Walls (MASK): a solid node pushes nothing (zero fields, as in push_column) and
+// Walls (MASK): a solid node pushes nothing (u is zero, as in push_column) and
 // keeps its T.  Where the
 // upstream node x - v_i of a fluid node is solid (bit i of its link set), the
 // node's own term for the opposite link comes back along i: with its sign kept
@@ -631,12 +631,14 @@ __device__ __forceinline__ void push_split_halo(float rho, float ux, float uy, f
 // flow's bounce-back.
 template <bool MASK>
 __device__ __forceinline__ void push_temp_column(float T, float ux, float uy, float uz, float h,
-                                                 Acc &A1, Acc &A0, Acc &Am, unsigned bits = 0u,
-                                                 uint2 tw = {0u, 0u})
+                                                 Acc &A1, Acc &A0, Acc &Am, int cls = 0,
+                                                 unsigned bits = 0u, uint2 tw = {0u, 0u})
 {
     const float usq = fmaf(ux, ux, fmaf(uy, uy, uz * uz));
-    const float AT = h * fmaf(-1.5f, usq, T);
-    const float H = 4.5f * h, T3 = 3.0f * T;
+    float AT = h * fmaf(-1.5f, usq, T);
+    float T3 = 3.0f * T;
+    const float H = 4.5f * h;
+    if (MASK && cls >= 2) AT = T3 = 0.0f;  // solid: push nothing (its u is zero)
     auto pair = [&](float c, float &lp, float &lm) {
         const float m = fmaf(H * c, c, AT);
         lp = fmaf(T3, c, m);
@@ -669,6 +671,7 @@ __device__ __forceinline__ void push_temp_column(float T, float ux, float uy, fl
     A0.qse = Tpm0;
     A0.qsw = Tmm0;
     A0.qd = fmaf(12.0f, AT, A0.qd);
+    A0.tx = T;
     if (MASK && __builtin_amdgcn_ballot_w64(bits > 1u) != 0ull) {
         // returned terms: all wall links, and again (twice, negated) the
         // fixed-temperature ones
