@@ -290,7 +290,11 @@ bool adj_march_supported(const ProblemArgs &p)
 // grids that it leaves half empty go through adj_split_depth.
 int adj_depth(const ProblemArgs &p) { return p.nz < 64 ? p.nz : 64; }
 
-int adj_split_depth(const ProblemArgs &p) { return p.march_nzc < p.nz ? p.march_nzc : p.nz; }
+int adj_split_depth(const ProblemArgs &p)
+{
+    const int c = p.march_deep > 0 ? p.march_deep : p.march_nzc;
+    return c < p.nz ? c : p.nz;
+}
 
 unsigned adj_blocks(const ProblemArgs &p, int nzc)
 {

@@ -23,6 +23,7 @@ struct lwacm_ctx {
     int storage;
     int variant;  // requested LWACM_KERNEL_*
     int ncu;      // compute units of the device
+    int deep;     // p.march_deep without a temperature
     bool force;
     double omega;
     double omega_p;  // relaxation of the density update (== omega: single relaxation)
@@ -162,6 +163,19 @@ bool sweep_scratch(lwacm_ctx *c, size_t doubles)
     }
     c->sweep_cap = doubles;
     return true;
+}
+
+// The forward tile kernels' chunk depths: without splitting the FP32 sums, and
+// with that (*deep, 0: not deeper).  Ragged sides add in FP64: any depth.
+void set_march_depths(int *deep, ProblemArgs &p, int ncu)
+{
+    constexpr int any = 0x7fffffff;
+    const bool aligned = lwacm::march_aligned(p);
+    p.march_sum = lwacm::march_sum_planes(p, ncu);
+    const int best = lwacm::march_choose_depth(p, ncu, any);
+    const int shallow = p.nz >= 8 ? lwacm::march_choose_depth(p, ncu, p.march_sum) : best;
+    p.march_nzc = aligned ? shallow : best;
+    *deep = aligned && best > shallow && p.nz >= 8 ? best : 0;
 }
 
 // Compute units of the current device.
@@ -604,7 +618,12 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
         nb = tb > nb ? tb : nb;
     }
     if (lwacm::march_supported(unforced)) {
-        p.march_nzc = unforced.march_nzc = lwacm::march_choose_depth(p, c->ncu);
+        set_march_depths(&c->deep, p, c->ncu);
+        unforced.march_nzc = p.march_nzc;
+        unforced.march_sum = p.march_sum;
+        const size_t db = lwacm::march_num_blocks(unforced);  // without march_deep: more of them
+        p.march_deep = unforced.march_deep = c->deep;
+        if (db > nb) nb = db;
         const size_t sb = lwacm::march_aligned(p) ? lwacm::march_scratch_blocks(p, c->ncu) : 0;
         if (sb > nb) nb = sb;
     }
@@ -733,16 +752,19 @@ int lwacm_set_march_chunk(lwacm_ctx *c, int planes)
 {
     if (!c || (planes != 32 && planes != 64 && planes != 128)) return LWACM_EINVAL;
     if (!lwacm::march_supported(c->p) || !lwacm::march_aligned(c->p)) return LWACM_EUNSUPPORTED;
-    const int keep = c->p.march_nzc;
+    const int keep = c->p.march_nzc, deep = c->p.march_deep;
     const int4 *plan = c->p.march_plan;
     c->p.march_plan = nullptr;
     c->p.march_nzc = planes;
+    c->p.march_deep = 0;
     if (lwacm::march_num_blocks(c->p) > c->n_partial_blocks ||
         lwacm::march2_num_blocks(c->p) > c->n_partial_blocks) {  // reduction scratch too small
         c->p.march_nzc = keep;
+        c->p.march_deep = deep;
         c->p.march_plan = plan;
         return LWACM_EUNSUPPORTED;
     }
+    c->deep = 0;
     return LWACM_OK;
 }
 
@@ -800,6 +822,7 @@ int lwacm_set_thermal(lwacm_ctx *c, double omega_t, float *d_T_a, float *d_T_b,
     if (!c) return LWACM_EINVAL;
     if (!d_T_a && !d_T_b) {
         c->thermal = false;
+        c->p.march_deep = c->deep;
         return LWACM_OK;
     }
     if (!d_T_a || !d_T_b || d_T_a == d_T_b || !(omega_t > 0.0 && omega_t < 2.0))
@@ -839,6 +862,7 @@ int lwacm_set_thermal(lwacm_ctx *c, double omega_t, float *d_T_a, float *d_T_b,
     c->T_buf[1] = d_T_b;
     c->tcur = 0;
     c->thermal = true;
+    c->p.march_deep = 0;  // its kernels have no split sums
     return omega_t < 1.0 ? LWACM_WOMEGA : LWACM_OK;
 }
 
@@ -1434,7 +1458,7 @@ int lwacm_step_static(int lattice, int nx, int ny, int nz, double omega, float *
     size_t nb = lwacm::generic_grid(p.n);
     const int ncu = device_cus();
     if (lwacm::march_supported(p) && lwacm::march_aligned(p)) {
-        p.march_nzc = lwacm::march_choose_depth(p, ncu);
+        set_march_depths(&p.march_deep, p, ncu);
         const size_t sb = lwacm::march_scratch_blocks(p, ncu);
         if (sb > nb) nb = sb;
         const size_t mb = lwacm::march_num_blocks(p);

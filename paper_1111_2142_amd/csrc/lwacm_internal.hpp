@@ -46,6 +46,8 @@ struct ProblemArgs {
     const float4 *corr;
     int ncu;                 // compute units of the device (0: not asked)
     int march_nzc;           // planes per workgroup of the forward tile kernels (0: unused)
+    int march_sum;           // planes a thread of theirs adds up in FP32 at most
+    int march_deep;          // planes per workgroup where the sums split (0: march_nzc; march_deep())
     // with walls: the workgroups of the forward tile kernels one by one (null:
     // march_nzc planes each): {xs, ys, zs, depth}, the depths of one residue
     // modulo 3 (march_plan)
@@ -148,7 +150,10 @@ hipError_t launch_mask_scan(const ProblemArgs &p, unsigned *d_out2, hipStream_t 
 // n unsigned).  Returns hipErrorNotSupported if the problem does not fit.
 bool march_supported(const ProblemArgs &p);
 bool march_aligned(const ProblemArgs &p);  // nx and ny are multiples of the 32 x 16 tile
-int march_choose_depth(const ProblemArgs &p, int ncu);  // chunk depth for a device of ncu CUs
+// chunk depth for a device of ncu CUs, at most `most` planes
+int march_choose_depth(const ProblemArgs &p, int ncu, int most);
+int march_sum_planes(const ProblemArgs &p, int ncu);  // p.march_sum
+bool march_deep(const ProblemArgs &p);
 // Blocks a context's reduction scratch holds at least, whatever depth is
 // chosen: those of the best of the depths a caller may set (32, 64, 128).
 size_t march_scratch_blocks(const ProblemArgs &p, int ncu);

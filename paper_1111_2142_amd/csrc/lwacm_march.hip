@@ -285,11 +285,13 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march(ProblemArgs p, const T *
 // state, pushes the temperature terms through the omega_p arrays and writes
 // the new T (p.T_out): 4 + 4 bytes more per node instead of a pass of its own
 // (with walls 8 more: the node's fixed-temperature wall links and their sum).
-// RAGGED: sides that are no multiples of the tile (with a temperature only).  A
-// thread adds its planes' mass and energy in FP32, here node by node in FP64: the
-// gather kernels, which ran these grids before, add so.  (On every grid that
-// would cost a step with a temperature 20.3 -> 21.1 us at 128^3.)
-template <class T, int TAIL, bool SR, bool MASK, bool SPLIT, int FRC, bool CORR, bool THERM, bool RAGGED>
+// SUMS: how a thread adds up its planes' mass and energy.  0: in FP32, chunks of at
+// most p.march_sum planes; 2: in FP32, on to FP64 after every p.march_sum planes
+// (deeper chunks; a scalar comparison a plane); 1: in FP64 node by node, on sides
+// that are no multiples of the tile (with a temperature only): the gather kernels,
+// which ran these grids before, add so.  (On every grid that would cost a step
+// with a temperature 20.3 -> 21.1 us at 128^3.)
+template <class T, int TAIL, bool SR, bool MASK, bool SPLIT, int FRC, bool CORR, bool THERM, int SUMS>
 __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, int depth,
                                                                const T *__restrict__ src,
                                                                T *__restrict__ dst,
@@ -425,6 +427,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
 
     float mass = 0.0f, energy = 0.0f;
     double mass64 = 0.0, energy64 = 0.0;
+    int due = p.march_sum;  // planes added before the FP32 sums move on (SUMS 2)
     const int N = nzc + 2;  // planes z0 - 1 .. z1
     auto value = [&](const Ring<T> &rg, float &dr, float &ux, float &uy, float &uz) {
         dr = BufIO<T>::value(rg.v, 0, p.ld_scale[0]);
@@ -530,13 +533,19 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
                 store_data_guard();
             }
             const bool count = tz >= zs && !solid;
-            if (RAGGED) {
+            if (SUMS == 1) {
                 const float e = fmaf(o.vz, o.vz, fmaf(o.vy, o.vy, o.vx * o.vx));
                 mass64 += count ? (double)o.D : 0.0;
                 energy64 += count ? (double)e : 0.0;
             } else {
                 mass += count ? o.D : 0.0f;
                 energy = count ? fmaf(o.vx, o.vx, fmaf(o.vy, o.vy, fmaf(o.vz, o.vz, energy))) : energy;
+            }
+            if (SUMS == 2 && tz - z0 + 1 == due) {
+                mass64 += (double)mass;
+                energy64 += (double)energy;
+                mass = energy = 0.0f;
+                due += p.march_sum;
             }
         });
     } else {
@@ -572,10 +581,11 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
         });
     }
 
+    // columns shared with the tile before (a ragged side) are its to count
+    if (gx < ti.xs || gy < ti.ys) mass = energy = 0.0f;
+    if (SUMS == 1 && (gx < ti.xs || gy < ti.ys)) mass64 = energy64 = 0.0;
     mass64 += (double)mass;
     energy64 += (double)energy;
-    // columns shared with the tile before (a ragged side) are its to count
-    if (RAGGED && (gx < ti.xs || gy < ti.ys)) mass64 = energy64 = 0.0;
     const double uu = UNITS ? (double)us * (double)us : 1.0;  // the energy is in units of us^2
     double v[2] = {mass64, 0.5 * uu * energy64};
     store_block_partials<2>(v, r.partials, blockIdx.x);
@@ -589,6 +599,7 @@ int rolled_nzc(const ProblemArgs &p)
 {
     if (p.nz < 8) return 0;
     if (p.march_plan) return p.march_plan_depth;
+    if (march_deep(p)) return p.march_deep;
     return p.march_nzc < p.nz ? p.march_nzc : p.nz;
 }
 
@@ -700,14 +711,14 @@ __global__ __launch_bounds__(NINT) void k_tile_walls(ProblemArgs p, const unsign
 
 // c: planes per workgroup; its loop of c + 2 iterations has a tail of 3 + (c + 2) % 3
 template <class T, bool SR, bool MASK, bool SPLIT = false, int FRC = 0, bool CORR = false,
-          bool THERM = false, bool RAGGED = false>
+          bool THERM = false, int SUMS = 0>
 void launch_rolled(int c, unsigned nb, hipStream_t s, const ProblemArgs &p, const T *a, T *b,
                    const unsigned *bits, const float4 *wallg, const ReduceArgs &r)
 {
     switch ((c + 2) % 3) {
-    case 0: k_fwd_march_rolled<T, 3, SR, MASK, SPLIT, FRC, CORR, THERM, RAGGED><<<nb, NTHREADS, 0, s>>>(p, c, a, b, bits, wallg, r); break;
-    case 1: k_fwd_march_rolled<T, 4, SR, MASK, SPLIT, FRC, CORR, THERM, RAGGED><<<nb, NTHREADS, 0, s>>>(p, c, a, b, bits, wallg, r); break;
-    default: k_fwd_march_rolled<T, 5, SR, MASK, SPLIT, FRC, CORR, THERM, RAGGED><<<nb, NTHREADS, 0, s>>>(p, c, a, b, bits, wallg, r); break;
+    case 0: k_fwd_march_rolled<T, 3, SR, MASK, SPLIT, FRC, CORR, THERM, SUMS><<<nb, NTHREADS, 0, s>>>(p, c, a, b, bits, wallg, r); break;
+    case 1: k_fwd_march_rolled<T, 4, SR, MASK, SPLIT, FRC, CORR, THERM, SUMS><<<nb, NTHREADS, 0, s>>>(p, c, a, b, bits, wallg, r); break;
+    default: k_fwd_march_rolled<T, 5, SR, MASK, SPLIT, FRC, CORR, THERM, SUMS><<<nb, NTHREADS, 0, s>>>(p, c, a, b, bits, wallg, r); break;
     }
 }
 
@@ -745,6 +756,7 @@ hipError_t dispatch(const ProblemArgs &p, const void *src, void *dst, const uint
     const T *a = static_cast<const T *>(src);
     T *b = static_cast<T *>(dst);
     const int c = rolled_nzc(p);
+    if (c != 0 && c < 8) return hipErrorInvalidValue;  // the plane loop's least
     const bool sr = std::is_same<T, __half>::value && p.fp16_sr;
     if (p.T_in) {  // with the temperature step (march_thermal_supported)
         if constexpr (std::is_same<T, __half>::value) {
@@ -756,8 +768,8 @@ hipError_t dispatch(const ProblemArgs &p, const void *src, void *dst, const uint
         }
         if constexpr (std::is_same<T, float>::value) {
             if (!march_aligned(p)) {
-                if (p.mask) launch_rolled<T, false, true, false, 0, false, true, true>(c, nb, s, p, a, b, bits, wallg, r);
-                else launch_rolled<T, false, false, false, 0, false, true, true>(c, nb, s, p, a, b, bits, wallg, r);
+                if (p.mask) launch_rolled<T, false, true, false, 0, false, true, 1>(c, nb, s, p, a, b, bits, wallg, r);
+                else launch_rolled<T, false, false, false, 0, false, true, 1>(c, nb, s, p, a, b, bits, wallg, r);
                 return hipGetLastError();
             }
         }
@@ -780,8 +792,13 @@ hipError_t dispatch(const ProblemArgs &p, const void *src, void *dst, const uint
         if (sr) launch_rolled<T, true, false, true>(c, nb, s, p, a, b, bits, wallg, r);
         else launch_rolled<T, false, false, true>(c, nb, s, p, a, b, bits, wallg, r);
     } else {
-        if (sr) launch_rolled<T, true, false>(c, nb, s, p, a, b, bits, wallg, r);
-        else launch_rolled<T, false, false>(c, nb, s, p, a, b, bits, wallg, r);
+        if (march_deep(p)) {
+            if (sr) launch_rolled<T, true, false, false, 0, false, false, 2>(c, nb, s, p, a, b, bits, wallg, r);
+            else launch_rolled<T, false, false, false, 0, false, false, 2>(c, nb, s, p, a, b, bits, wallg, r);
+        } else {
+            if (sr) launch_rolled<T, true, false>(c, nb, s, p, a, b, bits, wallg, r);
+            else launch_rolled<T, false, false>(c, nb, s, p, a, b, bits, wallg, r);
+        }
     }
     return hipGetLastError();
 }
@@ -789,6 +806,13 @@ hipError_t dispatch(const ProblemArgs &p, const void *src, void *dst, const uint
 }  // namespace
 
 bool march_aligned(const ProblemArgs &p) { return p.nx % TX == 0 && p.ny % TY == 0; }
+
+// Chunks deeper than p.march_sum planes (p.march_deep, 0: none): plain steps, whose
+// kernels have the instances that split the sums.
+bool march_deep(const ProblemArgs &p)
+{
+    return p.march_deep > 0 && !p.mask && !p.has_force && !p.split;
+}
 
 bool march_supported(const ProblemArgs &p)
 {
@@ -810,6 +834,31 @@ static long long march_blocks_for(const ProblemArgs &p, int nzc)
     return tiles * ((p.nz + nzc - 1) / nzc);
 }
 
+// The best of the depths that a caller may set.
+static int settable_depth(const ProblemArgs &p, int ncu)
+{
+    if (ncu < 1) ncu = 1;
+    int best = 0;
+    long long best_cost = -1;
+    for (int c : {32, 64, 128}) {
+        const long long cost = ((march_blocks_for(p, c) + ncu - 1) / ncu) * (c + 2);
+        if (best_cost < 0 || cost <= best_cost) {
+            best = c;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// Those were the only depths before march_choose_depth took any number, halved
+// while deeper than nz, and a thread added up a chunk in FP32: no sum is longer now.
+int march_sum_planes(const ProblemArgs &p, int ncu)
+{
+    int c = settable_depth(p, ncu);
+    while (c > 8 && c > p.nz) c /= 2;
+    return c;
+}
+
 // Chunk depth of the forward and the reverse tile kernels.  The workgroups a
 // CU receives run one after the other or share it, and each spends, besides
 // its planes, about ten planes' time on the halo planes and on filling and
@@ -817,25 +866,28 @@ static long long march_blocks_for(const ProblemArgs &p, int nzc)
 // 35.2 and 27.8 us, 0.46 us a plane and 5.7 us besides), so the step time
 // follows ceil(blocks / CUs) * (depth + 10).  The chunks are of equal depth (nz
 // over their number), at least 8 planes; ties go to the deeper chunk (fewer
-// halo planes).  Against the best of 32, 64 and 128 planes, the depths used
-// before: 128^3 13.4 us a step (16 planes) against 20.0 (32), 160 x 96 x 100
+// halo planes), at most `most` (p.march_sum planes where the kernel's sums don't
+// split: 256 x 256 x 192 takes 96 planes and sums of 32, 59.3 us a step against
+// 61.8 with chunks of 32; 256 x 160 x 200 67 planes, 38.0 against 55.6).  Against
+// the best of 32, 64 and 128 planes, the depths used before: 128^3 13.4 us a step (16 planes) against 20.0 (32), 160 x 96 x 100
 // with walls and a temperature 24.8 (13) against 46.7 (32), two reverse steps
 // at 96^3 29.6 (8) against 124.3 (64); 192^3 and 256^3 keep 64 and 128 planes.
-int march_choose_depth(const ProblemArgs &p, int ncu)
+int march_choose_depth(const ProblemArgs &p, int ncu, int most)
 {
     constexpr int extra = 10;
     if (p.nz < 8) return 32;  // the unrolled kernel's
     if (ncu < 1) ncu = 1;
-    int best = p.nz;
-    long long best_cost = -1;
-    for (int m = 1;; ++m) {
+    auto cost_of = [&](int c) {
+        return ((march_blocks_for(p, c) + ncu - 1) / ncu) * (long long)(c + extra);
+    };
+    int best = p.nz < most ? p.nz : most;  // most >= 8
+    long long best_cost = cost_of(best);
+    for (int m = (p.nz + best - 1) / best;; ++m) {
         const int c = (p.nz + m - 1) / m;
-        const long long nb = march_blocks_for(p, c);
-        if (m > 1 && (c < 8 || nb > 8LL * ncu)) break;
-        const long long cost = ((nb + ncu - 1) / ncu) * (c + extra);
-        if (best_cost < 0 || cost < best_cost) {
+        if (c < 8 || (c < best && march_blocks_for(p, c) > 8LL * ncu)) break;
+        if (cost_of(c) < best_cost) {
             best = c;
-            best_cost = cost;
+            best_cost = cost_of(c);
         }
     }
     return best;
@@ -893,8 +945,8 @@ int march_plan(const ProblemArgs &p, int ncu, const unsigned *counts, int4 *plan
     auto chunks = [&](int c) { return (p.nz + c - 1) / c; };
     for (int residue = 0; residue < 3; ++residue) {
         auto valid = [&](int c) { return c >= 8 && c % 3 == residue; };
-        int deepest = p.nz;
-        while (!valid(deepest)) --deepest;  // nz >= 16
+        int deepest = std::min(p.nz, p.march_sum);
+        while (!valid(deepest)) --deepest;  // nz and march_sum >= 16
         for (int t = 0; t < tiles; ++t) tile[t].depth = deepest;
         long long nb = (long long)tiles * chunks(deepest);
         if (nb > ncu) continue;
@@ -954,16 +1006,7 @@ hipError_t launch_tile_walls(const ProblemArgs &p, const unsigned *bits, unsigne
 
 size_t march_scratch_blocks(const ProblemArgs &p, int ncu)
 {
-    long long best = 0, best_cost = -1;
-    for (int c : {32, 64, 128}) {
-        const long long nb = march_blocks_for(p, c);
-        const long long cost = ((nb + ncu - 1) / ncu) * (c + 2);
-        if (best_cost < 0 || cost <= best_cost) {
-            best = nb;
-            best_cost = cost;
-        }
-    }
-    return (size_t)best;
+    return (size_t)march_blocks_for(p, settable_depth(p, ncu));
 }
 
 unsigned march_num_blocks(const ProblemArgs &p)

@@ -86,7 +86,9 @@ __device__ __forceinline__ void finish_previous_sums2(const ReduceArgs &r)
     }
 }
 
-template <int TAIL, bool MASK>
+// DEEP: chunks deeper than p.march_sum planes, sums moved on to FP64 after as many
+// (the same planes as in the single-step kernel's).
+template <int TAIL, bool MASK, bool DEEP>
 __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int depth,
                                                          const float *__restrict__ src,
                                                          float *__restrict__ dst,
@@ -165,6 +167,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
     for (int j = 0; j < RING; ++j) issue(j, ring[j], z0 - 2 + j);
 
     float m1 = 0.0f, e1 = 0.0f, m2 = 0.0f, e2 = 0.0f;
+    double sums[4] = {0.0, 0.0, 0.0, 0.0};
+    int due1 = p.march_sum, due2 = p.march_sum;  // planes added before they move on (DEEP)
     const int N = nzc + 4;  // planes z0 - 2 .. z1 + 1
 
     // The three roles run separate loops (wave-uniform), with the same
@@ -220,6 +224,12 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
             const bool count = tq >= zs && tq < z1 && cls < 2;
             m1 += count ? o.D : 0.0f;
             e1 = count ? fmaf(o.vx, o.vx, fmaf(o.vy, o.vy, fmaf(o.vz, o.vz, e1))) : e1;
+            if (DEEP && tq - z0 + 1 == due1) {
+                sums[0] += (double)m1;
+                sums[1] += (double)e1;
+                m1 = e1 = 0.0f;
+                due1 += p.march_sum;
+            }
         }
         if (MASK) zero_if_solid(bits, o.D, o.vx, o.vy, o.vz);
         if (tile) {
@@ -258,6 +268,12 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
             const bool count = tz >= zs && !solid;
             m2 += count ? o2.D : 0.0f;
             e2 = count ? fmaf(o2.vx, o2.vx, fmaf(o2.vy, o2.vy, fmaf(o2.vz, o2.vz, e2))) : e2;
+            if (DEEP && tz - z0 + 1 == due2) {
+                sums[2] += (double)m2;
+                sums[3] += (double)e2;
+                m2 = e2 = 0.0f;
+                due2 += p.march_sum;
+            }
         });
     } else if (tid < HALO0) {
         plane_loop<TAIL>(N, [&](int k, auto kc) {
@@ -286,7 +302,10 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
 
     // columns shared with the tile before (a ragged side) are its to count
     if (gx < ti.xs || gy < ti.ys) m1 = e1 = m2 = e2 = 0.0f;
-    double sums[4] = {(double)m1, 0.5 * (double)e1, (double)m2, 0.5 * (double)e2};
+    sums[0] += (double)m1;
+    sums[1] = 0.5 * (sums[1] + (double)e1);
+    sums[2] += (double)m2;
+    sums[3] = 0.5 * (sums[3] + (double)e2);
     block_sum<4>(sums);
     if (tid == 0) {
         r.partials[2 * (size_t)blockIdx.x] = sums[0];
@@ -301,6 +320,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
 int march2_nzc(const ProblemArgs &p)
 {
     if (p.march_plan) return p.march_plan_depth;
+    if (march_deep(p)) return p.march_deep;
     return p.march_nzc < p.nz ? p.march_nzc : p.nz;
 }
 
@@ -320,17 +340,18 @@ unsigned march2_num_blocks(const ProblemArgs &p)
     return march_num_blocks(p);  // the same tiles and chunks
 }
 
-template <bool MASK>
+template <bool MASK, bool DEEP>
 hipError_t launch_march2_t(const ProblemArgs &p, const float *src, float *dst,
                            const unsigned *bb_bits, const float4 *wallg, const ReduceArgs &r,
                            hipStream_t s)
 {
     const unsigned nb = march2_num_blocks(p);
+    if (march2_nzc(p) < 8) return hipErrorInvalidValue;  // the plane loop's least
     const int c = march2_nzc(p);  // a loop of c + 4 iterations, its tail 3 + (c + 4) % 3
     switch ((c + 4) % 3) {
-    case 0: k_fwd_march2<3, MASK><<<nb, NTHREADS, 0, s>>>(p, c, src, dst, bb_bits, wallg, r); break;
-    case 1: k_fwd_march2<4, MASK><<<nb, NTHREADS, 0, s>>>(p, c, src, dst, bb_bits, wallg, r); break;
-    default: k_fwd_march2<5, MASK><<<nb, NTHREADS, 0, s>>>(p, c, src, dst, bb_bits, wallg, r); break;
+    case 0: k_fwd_march2<3, MASK, DEEP><<<nb, NTHREADS, 0, s>>>(p, c, src, dst, bb_bits, wallg, r); break;
+    case 1: k_fwd_march2<4, MASK, DEEP><<<nb, NTHREADS, 0, s>>>(p, c, src, dst, bb_bits, wallg, r); break;
+    default: k_fwd_march2<5, MASK, DEEP><<<nb, NTHREADS, 0, s>>>(p, c, src, dst, bb_bits, wallg, r); break;
     }
     return hipGetLastError();
 }
@@ -341,8 +362,9 @@ hipError_t launch_fwd_march2(const ProblemArgs &p, const float *src, float *dst,
 {
     if (!march2_supported(p) || !r.partials_b) return hipErrorNotSupported;
     if (p.mask && !bb_bits) return hipErrorInvalidValue;  // the link sets come from k_classify
-    return p.mask ? launch_march2_t<true>(p, src, dst, bb_bits, wallg, r, s)
-                  : launch_march2_t<false>(p, src, dst, nullptr, nullptr, r, s);
+    if (p.mask) return launch_march2_t<true, false>(p, src, dst, bb_bits, wallg, r, s);
+    return march_deep(p) ? launch_march2_t<false, true>(p, src, dst, nullptr, nullptr, r, s)
+                         : launch_march2_t<false, false>(p, src, dst, nullptr, nullptr, r, s);
 }
 
 }  // namespace lwacm
