@@ -194,20 +194,36 @@ size_t state_bytes(const lwacm_ctx *c)
     return (size_t)(c->p.D + 1) * (size_t)c->p.n * (c->storage == LWACM_FP32 ? 4 : 2);
 }
 
-// Several D2Q9 steps per launch in LDS (lwacm_d2q9_multi.hip): FP32, no
-// history (it sums only a launch's last step), variant AUTO.
-bool use_multi(const lwacm_ctx *c)
+// Blocks that the partial sums of a step's launch may have.  lwacm_step_static has
+// room for kStaticMaxBlocks, and a context takes the same kernels for a problem
+// that both take, so that mass and energy are the same sums.
+size_t most_blocks(const lwacm_ctx *c)
+{
+    const bool both = c->storage == LWACM_FP32 && !c->p.mask && !c->p.has_force && !c->p.split;
+    return both && c->n_partial_blocks > lwacm::kStaticMaxBlocks ? lwacm::kStaticMaxBlocks
+                                                                 : c->n_partial_blocks;
+}
+
+// Several D2Q9 steps per launch: FP32, no history (they sum only a launch's last
+// step), variant AUTO.
+bool several_d2q9(const lwacm_ctx *c)
 {
     return c->variant == LWACM_KERNEL_AUTO && c->storage == LWACM_FP32 && !c->thermal &&
-           !c->semi_implicit && !c->d_hist && lwacm::d2q9_multi_supported(c->p) &&
-           lwacm::d2q9_multi_num_blocks(c->p) <= c->n_partial_blocks;
+           !c->semi_implicit && !c->d_hist;
+}
+
+// In LDS (lwacm_d2q9_multi.hip).
+bool use_multi(const lwacm_ctx *c)
+{
+    return several_d2q9(c) && lwacm::d2q9_multi_supported(c->p) &&
+           lwacm::d2q9_multi_num_blocks(c->p) <= most_blocks(c);
 }
 
 // kMultiSteps of them at a time as marching strips (lwacm_d2q9_strip.hip).
 bool use_strip(const lwacm_ctx *c)
 {
-    return use_multi(c) && lwacm::d2q9_strip_supported(c->p) &&
-           lwacm::d2q9_strip_num_blocks(c->p) <= c->n_partial_blocks;
+    return several_d2q9(c) && lwacm::d2q9_strip_supported(c->p) &&
+           lwacm::d2q9_strip_num_blocks(c->p) <= most_blocks(c);
 }
 
 // The temperature step rides in the flow's tile kernel (the flow's own
@@ -244,7 +260,7 @@ bool use_column(const lwacm_ctx *c)
            lwacm::column_supported(c->p) &&
            (c->p.mask ? c->d_cls && c->wlist_built
                       : c->p.n >= (c->storage == LWACM_FP32 ? 100000 : 250000)) &&
-           lwacm::column_num_blocks(c->p, c->n_wlist) <= c->n_partial_blocks;
+           lwacm::column_num_blocks(c->p, c->n_wlist) <= most_blocks(c);
 }
 
 bool use_adj_column(const lwacm_ctx *c)
@@ -486,7 +502,7 @@ lwacm::WallLinks wall_links(const lwacm_ctx *c)
 // doubles for the mass and energy when the caller passes no d_diag.  Each
 // device holds its own copy for the life of the process; host code reaches
 // it only through the address hipGetSymbolAddress returns on that device.
-constexpr size_t kStaticMaxBlocks = 8192;
+using lwacm::kStaticMaxBlocks;
 constexpr size_t kStaticScratchDoubles = 8 * kStaticMaxBlocks + 2;
 static __device__ __align__(256) double scratch[kStaticScratchDoubles];
 
@@ -1011,7 +1027,7 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
     const bool fuse = march && use_march2(c);
     const bool column = !march && use_column(c);
     const bool multi = !march && use_multi(c);
-    const bool strip = multi && use_strip(c);
+    const bool strip = use_strip(c);
     const unsigned nb1 = march ? lwacm::march_num_blocks(c->p)
                          : column ? lwacm::column_num_blocks(c->p, c->n_wlist)
                          : multi  ? lwacm::d2q9_multi_num_blocks(c->p)
@@ -1036,9 +1052,9 @@ int lwacm_step(lwacm_ctx *c, int nsteps)
         // an odd step count starts with one single step, then pairs; the
         // multi-step D2Q9 kernels take up to kMultiSteps steps at a time
         const bool two = fuse && (nsteps - s) % 2 == 0;
-        const int kk = multi ? (nsteps - s < lwacm::kMultiSteps ? nsteps - s : lwacm::kMultiSteps)
-                             : (two ? 2 : 1);
-        const bool stripped = strip && kk == lwacm::kMultiSteps;
+        const int several = nsteps - s < lwacm::kMultiSteps ? nsteps - s : lwacm::kMultiSteps;
+        const bool stripped = strip && several == lwacm::kMultiSteps;
+        const int kk = multi || stripped ? several : (two ? 2 : 1);
         double *part = c->d_partials + 2 * set * (size_t)(launch & 1);
         ReduceArgs r = reduce_args(c, c->d_diag, hist_slot(c, c->steps + 1));
         r.partials = part;

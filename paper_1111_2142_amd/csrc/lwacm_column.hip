@@ -589,6 +589,10 @@ int column_choose_depth(const ProblemArgs &p, int ncu)
     int m = 2 * ncu / (groups > 0 ? groups : 1);
     const int most = (p.nz + 1) / 2, least = (p.nz + 31) / 32;
     m = m > most ? most : (m < least ? least : m);
+    // no more workgroups than lwacm_step_static has room for, where that can be
+    // had (67 million nodes and more: 34 planes at 407^3)
+    const long long room = groups > 0 ? (long long)kStaticMaxBlocks / groups : 0;
+    if (room >= 1 && m > room) m = (int)room;
     return (p.nz + m - 1) / m;
 }
 

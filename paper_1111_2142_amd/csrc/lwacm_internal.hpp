@@ -272,5 +272,7 @@ unsigned generic_grid(long long n);
 
 constexpr int kGenericBlock = 256;
 constexpr unsigned kGenericMaxBlocks = 4096;
+// Blocks that the fixed scratch of lwacm_step_static has room for.
+constexpr size_t kStaticMaxBlocks = 8192;
 
 }  // namespace lwacm
