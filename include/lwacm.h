@@ -136,7 +136,11 @@ size_t lwacm_state_bytes(int lattice, int nx, int ny, int nz, int storage);
  *  stream       HIP stream every call of this context is issued on.
  *
  * On success (LWACM_OK or LWACM_WOMEGA) *out holds the context; on failure
- * *out is NULL.  The call synchronises the stream once (mask validation).
+ * *out is NULL.  With a mask the call synchronises the stream: once to validate
+ * it, and up to twice for what D3Q19 kernels need of it (the nodes next to a
+ * wall on sides that are no multiples of 32 x 16, with d_q on the others too; the
+ * work at walls tile by tile on those).  Where memory does not allow the former
+ * (1 byte a node, 4 a listed node) the generic kernel runs the problem.
  */
 int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omega, int storage,
                void *d_state_a, void *d_state_b, const uint8_t *d_mask, const float *h_wall_u,
@@ -282,11 +286,14 @@ int lwacm_set_wall_velocity_links(lwacm_ctx *c, const float *d_uw);
  *             profile between two such walls exactly steady.  n_wall_T <= 16.
  *             Solid nodes keep their T.
  * T stays FP32 with either flow storage; with FP16 flow storage the
- * temperature step reads u from the FP16 state (its load scales).  With walls on a D3Q19 flow the call allocates
- * (once per context) and fills, on the context's stream, a table of 8 bytes
- * per node: each node's links into fixed-temperature walls and the sum of
- * 36 w_i T_w over them, which the flow kernel's fused temperature step
- * reads; LWACM_ENOMEM if it cannot.
+ * temperature step reads u from the FP16 state (its load scales).  With walls on
+ * a D3Q19 flow the call allocates (once per context) and fills, on the context's
+ * stream, a table of 8 bytes per node: each node's links into fixed-temperature
+ * walls and the sum of 36 w_i T_w over them, which the flow kernel's fused
+ * temperature step reads; LWACM_ENOMEM if it cannot.  On sides that are no
+ * multiples of 32 x 16 (FP32 storage) the first call allocates 12 bytes per node
+ * (28 with moving walls), synchronises the stream, and leaves the filling to
+ * lwacm_step; without that memory the generic kernels run the problem.
  * LWACM_EINVAL for bad arguments, LWACM_EUNSUPPORTED with the two-step
  * kernel requested (the two-step kernel is not used while the temperature
  * is on).  The flow's reverse steps cover the flow only;

@@ -41,8 +41,8 @@ struct lwacm_ctx {
     double *d_diag;     // [2] mass deviation, energy of the last step's output
     double *d_scratch;  // [2] for lwacm_moments
     unsigned *d_scan;   // [2] mask scan, [1] the mask was edited since (launch_mask_check)
-    uint8_t *d_cls;     // node classes for the march kernel (masked problems)
-    int4 *h_plan;       // the forward tile kernels' chunks (p.march_plan), as copied to d_cls
+    uint8_t *d_cls;     // node classes (masked D3Q19 problems)
+    int4 *h_plan;       // the forward tile kernels' chunks (p.march_plan), as copied behind a table
     unsigned *d_bits;   // solid-upstream link bits for the march kernel
     float4 *d_wallg;    // moving-wall geometry sums for the march kernel (moving walls only)
     double *d_hist;
@@ -67,6 +67,7 @@ struct lwacm_ctx {
     unsigned *d_wlist;
     unsigned n_wlist;
     bool wlist_built;
+    bool column_tables;  // d_cls and d_wlist were made together, for the column kernels
     unsigned *d_flist;  // lwacm_wall_force's own, where it has one (ensure_force_list)
     unsigned n_flist;
     bool force_listed;
@@ -148,6 +149,14 @@ ReduceArgs reduce_args(lwacm_ctx *c, double *out, double *out2)
     r.accumulate = 0;
     r.out_scale = 1.0;
     return r;
+}
+
+bool moving_walls(const lwacm_ctx *c)
+{
+    bool moving = false;
+    for (int m = 1; m < lwacm::kMaxWallIds; ++m)
+        for (int k = 0; k < 3; ++k) moving = moving || c->p.wall_u[m][k] != 0.0f;
+    return moving;
 }
 
 // Room for `doubles` doubles in the sweeps' scratch (contents are not kept).
@@ -258,7 +267,7 @@ bool use_column(const lwacm_ctx *c)
 {
     return c->variant == LWACM_KERNEL_AUTO && !c->semi_implicit && !use_march(c) &&
            lwacm::column_supported(c->p) &&
-           (c->p.mask ? c->d_cls && c->wlist_built
+           (c->p.mask ? c->column_tables
                       : c->p.n >= (c->storage == LWACM_FP32 ? 100000 : 250000)) &&
            lwacm::column_num_blocks(c->p, c->n_wlist) <= most_blocks(c);
 }
@@ -334,7 +343,7 @@ void free_scratch(lwacm_ctx *c)
     c->d_wlist = nullptr;
     c->d_corr = nullptr;
     c->p.corr = nullptr;
-    c->wlist_built = false;
+    c->wlist_built = c->column_tables = false;
     c->d_force = nullptr;
     c->p.march_plan = nullptr;
     free(c->h_plan);
@@ -347,8 +356,8 @@ void free_scratch(lwacm_ctx *c)
     c->d_scan = nullptr;
 }
 
-// The forward tile kernels' chunks (lwacm::march_plan), at d (room for ncu
-// entries): the tiles' wall counts come back (one synchronisation), the list
+// The forward tile kernels' chunks (lwacm::march_plan) from the bit sets, at d (room
+// for ncu entries): the tiles' wall counts come back (one synchronisation), the list
 // goes out from memory the context keeps.
 hipError_t make_march_plan(lwacm_ctx *c, void *d)
 {
@@ -395,6 +404,7 @@ int make_wall_list(lwacm_ctx *c, unsigned **list, unsigned *n)
         e = hipMemcpyAsync(&total, d_total, sizeof(total), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e == hipSuccess) e = hipMalloc(list, (total ? total : 1) * sizeof(unsigned));
+    const bool memory = e == hipErrorOutOfMemory;
     if (e == hipSuccess) e = lwacm::launch_wall_list_scatter(c->p, counts, *list, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     (void)hipFree(counts);
@@ -402,7 +412,7 @@ int make_wall_list(lwacm_ctx *c, unsigned **list, unsigned *n)
     if (e != hipSuccess) {
         if (*list) (void)hipFree(*list);
         *list = nullptr;
-        return LWACM_EDEVICE;
+        return memory ? LWACM_ENOMEM : LWACM_EDEVICE;
     }
     *n = (unsigned)total;
     return LWACM_OK;
@@ -424,7 +434,7 @@ int ensure_force_list(lwacm_ctx *c)
 {
     if (c->force_listed) return LWACM_OK;
     unsigned edited = 0;
-    if (c->wlist_built && !lwacm::march_aligned(c->p)) {
+    if (c->column_tables) {
         hipError_t e = lwacm::launch_mask_check(c->p, c->d_cls, c->d_scan + 2, c->stream);
         if (e == hipSuccess)
             e = hipMemcpyAsync(&edited, c->d_scan + 2, sizeof(edited), hipMemcpyDeviceToHost,
@@ -435,6 +445,70 @@ int ensure_force_list(lwacm_ctx *c)
     const int rc = edited ? make_wall_list(c, &c->d_flist, &c->n_flist) : ensure_wall_list(c);
     c->force_listed = rc == LWACM_OK;
     return rc;
+}
+
+// What the column kernels need of a mask: the node classes, the list of fluid
+// nodes next to a wall and room for its blocks' partials.  Where memory does
+// not allow them the problem runs on the one-thread-per-node kernels.
+int make_column_tables(lwacm_ctx *c)
+{
+    if (hipMalloc(&c->d_cls, (size_t)c->p.n) != hipSuccess) {
+        (void)hipGetLastError();
+        c->d_cls = nullptr;
+        return LWACM_OK;
+    }
+    if (lwacm::launch_classify(c->p, c->d_cls, nullptr, nullptr, c->stream) != hipSuccess)
+        return LWACM_EDEVICE;
+    const int rc = ensure_wall_list(c);
+    if (rc != LWACM_OK) {
+        (void)hipGetLastError();
+        return rc == LWACM_EDEVICE ? rc : LWACM_OK;
+    }
+    c->column_tables = true;
+    const size_t lb = lwacm::column_num_blocks(c->p, c->n_wlist);
+    if (lb > c->n_partial_blocks) {
+        double *grown = nullptr;
+        if (hipMalloc(&grown, 8 * lb * sizeof(double)) != hipSuccess) {
+            (void)hipGetLastError();
+            return LWACM_OK;
+        }
+        (void)hipFree(c->d_partials);
+        c->d_partials = grown;
+        c->n_partial_blocks = lb;
+    }
+    return LWACM_OK;
+}
+
+// What the tile kernel needs of a mask for a temperature on sides that are no
+// multiples of the tile, made by the first lwacm_set_thermal: tables that
+// follow_mask fills and, from the mask as it is now, the chunks of unequal depth.
+// false: no memory (the gather kernels run the problem).
+bool make_follow_tables(lwacm_ctx *c)
+{
+    if (c->d_bits) return true;
+    const bool planned = lwacm::march_plan_fits(c->p, c->ncu);
+    const size_t at = ((size_t)c->p.n + 3) / 4 * 4;
+    const size_t words = at + (planned ? 4 * (size_t)c->ncu : 0);
+    bool ok = hipMalloc(&c->d_bits, words * sizeof(unsigned)) == hipSuccess;
+    if (ok && moving_walls(c))
+        ok = hipMalloc(&c->d_wallg, (size_t)c->p.n * sizeof(float4)) == hipSuccess;
+    if (ok) ok = hipMalloc(&c->d_twall, (size_t)c->p.n * sizeof(uint2)) == hipSuccess;
+    if (ok && planned)
+        ok = lwacm::launch_classify(c->p, nullptr, c->d_bits, nullptr, c->stream) == hipSuccess &&
+             make_march_plan(c, c->d_bits + at) == hipSuccess;
+    if (!ok) {
+        (void)hipGetLastError();
+        c->p.march_plan = nullptr;
+        free(c->h_plan);
+        c->h_plan = nullptr;
+        if (c->d_bits) (void)hipFree(c->d_bits);
+        if (c->d_wallg) (void)hipFree(c->d_wallg);
+        if (c->d_twall) (void)hipFree(c->d_twall);
+        c->d_bits = nullptr;
+        c->d_wallg = nullptr;
+        c->d_twall = nullptr;
+    }
+    return ok;
 }
 
 // Interpolated walls or link velocities on the D3Q19 tile kernels: the wall
@@ -686,16 +760,15 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
             }
             c->n_fluid = scan[1];
         }
-        if (e == hipSuccess && lwacm::column_supported(p)) {  // D3Q19
-            bool moving = false;
-            for (int m = 1; m < lwacm::kMaxWallIds; ++m)
-                for (int k = 0; k < 3; ++k) moving = moving || p.wall_u[m][k] != 0.0f;
+        if (e == hipSuccess && (lwacm::march_supported(unforced) ||
+                                lwacm::adj_march_supported(unforced)) &&
+            lwacm::march_aligned(p)) {
             // behind the classes: the tiles' wall counts, then the list of chunks
             const bool planned = lwacm::march_plan_fits(unforced, c->ncu);
             const size_t at = ((size_t)p.n + 15) / 16 * 16;
             e = hipMalloc(&c->d_cls, planned ? at + (size_t)c->ncu * sizeof(int4) : (size_t)p.n);
             if (e == hipSuccess) e = hipMalloc(&c->d_bits, (size_t)p.n * sizeof(unsigned));
-            if (e == hipSuccess && moving)
+            if (e == hipSuccess && moving_walls(c))
                 e = hipMalloc(&c->d_wallg, (size_t)p.n * sizeof(float4));
             if (e != hipSuccess) {
                 free_scratch(c);
@@ -719,19 +792,12 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
             return rc;
         }
     }
-    if (d_mask && lwacm::column_supported(p) &&
-        (!lwacm::march_aligned(p) || !lwacm::march_supported(unforced))) {
-        // the column kernels' list of nodes next to a wall (without it the
-        // problem runs on the generic kernel)
-        const int rc = ensure_wall_list(c);
-        const size_t lb = rc == LWACM_OK ? lwacm::column_num_blocks(p, c->n_wlist) : 0;
-        if (lb > c->n_partial_blocks) {
-            double *grown = nullptr;
-            if (hipMalloc(&grown, 8 * lb * sizeof(double)) == hipSuccess) {
-                (void)hipFree(c->d_partials);
-                c->d_partials = grown;
-                c->n_partial_blocks = lb;
-            }
+    if (d_mask && lwacm::column_supported(p) && !lwacm::march_aligned(p)) {
+        const int rc = make_column_tables(c);
+        if (rc != LWACM_OK) {
+            free_scratch(c);
+            delete c;
+            return rc;
         }
     }
     *out = c;
@@ -862,17 +928,18 @@ int lwacm_set_thermal(lwacm_ctx *c, double omega_t, float *d_T_a, float *d_T_b,
         t.wall_T[m] = m < n_wall_T ? h_wall_T[m] : __builtin_nanf("");
     // walls on a D3Q19 flow: the table of fixed-temperature wall links that
     // the flow kernel's fused temperature step reads
-    if (c->p.mask && c->p.Q == 19 && c->d_bits) {
+    if (c->p.mask && c->p.Q == 19 && lwacm::march_aligned(c->p) && c->d_bits) {
         if (!c->d_twall &&
             hipMalloc(&c->d_twall, sizeof(uint2) * (size_t)c->p.n) != hipSuccess) {
             c->d_twall = nullptr;
             return LWACM_ENOMEM;
         }
-        // (sides that are no multiples of the tile: made by lwacm_step, follow_mask)
-        if (lwacm::march_aligned(c->p) &&
-            lwacm::launch_thermal_wall_table(t, c->d_bits, c->d_twall, c->stream) != hipSuccess)
+        if (lwacm::launch_thermal_wall_table(t, c->d_bits, c->d_twall, c->stream) != hipSuccess)
             return LWACM_EDEVICE;
         c->p.T_wall = c->d_twall;
+    } else if (c->p.mask && c->storage == LWACM_FP32 && lwacm::march_supported(c->p) &&
+               make_follow_tables(c)) {
+        c->p.T_wall = c->d_twall;  // filled by lwacm_step (follow_mask)
     }
     c->T_buf[0] = d_T_a;
     c->T_buf[1] = d_T_b;

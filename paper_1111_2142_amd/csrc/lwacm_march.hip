@@ -611,7 +611,7 @@ int rolled_nzc(const ProblemArgs &p)
 // flag bit is set and wallg holds sum_i 36 w_i (v_i . u_w(x - v_i)) times
 // (1, v_i) over its bounce-back links: the moving-wall term per unit of
 // (1 - a) 6 rho0, which depends on the geometry only.
-// FOLLOW (launch_follow_mask): all but the classes, for the mask as it is: also
+// A table that is null is left out.  FOLLOW (launch_follow_mask): all but the classes, for the mask as it is: also
 // the fixed-temperature wall links (the sums of k_thermal_wall_table), and the
 // solid nodes' state in the buffer that the next step writes.
 template <bool FOLLOW>
@@ -634,8 +634,8 @@ __global__ __launch_bounds__(256) void k_classify(ProblemArgs p, uint8_t *cls, u
             ms[i] = p.mask[((unsigned)uz * p.ny + uy) * p.nx + ux];
         }
         if (ms[0] != 0) {
-            if (!FOLLOW) cls[idx] = 2;
-            bits[idx] = 1u;  // bit 0 (the rest link, never a bounce-back link): solid
+            if (cls) cls[idx] = 2;
+            if (bits) bits[idx] = 1u;  // bit 0 (the rest link, never a bounce-back link): solid
             if (FOLLOW) {
                 f.T_wall[idx] = make_uint2(0u, 0u);
                 f.other[idx] = f.state[idx];
@@ -682,10 +682,9 @@ __global__ __launch_bounds__(256) void k_classify(ProblemArgs p, uint8_t *cls, u
                 }
             }
             f.T_wall[idx] = make_uint2(fb, __builtin_bit_cast(unsigned, tw));
-        } else {
-            cls[idx] = bb ? 1 : 0;
         }
-        bits[idx] = bb;
+        if (cls) cls[idx] = bb ? 1 : 0;
+        if (bits) bits[idx] = bb;
     }
 }
 
@@ -1048,7 +1047,8 @@ hipError_t launch_fwd_march(const ProblemArgs &p, int storage, const void *src, 
                             const uint8_t *cls, const unsigned *bits, const float4 *wallg,
                             const ReduceArgs &r, hipStream_t s)
 {
-    if (!march_supported(p) || (p.mask && (!cls || !bits))) return hipErrorNotSupported;
+    if (!march_supported(p) || (p.mask && (!bits || (p.nz < 8 && !cls))))
+        return hipErrorNotSupported;
     if (p.T_in && (!p.T_out || !march_thermal_supported(p))) return hipErrorNotSupported;
     if (!march_aligned(p) && (storage || !p.T_in)) return hipErrorNotSupported;
     return storage ? dispatch<__half>(p, src, dst, cls, bits, wallg, r, s)
