@@ -41,6 +41,21 @@ static_assert(2 * TX <= kWave && 2 * (TY + 2) <= kWave, "halo rows must fit one 
 
 enum Role { INTERIOR = 0, HALO_Y = 1, HALO_X = 2 };
 
+// The plane loop; TAIL 0: grids of fewer than eight planes (n <= 9), too short for
+// plane_loop, unrolled.
+template <int TAIL, class F>
+__device__ __forceinline__ void adj_loop(int n, F &&body)
+{
+    if constexpr (TAIL != 0) {
+        plane_loop<TAIL>(n, body);
+    } else {
+        static_for<9>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            if (k < n) body(k, PlaneIter<k % 3, (k < 5 ? k : 5), true>{});
+        });
+    }
+}
+
 // XOUT (no walls): the factors (rho, x) of the nodes' dL/da = rho x go to xout
 // (n pairs) instead of into block partials; chunks of any depth then give the same sums
 // (k_adj_dadomega adds them).
@@ -102,7 +117,8 @@ __global__ __launch_bounds__((NTHREADS), (PAIR ? 6 : 1)) void k_adj_march(Proble
     const int slot = (ly + 1) * SX + (lx + 1);
     const int wslot = active ? slot : NSLOT;
 
-    auto wrapz = [&](int pz) { return wrap_index(pz, nz); };
+    // (fewer than eight planes: loads past the chunk stay at its upper end)
+    auto wrapz = [&](int pz) { return wrap_index(TAIL ? pz : min(pz, z0 + nzc), nz); };
     constexpr unsigned NB = StateIO<T>::kNodeBytes;
     const Rsrc rmu = make_rsrc(mu_in, (unsigned long long)n * 16u);
     const Rsrc rst = make_rsrc(state, (unsigned long long)n * NB);
@@ -153,7 +169,7 @@ __global__ __launch_bounds__((NTHREADS), (PAIR ? 6 : 1)) void k_adj_march(Proble
     };
 
     if (role == INTERIOR) {
-        plane_loop<TAIL>(N, [&](int k, auto kc) {
+        adj_loop<TAIL>(N, [&](int k, auto kc) {
             using I = decltype(kc);
             constexpr int jm = (I::j + 2) % 3;
             enter(k, I{});
@@ -198,7 +214,7 @@ __global__ __launch_bounds__((NTHREADS), (PAIR ? 6 : 1)) void k_adj_march(Proble
             if (I::refill) load_state(jm, z0 + 1 + k);
         });
     } else {
-        plane_loop<TAIL>(N, [&](int k, auto kc) {
+        adj_loop<TAIL>(N, [&](int k, auto kc) {
             enter(k, kc);
             __syncthreads();
         });
@@ -246,6 +262,12 @@ void launch_t(const ProblemArgs &p, int c, unsigned nb, const T *st, const float
               float *mu_out, const unsigned *bits, const float4 *wallg, float2 *x,
               const ReduceArgs &r, hipStream_t s)
 {
+    if constexpr (!XOUT && !PAIR) {
+        if (c < 8) {
+            k_adj_march<T, 0, MASK, FINAL, XOUT, PAIR><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r);
+            return;
+        }
+    }
     // a loop of c + 2 iterations, its tail 3 + (c + 2) % 3
     switch ((c + 2) % 3) {
     case 0: k_adj_march<T, 3, MASK, FINAL, XOUT, PAIR><<<nb, NTHREADS, 0, s>>>(p, c, st, mu_in, mu_out, bits, wallg, x, r); break;
@@ -267,7 +289,7 @@ void dispatch(const ProblemArgs &p, const void *state, const float *mu_in, float
         return;
     }
     // one round of two workgroups a CU, a sixteenth of it or less empty
-    const bool pair = 8LL * nb > 15LL * p.ncu && nb <= 2LL * p.ncu;
+    const bool pair = c >= 8 && 8LL * nb > 15LL * p.ncu && nb <= 2LL * p.ncu;
     if (p.mask) {
         if (pair) launch_t<T, true, FINAL, false, true>(p, c, nb, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
         else launch_t<T, true, FINAL, false, false>(p, c, nb, st, mu_in, mu_out, bits, wallg, nullptr, r, s);
@@ -282,7 +304,7 @@ void dispatch(const ProblemArgs &p, const void *state, const float *mu_in, float
 bool adj_march_supported(const ProblemArgs &p)
 {
     return p.Q == 19 && p.nx >= TX && p.ny >= TY && p.nx % TX == 0 && p.ny % TY == 0 &&
-           p.nz >= 8 && p.n < (1LL << 28);
+           p.nz >= 1 && p.n < (1LL << 28);
 }
 
 // Chunk depth: 64 planes.  A thread sums its planes' dL/da in FP32, so the

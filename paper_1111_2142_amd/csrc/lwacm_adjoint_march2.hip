@@ -255,7 +255,10 @@ void dispatch(const ProblemArgs &p, const void *sa, const void *sb, const float 
 
 }  // namespace
 
-bool adj_march2_supported(const ProblemArgs &p) { return adj_march_supported(p) && !p.mask; }
+bool adj_march2_supported(const ProblemArgs &p)
+{
+    return adj_march_supported(p) && !p.mask && p.nz >= 8;
+}
 
 int adj2_depth(const ProblemArgs &p)
 {

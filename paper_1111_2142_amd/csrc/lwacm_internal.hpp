@@ -186,7 +186,7 @@ struct FollowMask {
 hipError_t launch_follow_mask(const ProblemArgs &p, unsigned *bits, float4 *wallg,
                               const FollowMask &f, hipStream_t s);
 // D3Q19 reverse step as a z-marching tile kernel (any mask, with or without
-// force, nz >= 8); mu_in / mu_out node-interleaved, or field-major output when
+// force); mu_in / mu_out node-interleaved, or field-major output when
 // final_t0.  Masked problems need the bit sets (and wallg for moving walls)
 // of launch_classify.
 bool adj_march_supported(const ProblemArgs &p);
