@@ -65,8 +65,16 @@ constexpr int multi_threads(int MT, int rows)
 // more than one round, workgroups of 512 run in pairs, and one's arithmetic
 // fills the other's barriers and LDS reads (eight steps with walls at 520^2 38.2
 // -> 31.3 us, at 1501 x 1003 107 -> 82; omega_p at 1024^2 62.8 -> 50.7; a single
-// round is as fast with 1024, and the plain update fits twice as it is).
-constexpr bool fwd_pair(int MT, bool MASK, bool SPLIT) { return MT == 32 && (MASK || SPLIT); }
+// round is as fast with 1024, and the plain update fits twice as it is).  Not with
+// a force field (92 KB of LDS: one workgroup a CU either way) nor with walls, a
+// force and omega_p together (136 VGPRs, three waves a SIMD): in pairs of which
+// only one runs, eight steps at 520^2 with walls and a field took 57 us, now 49;
+// with omega_p beside them 75, now 63; walls, a force and omega_p 74, now 62.
+constexpr bool fwd_pair(int MT, bool MASK, int FORCE, bool SPLIT)
+{
+    return MT == 32 && (MASK || SPLIT) && FORCE < 2 && !(MASK && FORCE && SPLIT);
+}
+constexpr unsigned kLdsPerCu = 160 * 1024;
 
 // v in [-MK, n + MT + MK) wrapped into [0, n)
 template <int MT>
@@ -204,6 +212,9 @@ __global__ __launch_bounds__((multi_threads(MT, fwd_rows(MT, MASK)) >> PAIR)) vo
     constexpr int NQ = QW ? NREG : 1;
     __shared__ float ca[QW ? 8 : 1][NQ], wv[QW ? 8 : 1][NQ];
     __shared__ unsigned modes[NQ];
+    static_assert(!PAIR || 2 * (sizeof(buf) + sizeof(gf) + sizeof(wtab) + sizeof(wtab_p) +
+                                sizeof(ca) + sizeof(wv) + sizeof(modes)) <= kLdsPerCu,
+                  "two workgroups share a CU");
     const int ntx = (p.nx + MT - 1) / MT;
     const int tile_x0 = (int)(blockIdx.x % ntx) * MT;
     const int tile_y0 = (int)(blockIdx.x / ntx) * MT;
@@ -627,7 +638,7 @@ void fwd_multi(const ProblemArgs &p, unsigned nb, const MultiFwd &f, const Reduc
                hipStream_t s)
 {
     constexpr int nt = multi_threads(MT, fwd_rows(MT, MASK));
-    if constexpr (fwd_pair(MT, MASK, SPLIT))
+    if constexpr (fwd_pair(MT, MASK, FORCE, SPLIT))
         if (p.multi_many) {
             k_fwd_d2q9_multi<MT, MASK, FORCE, SPLIT, QW, true><<<nb, nt / 2, 0, s>>>(
                 p, f.src, f.dst, f.ksteps, r, f.slots, f.slot_floats);
