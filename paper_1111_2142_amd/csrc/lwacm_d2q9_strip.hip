@@ -198,19 +198,20 @@ long long strip_waves(const ProblemArgs &p, int rows)
 
 bool d2q9_strip_supported(const ProblemArgs &p)
 {
-    return p.Q == 9 && p.nz == 1 && !p.mask && !p.has_force && p.strip_rows > 0;
+    return p.Q == 9 && p.nz == 1 && !p.mask && !p.has_force && p.strip_rows[p.split] > 0;
 }
 
 // Rows per wave: a SIMD's waves run one after the other, each (rows + 8) rows long
 // (the levels' start costs about eight), so the least ceil(waves / SIMDs) *
-// (rows + 8).  Eight steps take 10.6 + 1.085 us times that (with omega_p 10.7 +
-// 1.55); on tiles of 32, which run a round of one per CU at a time, 6 + 10 us
-// times the rounds (with omega_p 5 + 11.4), so strips are taken where
-// cost + 5 < 9 rounds.  Tiles / strips: 512^2 17.5 / 24.9, 600^2 26.3 / 27.7,
-// 1024 x 512 25.2 / 32.3, 724^2 36.6 / 32.3, 1024^2 44.3 / 44.5, 1501 x 1003 63.0
-// / 54.0, 2000^2 156 / 114, 4096^2 608 / 392; with omega_p 1501 x
-// 1003 71 / 73, 2000^2 183 / 158.
-int d2q9_strip_choose_rows(const ProblemArgs &p, int ncu)
+// (rows + 8).  Eight steps take 10.6 + 1.085 us times that (with omega_p 11 +
+// 1.63); on tiles of 32, which run a round of one per CU at a time, 6 + 10 us
+// times the rounds (with omega_p 5 + 12), so strips are taken where
+// cost + 5 < 9 rounds, with omega_p where 1.63 cost + 6 < 12 rounds.  Tiles / strips:
+// 512^2 17.5 / 24.9, 600^2 26.3 / 27.7, 1024 x 512 25.2 / 32.3, 724^2 36.6 / 32.3,
+// 1024^2 44.3 / 44.5, 1501 x 1003 63.0 / 54.0, 2000^2 156 / 114, 4096^2 608 / 392;
+// with omega_p 724^2 43.4 / 43.6, 961 x 1009 55.4 / 59.6, 1501 x 1003 80.3 / 76.8,
+// 2000^2 188 / 161.
+int d2q9_strip_choose_rows(const ProblemArgs &p, int ncu, bool split)
 {
     if (ncu < 1) ncu = 1;
     int best = 0;
@@ -225,12 +226,14 @@ int d2q9_strip_choose_rows(const ProblemArgs &p, int ncu)
         }
     }
     const long long tiles = ((p.nx + 31LL) / 32) * ((p.ny + 31LL) / 32);
-    return best_cost + 5 < 9 * ((tiles + ncu - 1) / ncu) ? best : 0;
+    const long long rounds = (tiles + ncu - 1) / ncu;
+    const bool strips = split ? 163 * best_cost + 600 < 1200 * rounds : best_cost + 5 < 9 * rounds;
+    return strips ? best : 0;
 }
 
 unsigned d2q9_strip_num_blocks(const ProblemArgs &p)
 {
-    return (unsigned)((strip_waves(p, p.strip_rows) + WPB - 1) / WPB);
+    return (unsigned)((strip_waves(p, p.strip_rows[p.split]) + WPB - 1) / WPB);
 }
 
 hipError_t launch_fwd_d2q9_strip(const ProblemArgs &p, const float *src, float *dst,
@@ -238,8 +241,8 @@ hipError_t launch_fwd_d2q9_strip(const ProblemArgs &p, const float *src, float *
 {
     if (!d2q9_strip_supported(p)) return hipErrorInvalidValue;
     const unsigned nb = d2q9_strip_num_blocks(p);
-    if (p.split) k_fwd_d2q9_strip<true><<<nb, NT, 0, s>>>(p, src, dst, p.strip_rows, r);
-    else k_fwd_d2q9_strip<false><<<nb, NT, 0, s>>>(p, src, dst, p.strip_rows, r);
+    if (p.split) k_fwd_d2q9_strip<true><<<nb, NT, 0, s>>>(p, src, dst, p.strip_rows[p.split], r);
+    else k_fwd_d2q9_strip<false><<<nb, NT, 0, s>>>(p, src, dst, p.strip_rows[p.split], r);
     return hipGetLastError();
 }
 

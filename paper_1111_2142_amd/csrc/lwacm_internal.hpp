@@ -56,7 +56,7 @@ struct ProblemArgs {
     int col_nzc;             // planes per workgroup of the column kernels (0: unused)
     int multi_tile;          // tile side of the multi-step D2Q9 kernels (0: unused)
     int multi_many;          // more such tiles than CUs
-    int strip_rows;          // rows per wave of the D2Q9 strip kernel (0: unused)
+    int strip_rows[2];       // rows per wave of the D2Q9 strip kernel, without and with split (0: unused)
     // the temperature step fused into the single-step tile kernel (thermal
     // problems, march_thermal_supported): T at the step's time and one step
     // later, h = 2/omega_t - 1 and kap = 2 - 2/omega_t; T_in null: no fusion
@@ -255,9 +255,10 @@ hipError_t launch_adj_d2q9_multi(const ProblemArgs &p, const float *states, size
                                  float *mu_out, double *partials, size_t stride, unsigned slice0,
                                  hipStream_t s);
 // kMultiSteps D2Q9 steps per launch as marching strips of columns in registers
-// (FP32, no walls, no force; p.strip_rows > 0): bitwise the same fields.
+// (FP32, no walls, no force; p.strip_rows[p.split] > 0): bitwise the same fields.
 bool d2q9_strip_supported(const ProblemArgs &p);
-int d2q9_strip_choose_rows(const ProblemArgs &p, int ncu);  // 0: the tile kernels are as fast
+// 0: the tile kernels are as fast
+int d2q9_strip_choose_rows(const ProblemArgs &p, int ncu, bool split);
 unsigned d2q9_strip_num_blocks(const ProblemArgs &p);
 hipError_t launch_fwd_d2q9_strip(const ProblemArgs &p, const float *src, float *dst,
                                  const ReduceArgs &r, hipStream_t s);
