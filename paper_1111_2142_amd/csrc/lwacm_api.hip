@@ -245,37 +245,33 @@ bool fuses_thermal(const lwacm_ctx *c)
 // Grids whose sides are no multiples of the 32 x 16 tile run the tile kernel
 // with a temperature (FP32 state), where it replaces two gather kernels: with walls at every
 // size (22 -> 14 us a step at 33x17x8, 99 -> 25 at 100^3, 258 -> 52 at 150^3),
-// without from about 10^5 nodes on (its shortest chunk takes 11 us on any
-// grid: 10.2 against 10.9 us at 33x17x40, 12.6 / 11.1 at 50^3, 40 / 17.6 at
-// 100^3, gather / tiles).  Without a temperature they stay on the gather
+// without from about 390 nodes a CU on (its shortest chunk takes 11 us on any
+// grid: 10.2 against 10.9 us at 33x17x40, 11.2 / 11.1 at 47x46x46, 12.6 / 12.4 at
+// 33x17x200, 12.0 / 11.0 at 50^3, 40 / 17.6 at 100^3, gather / tiles).  Without a temperature they stay on the gather
 // kernels, whose results the tile kernels reproduce only to FP32 rounding.
 bool use_march(const lwacm_ctx *c)
 {
     if (c->variant == LWACM_KERNEL_GENERIC || c->semi_implicit) return false;
     if (!lwacm::march_supported(c->p)) return false;
     return lwacm::march_aligned(c->p) ||
-           (c->storage == LWACM_FP32 && fuses_thermal(c) && (c->p.mask || c->p.n >= 100000));
+           (c->storage == LWACM_FP32 && fuses_thermal(c) &&
+            (c->p.mask || c->p.n >= 390LL * c->ncu));
 }
 
-// The other D3Q19 problems: column-marching gathers, with walls once the wall
-// list is there (a step at 33x17x8 7.8 us against the generic kernel's 13.2, at
-// 150x84x75 with link distances and a force 19 against 73).  Without walls the
-// generic kernel is the faster one on small grids: 6.1 against 6.0 us at 33x17x8,
-// 7.9 / 6.6 at 50^3, 11.8 / 9.0 at 75^3; FP16 6.7 / 7.4 at 50^3, 13.5 / 11.5 at 75^3; reverse
-// 6.3 / 7.9 at 33^3, 9.1 / 8.6 at 50^3, 16.0 / 13.0 at 75^3 (generic / columns).
+// The other D3Q19 problems: column-marching gathers, with walls once the classes
+// and the wall list are there.
 bool use_column(const lwacm_ctx *c)
 {
     return c->variant == LWACM_KERNEL_AUTO && !c->semi_implicit && !use_march(c) &&
-           lwacm::column_supported(c->p) &&
-           (c->p.mask ? c->column_tables
-                      : c->p.n >= (c->storage == LWACM_FP32 ? 100000 : 250000)) &&
+           lwacm::column_supported(c->p) && (!c->p.mask || c->column_tables) &&
+           lwacm::column_pays(c->p, c->storage, false) &&
            lwacm::column_num_blocks(c->p, c->n_wlist) <= most_blocks(c);
 }
 
 bool use_adj_column(const lwacm_ctx *c)
 {
     return c->variant == LWACM_KERNEL_AUTO && !lwacm::adj_march_supported(c->p) && !c->p.mask &&
-           lwacm::column_supported(c->p) && c->p.n >= 100000 &&
+           lwacm::column_supported(c->p) && lwacm::column_pays(c->p, c->storage, true) &&
            lwacm::column_num_blocks(c->p, 0) <= c->n_partial_blocks;
 }
 
@@ -793,7 +789,8 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
             return rc;
         }
     }
-    if (d_mask && lwacm::column_supported(p) && !lwacm::march_aligned(p)) {
+    if (d_mask && lwacm::column_supported(p) && !lwacm::march_aligned(p) &&
+        lwacm::column_pays(p, storage, false)) {
         const int rc = make_column_tables(c);
         if (rc != LWACM_OK) {
             free_scratch(c);
@@ -1540,7 +1537,7 @@ int lwacm_step_static(int lattice, int nx, int ny, int nz, double omega, float *
     set_wall_terms(&c);
     // the partial sets of the kernels lwacm_step may launch must fit the scratch
     size_t nb = lwacm::generic_grid(p.n);
-    const int ncu = device_cus();
+    const int ncu = p.ncu = device_cus();
     if (lwacm::march_supported(p) && lwacm::march_aligned(p)) {
         set_march_depths(&p.march_deep, p, ncu);
         const size_t sb = lwacm::march_scratch_blocks(p, ncu);

@@ -596,6 +596,35 @@ int column_choose_depth(const ProblemArgs &p, int ncu)
     return (p.nz + m - 1) / m;
 }
 
+// Where the columns beat one thread per node.  What they load beyond the nodes'
+// own planes is the lanes past a small plane's end and two planes a chunk: over =
+// loaded / own.  Generic / columns, us a step:
+//   without walls, FP32   41^3 (over 2.2) 6.75 / 6.72, 49^3 7.3 / 6.4, 57^3 8.8 / 7.0,
+//     76^3 11.2 / 8.7; 2 x 800 x 801 (2.0) 27.6 / 20.7, 3 x 250 x 251 (2.3) 9.6 / 7.9,
+//     1 x 800 x 801 (3.0) 14.3 / 20.0, 4000 x 8 x 9 (5.3) 8.6 / 10.6, 20000 x 3 x 3 6.7 / 35
+//   FP16   57^3 7.2 / 8.0, 65^3 9.0 / 10.1, 76^3 12.5 / 10.2, 4 x 300 x 301 (1.5) 11.5 /
+//     10.1, 3000 x 17 x 17 (2.1) 18.0 / 18.8, 1500 x 23 x 23 (1.8) 16.8 / 16.6
+//   reverse, FP32   49^3 8.07 / 8.14, 57^3 10.5 / 9.8, 76^3 15.3 / 12.3, 3 x 250 x 251
+//     9.6 / 10.6, 1 x 800 x 801 19.7 / 34, 2 x 800 x 801 35.9 / 39.1; FP16   65^3 12.9 /
+//     13.3, 76^3 14.9 / 13.9
+//   walls and a force, FP32 (FP16 alike)   9^3 12.9 / 10.0, 33^3 13.8 / 9.8, 100^3 58.5 /
+//     18.1, 1 x 400 x 401 17.4 / 10.5, 1000 x 9 x 9 (6.3) 15.2 / 11.0, 20000 x 5 x 5
+//     (10.7) 30 / 51, 9001 x 3 x 3 12 / 22
+// Below some nodes a CU (at 256 CUs 10^5 for the FP32 step, 1.3 10^5 for its
+// reverse, 3.6 10^5 in FP16) both take a launch's latency and the simple kernel
+// starts sooner.
+bool column_pays(const ProblemArgs &p, int storage, bool reverse)
+{
+    const double plane = (double)p.nx * p.ny;
+    const double groups = (double)(((long long)p.nx * p.ny + NT - 1) / NT);
+    const double chunks = (double)((p.nz + p.col_nzc - 1) / p.col_nzc);
+    const double over = groups * NT / plane * (p.nz + 2.0 * chunks) / p.nz;
+    if (p.mask) return over <= 8.0;
+    const long long per_cu = p.n / (p.ncu > 0 ? p.ncu : 1);
+    if (storage) return per_cu >= 1400 && over <= 1.8;
+    return reverse ? per_cu >= 500 && over <= 2.3 && p.nz >= 4 : per_cu >= 390 && over <= 2.4;
+}
+
 unsigned column_num_blocks(const ProblemArgs &p, unsigned nlist)
 {
     return column_blocks(p, p.col_nzc) + (p.mask ? wall_blocks(nlist) : 0u);

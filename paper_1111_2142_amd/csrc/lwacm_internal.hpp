@@ -122,6 +122,7 @@ hipError_t launch_adj_generic(const ProblemArgs &p, int storage, const void *sta
 // next to a wall; the reverse step takes problems without walls.
 bool column_supported(const ProblemArgs &p);
 int column_choose_depth(const ProblemArgs &p, int ncu);  // planes per chunk
+bool column_pays(const ProblemArgs &p, int storage, bool reverse);  // against the generic kernels
 unsigned column_num_blocks(const ProblemArgs &p, unsigned nlist);
 hipError_t launch_fwd_column(const ProblemArgs &p, int storage, const void *src, void *dst,
                              const uint8_t *cls, const unsigned *list, unsigned nlist,
