@@ -300,8 +300,6 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march2(ProblemArgs p, int dept
         });
     }
 
-    // columns shared with the tile before (a ragged side) are its to count
-    if (gx < ti.xs || gy < ti.ys) m1 = e1 = m2 = e2 = 0.0f;
     sums[0] += (double)m1;
     sums[1] = 0.5 * (sums[1] + (double)e1);
     sums[2] += (double)m2;
@@ -360,7 +358,7 @@ hipError_t launch_fwd_march2(const ProblemArgs &p, const float *src, float *dst,
                              const unsigned *bb_bits, const float4 *wallg, const ReduceArgs &r,
                              hipStream_t s)
 {
-    if (!march2_supported(p) || !r.partials_b) return hipErrorNotSupported;
+    if (!march2_supported(p) || !march_aligned(p) || !r.partials_b) return hipErrorNotSupported;
     if (p.mask && !bb_bits) return hipErrorInvalidValue;  // the link sets come from k_classify
     if (p.mask) return launch_march2_t<true, false>(p, src, dst, bb_bits, wallg, r, s);
     return march_deep(p) ? launch_march2_t<false, true>(p, src, dst, nullptr, nullptr, r, s)
