@@ -698,8 +698,7 @@ int lwacm_init(lwacm_ctx **out, int lattice, int nx, int ny, int nz, double omeg
         p.multi_tile = 16;  // the most blocks: link velocities, which may be set later
         const size_t qb = d_mask ? lwacm::d2q9_multi_num_blocks(p) : 0;
         lwacm::d2q9_multi_choose_tile(p, c->ncu);
-        for (int split = 0; split < 2; ++split)
-            p.strip_rows[split] = lwacm::d2q9_strip_choose_rows(p, c->ncu, split != 0);
+        lwacm::d2q9_strip_choose_rows(p, c->ncu);
         const size_t tb = lwacm::d2q9_multi_num_blocks(p);
         nb = qb > nb ? qb : nb;
         nb = tb > nb ? tb : nb;
@@ -1548,7 +1547,7 @@ int lwacm_step_static(int lattice, int nx, int ny, int nz, double omega, float *
     if (nb > kStaticMaxBlocks) return LWACM_ESCRATCH;
     if (lattice == LWACM_D2Q9) {
         lwacm::d2q9_multi_choose_tile(p, ncu);
-        p.strip_rows[0] = lwacm::d2q9_strip_choose_rows(p, ncu, false);
+        lwacm::d2q9_strip_choose_rows(p, ncu);
     } else p.col_nzc = lwacm::column_choose_depth(p, ncu);
     double *base = nullptr;
     const int rc = static_scratch(&base);

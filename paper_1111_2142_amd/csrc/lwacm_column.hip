@@ -118,8 +118,9 @@ struct WallList {
 };
 
 // Solid or fluid in the mask where the classes say otherwise?  Bound by the
-// launch: 3.5 us a call (not a step) at 33x17x8 and at 150x84x75, where the flag's
-// read takes another 0.3 us a step (8.2 -> 8.6, 16.9 -> 17.2).
+// launch: 3.5 us a call (not a step) at 33x17x8 and at 150x84x75.  A step asks the
+// flag: 8.2 -> 8.4 us at 33x17x8; at 150x84x75 15.2 -> 15.5, with a force 16.2 as
+// before, with a field 19.5 -> 20.1 (two registers more are spilled).
 __global__ __launch_bounds__(NT) void k_mask_check(const uint8_t *__restrict__ mask,
                                                    const uint8_t *__restrict__ cls, unsigned n,
                                                    unsigned *edited)
@@ -261,22 +262,6 @@ __global__ __launch_bounds__((NT), (fwd_waves(MASK, FORCE))) void k_fwd_column(P
             gather_node<T, FORCE != 0, false>(p, moving ? table : nullptr, src, idx, out, e);
             if (!edited) store_gathered<T, SR>(p, dst, idx, out, e, acc);
         }
-    } else if (MASK && __builtin_amdgcn_readfirstlane(edited) != 0u) {
-        // every node of the columns by the mask as it is
-        __shared__ float table[kMaxWallIds][3];
-        const bool moving = load_wall_table(p, table);
-        const ColumnIdx ci = column_of(p, nzc, blockIdx.x - first, gridDim.x - first);
-#pragma unroll 1
-        for (int z = ci.z0; z < ci.z1 && ci.active; ++z) {
-            const unsigned idx = (unsigned)z * plane + ci.col[0];
-            float out[4], e;
-            if (gather_node<T, FORCE != 0, true>(p, moving ? table : nullptr, src, idx, out, e)) {
-                store_gathered<T, SR>(p, dst, idx, out, e, acc);
-            } else {  // solid: written through
-                using Raw = typename BufIO<T>::Raw;
-                reinterpret_cast<Raw *>(dst)[idx] = reinterpret_cast<const Raw *>(src)[idx];
-            }
-        }
     } else {
         const ColumnIdx ci = column_of(p, nzc, blockIdx.x - first, gridDim.x - first);
         constexpr unsigned NB = BufIO<T>::kNodeBytes;
@@ -409,6 +394,26 @@ __global__ __launch_bounds__((NT), (fwd_waves(MASK, FORCE))) void k_fwd_column(P
             load(a, ci.z0 + k + 1);
             __builtin_amdgcn_sched_barrier(0);
             process(b, ci.z0 + k);
+        }
+        if (MASK && __builtin_amdgcn_readfirstlane(edited) != 0u) {
+            // every node of the columns again, by the mask as it is and by the
+            // thread that stored it above (asked for last: before the planes the
+            // flag's latency cost a step 0.3 us)
+            __shared__ float table[kMaxWallIds][3];
+            const bool moving = load_wall_table(p, table);
+            acc[0] = acc[1] = 0.0;
+#pragma unroll 1
+            for (int z = ci.z0; z < ci.z1 && ci.active; ++z) {
+                const unsigned idx = (unsigned)z * plane + ci.col[0];
+                float out[4], e;
+                if (gather_node<T, FORCE != 0, true>(p, moving ? table : nullptr, src, idx, out,
+                                                     e)) {
+                    store_gathered<T, SR>(p, dst, idx, out, e, acc);
+                } else {  // solid: written through
+                    using Raw = typename BufIO<T>::Raw;
+                    reinterpret_cast<Raw *>(dst)[idx] = reinterpret_cast<const Raw *>(src)[idx];
+                }
+            }
         }
     }
     store_block_partials<2>(acc, r.partials, blockIdx.x);

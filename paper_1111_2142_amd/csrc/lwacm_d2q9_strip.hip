@@ -211,7 +211,7 @@ bool d2q9_strip_supported(const ProblemArgs &p)
 // 1024^2 44.3 / 44.5, 1501 x 1003 63.0 / 54.0, 2000^2 156 / 114, 4096^2 608 / 392;
 // with omega_p 724^2 43.4 / 43.6, 961 x 1009 55.4 / 59.6, 1501 x 1003 80.3 / 76.8,
 // 2000^2 188 / 161.
-int d2q9_strip_choose_rows(const ProblemArgs &p, int ncu, bool split)
+void d2q9_strip_choose_rows(ProblemArgs &p, int ncu)
 {
     if (ncu < 1) ncu = 1;
     int best = 0;
@@ -227,8 +227,8 @@ int d2q9_strip_choose_rows(const ProblemArgs &p, int ncu, bool split)
     }
     const long long tiles = ((p.nx + 31LL) / 32) * ((p.ny + 31LL) / 32);
     const long long rounds = (tiles + ncu - 1) / ncu;
-    const bool strips = split ? 163 * best_cost + 600 < 1200 * rounds : best_cost + 5 < 9 * rounds;
-    return strips ? best : 0;
+    p.strip_rows[0] = best_cost + 5 < 9 * rounds ? best : 0;
+    p.strip_rows[1] = 163 * best_cost + 600 < 1200 * rounds ? best : 0;
 }
 
 unsigned d2q9_strip_num_blocks(const ProblemArgs &p)

@@ -258,8 +258,7 @@ hipError_t launch_adj_d2q9_multi(const ProblemArgs &p, const float *states, size
 // kMultiSteps D2Q9 steps per launch as marching strips of columns in registers
 // (FP32, no walls, no force; p.strip_rows[p.split] > 0): bitwise the same fields.
 bool d2q9_strip_supported(const ProblemArgs &p);
-// 0: the tile kernels are as fast
-int d2q9_strip_choose_rows(const ProblemArgs &p, int ncu, bool split);
+void d2q9_strip_choose_rows(ProblemArgs &p, int ncu);  // p.strip_rows, 0 where the tiles are as fast
 unsigned d2q9_strip_num_blocks(const ProblemArgs &p);
 hipError_t launch_fwd_d2q9_strip(const ProblemArgs &p, const float *src, float *dst,
                                  const ReduceArgs &r, hipStream_t s);
