@@ -509,7 +509,12 @@ __global__ __launch_bounds__(NTHREADS) void k_fwd_march_rolled(ProblemArgs p, in
                 sr_a += sr_da;
                 out = BufIO<T>::pack_sr(o.D, o.vx, o.vy, o.vz, st, h);
             } else {
-                out = BufIO<T>::pack(o.D, o.vx, o.vy, o.vz, st);
+                float vx = o.vx, vy = o.vy, vz = o.vz;
+                // rounded to FP32 first: with no scale to multiply by, the last FMA and
+                // the conversion to FP16 would become one instruction (v_fma_mixlo_f16)
+                // and round once, to other bits than the plain velocities'
+                if (UNITS) asm("" : "+v"(vx), "+v"(vy), "+v"(vz));
+                out = BufIO<T>::pack(o.D, vx, vy, vz, st);
             }
             const bool solid = MASK && Am.cls >= 2;
             if (MASK) {
