@@ -125,13 +125,16 @@ size_t lwacm_state_bytes(int lattice, int nx, int ny, int nz, int storage);
  *                 13 (-y+z), 14 (-z), 15 (-x-z), 16 (+x-z), 17 (-y-z), 18 (+y-z)
  *               (D2Q9: 0..8).  For q < 1/2 the rule also takes the
  *               node x - v_j; where that node is solid too, the halfway rule
- *               is used.  D3Q19 problems the tile kernels take run there
- *               (halfway terms plus a per-step correction of the fluid nodes
- *               next to a wall, made by a small kernel over those nodes);
- *               for them d_q is read once, here, like the mask: change
- *               neither afterwards.  Other problems run on the generic kernel,
- *               which reads d_q at every step.  The reverse steps return
- *               LWACM_EUNSUPPORTED.
+ *               is used.  The reverse steps return LWACM_EUNSUPPORTED.
+ *               On D3Q19 grids with nx a multiple of 32 and ny of 16 the mask
+ *               and d_q are read once, here: change neither afterwards.
+ *               (There the tile kernels run, with d_q as halfway terms plus a
+ *               per-step correction of the fluid nodes next to a wall, made by
+ *               a small kernel over those nodes.)  On all other grids each
+ *               call takes both as they are then, so they may be edited in
+ *               place between calls (mask values below n_wall_ids; the mass of
+ *               lwacm_diagnostics keeps counting the fluid nodes of this call);
+ *               a D3Q19 context whose mask was edited runs slower from then on.
  *  h_g          host body acceleration g[3] (Eq. force), or NULL; copied.
  *  stream       HIP stream every call of this context is issued on.
  *
@@ -187,7 +190,8 @@ int lwacm_set_variant(lwacm_ctx *c, int variant);
  * that minimises the plane steps per compute unit, ceil(workgroups / CUs) *
  * (depth + 10), with walls tile by tile (tiles next to walls cost more and take
  * shallower chunks); this call sets one depth for all (tuning, tests).  The
- * state does not depend on the depth. */
+ * state does not depend on the depth; mass and energy do in their last digits
+ * (a thread adds up its planes in FP32, see lwacm_step). */
 int lwacm_set_march_chunk(lwacm_ctx *c, int planes);
 
 /* Separate relaxation frequency omega_p of the continuity (density) update
@@ -204,8 +208,9 @@ int lwacm_set_march_chunk(lwacm_ctx *c, int planes);
  * (the default after lwacm_init) is the single-relaxation step; omega_p !=
  * omega with link-wall distances (d_q) or with wall velocities given link by
  * link gives LWACM_EUNSUPPORTED.  With omega_p != omega the forward step runs
- * on the single-step tile kernel (D3Q19 without walls, nz >= 8) or else on
- * the generic kernel (every lattice, walls and force allowed), never on the
+ * on the single-step tile kernel (D3Q19 without walls or force, nz >= 8), on
+ * the D2Q9 kernels that take several steps per launch (see lwacm_step) or else
+ * on the generic kernel (every lattice, walls and force allowed), never on the
  * two-step kernel, and the reverse steps return LWACM_EUNSUPPORTED.  Takes
  * effect from the next lwacm_step. */
 int lwacm_set_omega_p(lwacm_ctx *c, double omega_p);
@@ -219,7 +224,8 @@ int lwacm_set_omega_p(lwacm_ctx *c, double omega_p);
  * momentum of node x (Eq. force, with the density before the step).  A g that
  * changes in time is set before each lwacm_step(c, 1), with the field of the
  * step's starting time.  The forward step then runs on the single-step tile
- * kernel (D3Q19, nz >= 8, omega_p == omega) or else on the generic kernel,
+ * kernel (D3Q19, nz >= 8, omega_p == omega), on the kernels of the other D3Q19
+ * grids and of D2Q9 that take a uniform g too, or else on the generic kernel,
  * never on the two-step kernel; the reverse steps return LWACM_EUNSUPPORTED
  * while a field is set.  LWACM_EINVAL for a null context. */
 int lwacm_set_force_field(lwacm_ctx *c, const float *d_g);
@@ -249,9 +255,10 @@ int lwacm_set_semi_implicit(lwacm_ctx *c, int on);
  *         read only where x + v_j is solid.  It replaces the per-id table of
  *         lwacm_init for every wall while set; NULL returns to the table.
  * The forward step then runs on the D3Q19 tile kernels with the per-step
- * wall correction (as with d_q; the call synchronises the stream once to
- * set it up) or else on the generic kernel; the reverse steps return
- * LWACM_EUNSUPPORTED while it is set.  lwacm_wall_force leaves wall motion
+ * wall correction (as with d_q; the call synchronises the stream to set it
+ * up), on the kernels of the other D3Q19 grids and of D2Q9 with walls, or else
+ * on the generic kernel; the reverse steps return LWACM_EUNSUPPORTED while it
+ * is set.  lwacm_wall_force leaves wall motion
  * out (bodies at rest), so the links into the wall it is asked about must
  * carry zero velocity.  LWACM_EINVAL without a mask; LWACM_EUNSUPPORTED with
  * a separate omega_p. */
@@ -378,7 +385,8 @@ int lwacm_set_state(lwacm_ctx *c, const float *d_drho, const float *d_u);
  * wall rules), toggling the two state buffers.  Each step also reduces the
  * mass sum(rho) and kinetic energy 1/2 sum|u|^2 of its output over fluid
  * nodes in FP64 (per-block partials, fixed-order final sum: bitwise
- * reproducible); see lwacm_diagnostics.  Where LWACM_KERNEL_MARCH2 applies,
+ * reproducible; the D3Q19 tile kernels add up to 128 planes of a column in
+ * FP32 first); see lwacm_diagnostics.  Where LWACM_KERNEL_MARCH2 applies,
  * pairs of steps run as one launch (an odd count starts with a single step);
  * the state, the diagnostics and the history are the same as with single
  * steps.  D2Q9 problems in FP32 storage without a diagnostics history, a

@@ -1,6 +1,6 @@
 """Record counter-derived figures of a kernel in measured_traffic.json.
 
-    python -m paper_1111_2142_amd.record_traffic --kernel 'k_fwd_march2<3,false>' \
+    python -m paper_1111_2142_amd.record_traffic --kernel 'k_fwd_march2<3,false,false>' \
         --workload '...' --profile profiles/....md \
         --fetch F.csv --write W.csv [--valu V.csv] --copy-fetch CF.csv --copy-write CW.csv
 
