@@ -236,7 +236,8 @@ __device__ __forceinline__ void store_gathered(const ProblemArgs &p, T *dst, uns
 // overlapped the planes' arithmetic and a step took twice as long.
 // Three waves a SIMD (168 VGPRs): with walls and a force it took 170 and ran two
 // (150x84x75, sphere in a duct with distances and a uniform force 18.7 us a
-// step, now 15.8; force field 19.8, now 18.7).  Not for the force field
+// step, then 15.8; force field 19.8, then 18.7; 16.1 and 19.0 with the branch for
+// an edited mask, whose instances spill 2 to 9 VGPRs).  Not for the force field
 // without walls, which would spill eight VGPRs in the plane loop (14.5, held to
 // 168 16.7; 250^3 176, 209), nor the reverse step (19.7, held 22.1).
 constexpr int fwd_waves(bool MASK, int FORCE) { return MASK || FORCE < 2 ? 3 : 2; }
